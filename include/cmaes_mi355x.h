@@ -300,17 +300,20 @@ int cmaes_phase_times(const cmaes_t* h, double* out);
  * not used while phase or kernel timing is enabled, with caller-supplied z,
  * or on the legacy null stream. */
 int cmaes_enable_graphs(cmaes_t* h, int on);
-/* Closing correction of the eigensolve (C = B D^2 B^T, Sec. 2.1).  Once the
- * block-Jacobi sweeps have brought off(A) below 1e-8 of ||A||_F, one
- * simultaneous rotation of every index pair by its 2 x 2 Jacobi angle
- * (five float64 products) takes the place of the last sweep.  A correction
- * whose angles are not small (||Theta||_F > max_angle_norm) leaves A
- * unchanged and the solve finishes with sweeps.  Either way the solve stops
- * at the same off(A) <= 1e-13 ||A||_F.  on: 0 or 1 (default 1);
- * max_angle_norm in [0, 2e-3] (default 2e-3, the bound below which the
- * rotation is orthogonal to rounding; 0 rejects every correction that would
- * rotate).  CMAES_EINVAL outside that range.  cmaes_state() reports the
- * sweeps and corrections (rejected ones included) of the last eigensolve. */
+/* How an eigensolve (C = B D^2 B^T, Sec. 2.1) ends.  Block-Jacobi sweeps run
+ * while the angles that remain are large; once they are not (n > 64), steps
+ * that rotate every index pair at once by float64 products finish the solve,
+ * each taking the off-diagonal part and B's distance from orthogonality to
+ * the order of their squares.  The last ones, with ||Theta||_F <= 2e-3, are
+ * its closing corrections.  on = 0: sweeps only, until off(A) <= 1e-13
+ * ||A||_F.  on = 1 with max_angle_norm below 2e-3: sweeps until off(A) <=
+ * 1e-8 ||A||_F, then one rotation of every pair in place of the last sweep;
+ * one whose angles exceed the bound leaves A unchanged and the solve finishes
+ * with sweeps (0 rejects every one that would rotate).  on: 0 or 1 (default
+ * 1); max_angle_norm in [0, 2e-3] (default 2e-3).  CMAES_EINVAL outside that
+ * range.  cmaes_state() reports the sweeps (with the steps before the closing
+ * ones) and corrections (rejected ones included) of the last eigensolve.
+ * Concurrent descents (cmaes_batch_*, cmaes_krep_*) sweep only. */
 int cmaes_set_eigen_correction(cmaes_t* h, int on, double max_angle_norm);
 int cmaes_enable_kernel_timing(cmaes_t* h, int on);
 int cmaes_kernel_times(const cmaes_t* h, double* total_us, int64_t* calls);

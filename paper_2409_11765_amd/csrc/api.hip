@@ -284,6 +284,10 @@ void free_all(cmaes* h) {
   dev_free(h, h->ew.A2);
   dev_free(h, h->ew.X1);
   dev_free(h, h->ew.X2);
+  dev_free(h, h->ew.X3);
+  dev_free(h, h->ew.dsum);
+  dev_free(h, h->ew.dv);
+  dev_free(h, h->ew.rctl);
   dev_free(h, h->ew.Q2);
   dev_free(h, h->ew.evals);
   dev_free(h, h->ew.perm);
@@ -386,6 +390,8 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.Q, 8ull * (N / 32) * 32 * 32)) || (rc = dev_alloc(h, &h->ew.T, 8 * nn)) ||
       (rc = dev_alloc(h, &h->ew.A2, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.Q2, 8ull * (N / 32) * 32 * 32)) ||
       (rc = dev_alloc(h, &h->ew.X1, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.X2, 8ull * N * N)) ||
+      (rc = dev_alloc(h, &h->ew.X3, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.dsum, 8ull * (N / 32) * N)) ||
+      (rc = dev_alloc(h, &h->ew.dv, 8ull * N)) || (rc = dev_alloc(h, &h->ew.rctl, 4ull * 8)) ||
       (rc = dev_alloc(h, &h->ew.evals, 8ull * N)) || (rc = dev_alloc(h, &h->ew.perm, 4ull * N)) ||
       (rc = dev_alloc(h, &h->ew.sign, 8ull * N)) || (rc = dev_alloc(h, &h->ew.scale, 16)) ||
       (rc = dev_alloc(h, &h->ew.status, 16)) || (rc = dev_alloc(h, &h->ew.gctl, 4ull * GC_WORDS)))
@@ -394,13 +400,14 @@ int alloc_fixed(cmaes* h) {
     const int q = N / 32;
     if ((rc = dev_alloc(h, &h->ew.part, 8ull * 3 * std::max(n, q * (q + 1) / 2)))) return rc;
   }
-  // convergence flags (words 0-3) and the stop bits (word 4): pinned, mapped
-  // host memory the device writes directly
+  // convergence flags (words 0-3), the stop bits (word 4), f_best (words 6-7)
+  // and the refinement's outcome (words 8-10): pinned, mapped host memory the
+  // device writes directly
   void* hf = nullptr;
-  if (hipHostMalloc(&hf, 32, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+  if (hipHostMalloc(&hf, sizeof(int) * kHostFlagWords, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     return fail(CMAES_ENOMEM, "hipHostMalloc failed");
   h->ew.hflags = static_cast<int*>(hf);
-  for (int i = 0; i < 8; ++i) h->ew.hflags[i] = 0;
+  for (int i = 0; i < kHostFlagWords; ++i) h->ew.hflags[i] = 0;
   void* dp = nullptr;
   if (hipHostGetDevicePointer(&dp, hf, 0) != hipSuccess) return fail(CMAES_EDEVICE, "hipHostGetDevicePointer failed");
   h->ew.dflags = static_cast<int*>(dp);
@@ -477,6 +484,7 @@ int init_descent(cmaes* h, bool fresh) {
   h->eig_uncounted = false;
   h->ew.last_sweeps = 0;
   h->ew.last_closed = false;
+  h->ew.last_steps = 0;
   refresh_stop_params(h);
   return 0;
 }
@@ -643,7 +651,8 @@ bool due_next(const cmaes* h) { return (h->gen + 1) % h->hp.kp.kappa == 0; }
 constexpr int kReorthSweeps = 48;
 void set_due(cmaes* h) {
   if (h->eig_uncounted) {  // the previous generation's eigensolve has finished
-    h->reorth_sweeps += h->ew.sweeps;
+    // (a refinement takes B's orthogonality from B itself: no drift is left)
+    h->reorth_sweeps = h->ew.refined ? 0 : h->reorth_sweeps + h->ew.sweeps;
     h->eig_uncounted = false;
   }
   h->eig_due = due_next(h) && h->opt.variant != CMAES_VARIANT_SEPARABLE;
@@ -663,7 +672,7 @@ int eigen_advance(cmaes* h, bool* done, bool ahead = false) {
   // a decomposition that does not converge within the sweep limit (or meets
   // non-finite values) clears eig_ok on the device, which raises the
   // ConditionCov stop bit
-  return eigen_step(h->st, h->n, h->B, h->ldn, h->D, h->BD, h->fp64, h->ldn, h->ew, h->sc, 40, &h->kt,
+  return eigen_step(h->st, h->n, h->C, h->ldn, h->B, h->ldn, h->D, h->BD, h->fp64, h->ldn, h->ew, h->sc, 40, &h->kt,
                     h->graphs && h->st != nullptr && !h->timing, done, ahead);
 }
 // the eigensolve of the generation just queued: its first batch of sweeps
@@ -715,10 +724,6 @@ int numeric_failure(const cmaes* h) {
 
 GEigDesc eig_desc(cmaes* h);
 
-// dimensions whose eigensolve runs as a grouped solve of one descent: a sweep
-// is one to three rounds there, so several are queued per host wait
-constexpr int kSmallEigenN = 64;
-
 // the eigensolve of the generation just queued, as a grouped solve of this
 // descent (no closing correction); *nonfinite when it met non-finite values
 int eigen_run_small(cmaes* h, bool* nonfinite) {
@@ -735,6 +740,8 @@ int eigen_run_small(cmaes* h, bool* nonfinite) {
   h->ew.corrections = 0;
   h->ew.last_sweeps = sweeps;
   h->ew.last_closed = false;
+  h->ew.last_steps = 0;
+  h->ew.refined = false;
   h->ew.pending = false;
   *nonfinite = code == 3;
   return 0;
@@ -800,6 +807,7 @@ uint64_t front_key(const cmaes* h, bool due) {
   for (int i = 0; i < G32_NUM_SITES; ++i) mix(static_cast<uint64_t>(h->gcfg[i]));
   mix(due ? 1u : 0u);
   mix(h->reorth_due ? 1u : 0u);
+  mix(h->ew.refines() ? 3u : 5u);
   return k | 1u;  // never 0 (0 marks an empty slot)
 }
 
@@ -1279,6 +1287,7 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     h->eig_uncounted = false;
     h->ew.last_sweeps = 0;
     h->ew.last_closed = false;
+    h->ew.last_steps = 0;
   }
   if (in->B || in->D) {
     // B D in the sampling precision
@@ -1813,8 +1822,10 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     if (h->obj_kind == CMAES_OBJ_NONE) return fail(CMAES_ESTATE, "every instance needs a fused objective");
   const int count = static_cast<int>(hs.size());
   if (count > kGroupMax) return fail(CMAES_EINVAL, "too many descents in one lockstep group");
-  for (cmaes* h : hs)
+  for (cmaes* h : hs) {
     if (int rc = ensure_ready(h)) return rc;
+    h->ew.grouped = true;
+  }
   const bool grouped = front_groupable(hs);
   GroupDueMask due{}, reorth{};
   bool any_reorth = false;
@@ -1899,6 +1910,8 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
         h->ew.corrections = 0;
         h->ew.last_sweeps = g.sweeps[i];
         h->ew.last_closed = false;
+        h->ew.last_steps = 0;
+        h->ew.refined = false;
         h->ew.pending = false;
       }
   }

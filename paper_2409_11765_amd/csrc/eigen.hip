@@ -24,8 +24,11 @@
 //     Rotation angles are formed in float32 (they only set how far an entry
 //     is reduced); cosines and sines are float64 and orthogonal to rounding.
 //     Sweeps stop when the off-diagonal Frobenius norm of A falls below
-//     1e-13 of its total norm (summed per tile by the last round); once it
-//     is below 1e-8, a closing correction (below) takes the last sweep's place.
+//     1e-13 of its total norm (summed per tile by the last round).  By default
+//     a solve of its own (n > 64) sweeps only until the angles that remain are
+//     moderate, and products finish it (refine.hip); with a narrower
+//     correction bound, a closing correction (below) takes the last sweep's
+//     place once the norm is below 1e-8.
 //     V starts as B_old, so the rotations land straight in B = B_old V.
 //  3. D = sqrt(diag A), then the pairs are canonicalised like the
 //     oracle: ascending eigenvalues, each column's largest-magnitude entry
@@ -51,6 +54,7 @@ constexpr double kOffTol = 1e-13;
 // the angles satisfy ||Theta||_F <= EigWork::corr_max_theta (at most 2e-3)
 constexpr double kCorrOff = 1e-8;
 constexpr int kMaxCorrections = 4;  // per solve
+constexpr int kMaxSteps = 16;  // refinement steps per solve before it is done by sweeps
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
@@ -840,17 +844,18 @@ __global__ void k_copy_block(const double* __restrict__ src, int lds, int n, dou
 // the diagonal is staged through LDS in chunks, kRankTPI threads count for one
 // eigenvalue (every kRankTPI-th entry each) and sum their integer counts
 constexpr int kRankTPI = 8;
-__device__ __forceinline__ void eig_rank_body(int bx, const double* __restrict__ A, int N, int n,
+// A: the eigenvalues, `stride` apart (N + 1: the diagonal of A)
+__device__ __forceinline__ void eig_rank_body(int bx, const double* __restrict__ A, int stride, int n,
                                               int32_t* __restrict__ perm, double* __restrict__ ev,
                                               const int* __restrict__ status, DevScalars* __restrict__ sc,
                                               double* dg) {
   const int sub = threadIdx.x % kRankTPI;
   const int i = bx * (256 / kRankTPI) + threadIdx.x / kRankTPI;
-  const double vi = i < n ? A[static_cast<int64_t>(i) * N + i] : 0.0;
+  const double vi = i < n ? A[static_cast<int64_t>(i) * stride] : 0.0;
   int cnt = 0;
   for (int base = 0; base < n; base += 1024) {
     const int lim = min(1024, n - base);
-    for (int j = threadIdx.x; j < lim; j += 256) dg[j] = A[static_cast<int64_t>(base + j) * N + base + j];
+    for (int j = threadIdx.x; j < lim; j += 256) dg[j] = A[static_cast<int64_t>(base + j) * stride];
     __syncthreads();
 #pragma unroll 8
     for (int j = sub; j < lim; j += kRankTPI) {
@@ -872,11 +877,11 @@ __device__ __forceinline__ void eig_rank_body(int bx, const double* __restrict__
   }
 }
 
-__global__ void __launch_bounds__(256) k_eig_rank(const double* __restrict__ A, int N, int n,
+__global__ void __launch_bounds__(256) k_eig_rank(const double* __restrict__ A, int stride, int n,
                                                   int32_t* __restrict__ perm, double* __restrict__ ev,
                                                   const int* __restrict__ status, DevScalars* __restrict__ sc) {
   __shared__ double dg[1024];
-  eig_rank_body(blockIdx.x, A, N, n, perm, ev, status, sc, dg);
+  eig_rank_body(blockIdx.x, A, stride, n, perm, ev, status, sc, dg);
 }
 
 // sign of each column: the entry of largest magnitude (first on ties) made positive
@@ -1321,7 +1326,7 @@ __global__ void __launch_bounds__(256) kg_rank(const GEigDesc* __restrict__ g, c
   const GEigDesc& e = g[i];
   if (!e.ctl[GC_DUE]) return;
   const double* A = (e.status[1] & 1) ? e.A2 : e.A;
-  eig_rank_body(blockIdx.x - off[i], A, e.N, e.n, e.perm, e.evals, e.status, e.sc, dg);
+  eig_rank_body(blockIdx.x - off[i], A, e.N + 1, e.n, e.perm, e.evals, e.status, e.sc, dg);
 }
 
 __global__ void __launch_bounds__(256) kg_colsign(const GEigDesc* __restrict__ g, const int* __restrict__ off,
@@ -1366,6 +1371,9 @@ void eigen_begin_host(EigWork& w) {
   w.corr_queued = false;
   w.corr_blocked = false;
   w.pending = true;
+  w.steps = 0;
+  w.refine_blocked = false;
+  w.refined = false;
 }
 
 int eigen_begin(hipStream_t st, int n, const double* C, int ldc, const double* B, int ldb, EigWork& w,
@@ -1375,12 +1383,25 @@ int eigen_begin(hipStream_t st, int n, const double* C, int ldc, const double* B
   eigen_begin_host(w);
   k_init_solve<<<static_cast<int>((NN + 255) / 256), 256, 0, st>>>(w.V, w.Acur, w.Anext, N, n, B, ldb);
   CMX_HIP(hipGetLastError());
-  kt_begin(kt, KID_EIG_GEMM);
-  CMX_HIP(launch_dgemm_ksplit(st, false, false, n, n, n, C, ldc, B, ldb, w.T, ldb, w.X2, N));   // T = C B
-  kt_end(kt);
-  kt_begin(kt, KID_EIG_GEMM);
-  CMX_HIP(launch_dgemm_ksplit(st, true, false, n, n, n, B, ldb, w.T, ldb, w.Acur, N, w.X2, N));   // A = B^T T
-  kt_end(kt);
+  if (w.refines()) {
+    RefineStep a{};
+    a.n = n;
+    a.N = N;
+    a.C = C;
+    a.ldc = ldc;
+    a.V = w.V;  // B
+    a.S = w.Acur;
+    a.T = w.X3;
+    CMX_HIP(launch_refine_start(st, a, kt));
+  } else {
+    // (the products of a grouped solve, whose descents equal solo ones bit for bit)
+    kt_begin(kt, KID_EIG_GEMM);
+    CMX_HIP(launch_dgemm_ksplit(st, false, false, n, n, n, C, ldc, B, ldb, w.T, ldb, w.X2, N));   // T = C B
+    kt_end(kt);
+    kt_begin(kt, KID_EIG_GEMM);
+    CMX_HIP(launch_dgemm_ksplit(st, true, false, n, n, n, B, ldb, w.T, ldb, w.Acur, N, w.X2, N));   // A = B^T T
+    kt_end(kt);
+  }
   k_offnorm_cols<<<n, 256, 0, st>>>(w.Acur, N, n, w.part);
   k_offnorm_final<<<1, 256, 0, st>>>(w.part, n, w.dflags, w.scale, w.gctl);
   CMX_HIP(hipGetLastError());
@@ -1404,45 +1425,181 @@ void eigen_drop_graphs(EigWork& w) {
   w.gstream = nullptr;
 }
 
-int eigen_step(hipStream_t st, int n, double* B, int ldb, double* D, void* BD, bool fp64_bd, int ldbd, EigWork& w,
-               DevScalars* sc, int max_sweeps, KTimer* kt, bool use_graph, bool* done, bool ahead) {
+int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int ldb, double* D, void* BD, bool fp64_bd,
+               int ldbd, EigWork& w, DevScalars* sc, int max_sweeps, KTimer* kt, bool use_graph, bool* done,
+               bool ahead) {
   *done = false;
   const int N = w.N;
   const int p = N / kNB, q = p / 2;
   const int ntiles = q * (q + 1) / 2;
+  const bool refine = w.refines() && !w.refine_blocked;
   // ahead: the first batch of a warm-started solve, queued behind the warm
   // start before its flags are read (a solve after one that took several
   // sweeps needs at least that batch; on a converged or non-finite warm
   // start the extra sweeps change nothing that the next check does not see)
-  if (ahead && (w.sweeps != 0 || w.last_sweeps < 2)) return 0;
+  if (ahead && (w.sweeps != 0 || (w.last_sweeps < 2 && !(refine && w.last_steps > 0)))) return 0;
+  // replay step `slot` from a graph captured on first use (queue() queues
+  // its launches), or queue it directly
+  auto run = [&](int slot, const std::function<hipError_t()>& queue) -> int {
+    if (!(use_graph && !(kt && kt->on))) {
+      CMX_HIP(queue());
+      return 0;
+    }
+    if (w.gx[slot] == nullptr || w.gstream != st) {
+      if (w.gstream != st) eigen_drop_graphs(w);
+      CMX_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+      const hipError_t qe = queue();
+      hipGraph_t g = nullptr;
+      const hipError_t ce = hipStreamEndCapture(st, &g);
+      if (qe != hipSuccess || ce != hipSuccess) {
+        if (g) (void)hipGraphDestroy(g);
+        return fail(-3, std::string("eigen step capture: ") + hipGetErrorString(qe != hipSuccess ? qe : ce));
+      }
+      const hipError_t ie = hipGraphInstantiate(&w.gx[slot], g, nullptr, nullptr, 0);
+      (void)hipGraphDestroy(g);
+      if (ie != hipSuccess) return fail(-3, std::string("eigen step graph: ") + hipGetErrorString(ie));
+      w.gstream = st;
+    }
+    CMX_HIP(hipGraphLaunch(w.gx[slot], st));
+    return 0;
+  };
+  const int round_blocks = q + ntiles + (N / kS) * q;
+  // one sweep's launches (sweeps alternate between the two A and Q buffers
+  // because a sweep has an odd number p - 1 of rounds)
+  auto queue_sweep = [&](double* a0, double* a1, double* q0, double* q1, bool first) -> hipError_t {
+    if (first) {
+      kt_begin(kt, KID_JACOBI);
+      k_jac_first<<<q, 256, 0, st>>>(a0, N, n, p, w.scale, q0);
+      kt_end(kt);
+    }
+    for (int r = 0; r < p - 1; ++r) {
+      hipEvent_t t0, t1;
+      if (kt_ext(kt, KID_JACOBI, &t0, &t1))
+        hipExtLaunchKernelGGL(k_jac_round, dim3(round_blocks), dim3(256), 0, st, t0, t1, 0, a0, a1, w.V, q0, q1,
+                              N, n, r, w.scale, w.part);
+      else
+        k_jac_round<<<round_blocks, 256, 0, st>>>(a0, a1, w.V, q0, q1, N, n, r, w.scale, w.part);
+      std::swap(a0, a1);
+      std::swap(q0, q1);
+    }
+    k_offnorm_final<<<1, 256, 0, st>>>(w.part, ntiles, w.dflags, w.scale, nullptr);
+    return hipGetLastError();
+  };
+  auto sweeps = [&](int batch) -> int {
+    for (int i = 0; i < batch; ++i) {
+      const bool first = w.fresh;
+      const int slot = first ? (w.Acur == w.A ? 2 : 3) : (w.Acur == w.A ? 0 : 1);
+      double *a0 = w.Acur, *a1 = w.Anext, *q0 = w.Qcur, *q1 = w.Qnext;
+      if (const int rc = run(slot, [&] { return queue_sweep(a0, a1, q0, q1, first); })) return rc;
+      for (int r = 0; r < p - 1; ++r) {
+        std::swap(w.Acur, w.Anext);
+        std::swap(w.Qcur, w.Qnext);
+      }
+      ++w.sweeps;
+      w.fresh = false;
+    }
+    return 0;
+  };
+  // `count` refinement steps behind what is queued.  The eigenvectors
+  // alternate between V and Anext with the step's parity; A holds S.  A first
+  // step that the device rejects leaves A, V and the pair solves carried over
+  // from the last sweep as they are, and the steps behind it return at once.
+  auto steps = [&](int count) -> int {
+    for (int i = 0; i < count; ++i, ++w.steps) {
+      const int par = w.steps & 1;
+      RefineStep a{};
+      a.n = n;
+      a.N = N;
+      a.C = C;
+      a.ldc = ldc;
+      a.V = par ? w.Anext : w.V;
+      a.Vn = par ? w.V : w.Anext;
+      a.S = w.Acur;
+      a.Th = w.X2;
+      a.X = w.X1;
+      a.T = w.X3;
+      a.part = w.part;
+      a.dsum = w.dsum;
+      a.dv = w.dv;
+      a.evals = w.evals;
+      a.scale = w.scale;
+      a.ctl = w.rctl;
+      a.flags = w.dflags;
+      a.par = par;
+      a.first = w.steps == 0;
+      const int in2 = w.Acur == w.A ? 0 : 1;
+      if (const int rc = run(a.first ? 6 + in2 : 8 + 2 * in2 + par, [&] { return launch_refine_step(st, a, kt); }))
+        return rc;
+    }
+    return 0;
+  };
+  // converged (1), sweep limit (2) or non-finite (3): V (N x N) holds
+  // B_new = B_old V_rot; canonical order / signs into B, D, BD
+  auto finish = [&](const double* V, const double* ev, int stride, int code, int nsweeps, int ncorr) -> int {
+    k_set_status<<<1, 64, 0, st>>>(w.status, code, nsweeps, ncorr);
+    k_eig_rank<<<ceil_div(n, 256 / kRankTPI), 256, 0, st>>>(ev, stride, n, w.perm, w.evals, w.status, sc);
+    k_colsign<<<n, 256, 0, st>>>(V, N, n, w.sign);
+    dim3 grid(ceil_div(n, 256), n);
+    if (fp64_bd)
+      k_permute<double><<<grid, 256, 0, st>>>(V, N, n, w.perm, w.evals, w.sign, B, ldb, D, static_cast<double*>(BD),
+                                              ldbd);
+    else
+      k_permute<float><<<grid, 256, 0, st>>>(V, N, n, w.perm, w.evals, w.sign, B, ldb, D, static_cast<float*>(BD),
+                                             ldbd);
+    CMX_HIP(hipGetLastError());
+    w.pending = false;
+    *done = true;
+    return 0;
+  };
+
+  if (refine) {
+    if (ahead) {
+      // the spectrum spreads from one generation to the next, so a solve
+      // rarely needs more sweeps than the one before it, and often fewer: one
+      // fewer are queued before its first step decides; with no sweeps
+      // expected, as many steps as the previous solve applied
+      if (const int rc = sweeps(std::min(std::max(0, w.last_sweeps - 1), max_sweeps))) return rc;
+      return steps(w.last_sweeps == 0 ? w.last_steps : 1);
+    }
+    const bool more = w.hflags[0] != 0, nonfinite = w.hflags[1] != 0;
+    if (w.steps == 0 && more && !nonfinite) return steps(1);
+    if (!nonfinite && w.steps > 0) {
+      const int state = w.hflags[RF_STATE], applied = w.hflags[RF_APPLIED];
+      if (state == RS_DONE) {
+        const int small = std::min(w.hflags[RF_SMALL], kMaxCorrections);
+        w.last_sweeps = w.sweeps;
+        w.last_steps = applied;
+        w.last_closed = false;
+        w.refined = true;
+        return finish(applied & 1 ? w.Anext : w.V, w.evals, 1, 1, w.sweeps + applied - small, small);
+      }
+      if (state == RS_ACTIVE && applied < kMaxSteps)
+        return steps(applied == 1 ? std::max(2, std::min(w.last_steps, kMaxSteps) - 1) : 1);
+      if (state == RS_REJECTED && more && w.sweeps < max_sweeps) {
+        if (const int rc = sweeps(1)) return rc;
+        w.steps = 0;
+        return steps(1);
+      }
+      if (state == RS_ACTIVE || state == RS_DIVERGED) {
+        // from the start again, by sweeps
+        if (const int rc = eigen_begin(st, n, C, ldc, B, ldb, w, kt)) return rc;
+        w.refine_blocked = true;
+        return 0;
+      }
+    }
+    // a converged warm start, non-finite values, or sweeps that went all the way
+    w.last_sweeps = w.sweeps;
+    w.last_steps = 0;
+    w.last_closed = false;
+    return finish(w.V, w.Acur, N + 1, nonfinite ? 3 : (more ? 2 : 1), w.sweeps, 0);
+  }
+
   if (!ahead && w.corr_queued) {  // a rejected correction (its rotation was not small) is not tried again
     if (w.hflags[3] || w.corrections >= kMaxCorrections) w.corr_blocked = true;
     w.corr_queued = false;
   }
   const bool more = ahead || (w.hflags[0] && !w.hflags[1]);
   if (more && w.sweeps < max_sweeps) {
-    const int round_blocks = q + ntiles + (N / kS) * q;
-    // one sweep's launches (sweeps alternate between the two A and Q buffers
-    // because a sweep has an odd number p - 1 of rounds)
-    auto queue_sweep = [&](double* a0, double* a1, double* q0, double* q1, bool first) -> hipError_t {
-      if (first) {
-        kt_begin(kt, KID_JACOBI);
-        k_jac_first<<<q, 256, 0, st>>>(a0, N, n, p, w.scale, q0);
-        kt_end(kt);
-      }
-      for (int r = 0; r < p - 1; ++r) {
-        hipEvent_t t0, t1;
-        if (kt_ext(kt, KID_JACOBI, &t0, &t1))
-          hipExtLaunchKernelGGL(k_jac_round, dim3(round_blocks), dim3(256), 0, st, t0, t1, 0, a0, a1, w.V, q0, q1,
-                                N, n, r, w.scale, w.part);
-        else
-          k_jac_round<<<round_blocks, 256, 0, st>>>(a0, a1, w.V, q0, q1, N, n, r, w.scale, w.part);
-        std::swap(a0, a1);
-        std::swap(q0, q1);
-      }
-      k_offnorm_final<<<1, 256, 0, st>>>(w.part, ntiles, w.dflags, w.scale, nullptr);
-      return hipGetLastError();
-    };
     // one closing correction from a0 into a1 (X1: Theta, then Q; X2: S, then
     // A Q; a1: S^2, then V Q, then the result; the k-split products use a1 or
     // T as scratch while those are free)
@@ -1475,31 +1632,6 @@ int eigen_step(hipStream_t st, int n, double* B, int ldb, double* D, void* BD, b
       k_offnorm_final<<<1, 256, 0, st>>>(w.part, n, w.dflags, w.scale, nullptr);
       return hipGetLastError();
     };
-    // replay step `slot` from a graph captured on first use (queue() queues
-    // its launches), or queue it directly
-    auto run = [&](int slot, const std::function<hipError_t()>& queue) -> int {
-      if (!(use_graph && !(kt && kt->on))) {
-        CMX_HIP(queue());
-        return 0;
-      }
-      if (w.gx[slot] == nullptr || w.gstream != st) {
-        if (w.gstream != st) eigen_drop_graphs(w);
-        CMX_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        const hipError_t qe = queue();
-        hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(st, &g);
-        if (qe != hipSuccess || ce != hipSuccess) {
-          if (g) (void)hipGraphDestroy(g);
-          return fail(-3, std::string("eigen step capture: ") + hipGetErrorString(qe != hipSuccess ? qe : ce));
-        }
-        const hipError_t ie = hipGraphInstantiate(&w.gx[slot], g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (ie != hipSuccess) return fail(-3, std::string("eigen step graph: ") + hipGetErrorString(ie));
-        w.gstream = st;
-      }
-      CMX_HIP(hipGraphLaunch(w.gx[slot], st));
-      return 0;
-    };
     const bool from_a = (w.Acur == w.A);
     if (!ahead && w.correct_on && !w.corr_blocked && w.hflags[2]) {
       double *a0 = w.Acur, *a1 = w.Anext;
@@ -1523,39 +1655,13 @@ int eigen_step(hipStream_t st, int n, double* B, int ldb, double* D, void* BD, b
     int batch = 1;
     if (w.sweeps == 0) batch = std::max(1, w.last_closed ? w.last_sweeps : w.last_sweeps - 1);
     batch = std::min(batch, max_sweeps - w.sweeps);
-    for (int i = 0; i < batch; ++i) {
-      const bool first = w.fresh;
-      const int slot = first ? (w.Acur == w.A ? 2 : 3) : (w.Acur == w.A ? 0 : 1);
-      double *a0 = w.Acur, *a1 = w.Anext, *q0 = w.Qcur, *q1 = w.Qnext;
-      if (const int rc = run(slot, [&] { return queue_sweep(a0, a1, q0, q1, first); })) return rc;
-      for (int r = 0; r < p - 1; ++r) {
-        std::swap(w.Acur, w.Anext);
-        std::swap(w.Qcur, w.Qnext);
-      }
-      ++w.sweeps;
-      w.fresh = false;
-    }
-    return 0;
+    return sweeps(batch);
   }
-  // converged (1), sweep limit (2) or non-finite (3): finish
-  k_set_status<<<1, 64, 0, st>>>(w.status, w.hflags[1] ? 3 : (w.hflags[0] ? 2 : 1), w.sweeps - w.corrections,
-                                 w.corrections);
-  // V holds B_new = B_old V_rot: canonical order / signs into B, D, BD
-  k_eig_rank<<<ceil_div(n, 256 / kRankTPI), 256, 0, st>>>(w.Acur, N, n, w.perm, w.evals, w.status, sc);
-  k_colsign<<<n, 256, 0, st>>>(w.V, N, n, w.sign);
-  dim3 grid(ceil_div(n, 256), n);
-  if (fp64_bd)
-    k_permute<double><<<grid, 256, 0, st>>>(w.V, N, n, w.perm, w.evals, w.sign, B, ldb, D,
-                                            static_cast<double*>(BD), ldbd);
-  else
-    k_permute<float><<<grid, 256, 0, st>>>(w.V, N, n, w.perm, w.evals, w.sign, B, ldb, D,
-                                           static_cast<float*>(BD), ldbd);
-  CMX_HIP(hipGetLastError());
-  w.pending = false;
+  if (ahead) return 0;
   w.last_sweeps = w.sweeps - w.corrections;
+  w.last_steps = 0;
   w.last_closed = w.corrections > 0;
-  *done = true;
-  return 0;
+  return finish(w.V, w.Acur, N + 1, w.hflags[1] ? 3 : (w.hflags[0] ? 2 : 1), w.sweeps - w.corrections, w.corrections);
 }
 
 

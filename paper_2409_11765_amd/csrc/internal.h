@@ -215,6 +215,10 @@ hipError_t launch_dgemm2(hipStream_t st, int M, int N, int K, const double* A0, 
                          int lda1, const double* B, int ldb, double* C0, int ldc0, double* C1, int ldc1);
 
 // eigensolver
+// padded size up to which a descent's eigensolve runs as a grouped solve of
+// one descent: a sweep is one to three rounds there, so several are queued
+// per host wait
+constexpr int kSmallEigenN = 64;
 struct EigWork {
   int N = 0;      // padded size (multiple of 32)
   int* gctl = nullptr;   // control block of a grouped solve (GC_WORDS ints, device memory)
@@ -226,6 +230,10 @@ struct EigWork {
   double* T = nullptr;   // n*n scratch
   double* X1 = nullptr;  // N*N: angles, then the correction's rotation
   double* X2 = nullptr;  // N*N: products of the correction
+  double* X3 = nullptr;  // N*N: products of the refinement
+  double* dsum = nullptr;  // (N/32) * N: the refinement's second-order eigenvalue terms
+  double* dv = nullptr;    // N: its first-order eigenvalues
+  int* rctl = nullptr;     // its control words (8 ints, device memory)
   double* evals = nullptr;  // N
   int32_t* perm = nullptr;  // N
   double* sign = nullptr;   // N
@@ -234,7 +242,8 @@ struct EigWork {
   int* status = nullptr;  // [0] 1 converged, 2 sweep limit, 3 non-finite; [1] sweeps; [2] corrections
   int* hflags = nullptr;  // pinned host memory: [0] more sweeps needed, [1] non-finite,
                   // [2] off(A) small enough for a closing correction, [3] the last
-                  // correction was rejected (its rotation was not small)
+                  // correction was rejected (its rotation was not small),
+                  // [RF_STATE .. RF_SMALL] the refinement's outcome
   int* dflags = nullptr;  // device address of hflags (written by the convergence test)
   // progress of the eigensolve in flight
   double *Acur = nullptr, *Anext = nullptr, *Qcur = nullptr, *Qnext = nullptr;
@@ -247,12 +256,46 @@ struct EigWork {
   bool corr_blocked = false;  // a correction was rejected: sweeps only for the rest of this solve
   bool correct_on = true;  // closing corrections enabled
   double corr_max_theta = 2e-3;  // acceptance bound on ||Theta||_F (graphs capture it)
+  // whether products refine what the sweeps leave: a caller that narrows the
+  // closing correction's bound gets sweeps closed by corrections within it
+  bool grouped = false;  // the descent's eigensolves run in a group's (sweeps only)
+  bool refines() const { return correct_on && corr_max_theta >= 2e-3 && N > kSmallEigenN && !grouped; }
   bool pending = false;
+  int steps = 0;         // refinement steps queued so far since the last sweep
+  int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
+  bool refine_blocked = false;  // a refinement diverged: sweeps only for the rest of this solve
+  bool refined = false;  // the last solve ended with a refinement (B is orthogonal to rounding)
   // captured steps: [0] sweep from A, [1] from A2, [2] first sweep from A,
-  // [3] from A2, [4] correction from A, [5] from A2
-  hipGraphExec_t gx[6] = {};
+  // [3] from A2, [4] correction from A, [5] from A2, [6] first refinement step
+  // from A, [7] from A2, [8 + 2 (S in A2) + parity] a later one
+  hipGraphExec_t gx[12] = {};
   hipStream_t gstream = nullptr;
 };
+// ---- refinement of a nearly diagonal solve by products (refine.hip)
+// outcome of the last step that ran (host flags; the words follow the
+// convergence flags, the stop bits and f_best)
+enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, kHostFlagWords = 16 };
+// RS_ACTIVE: applied, more to do; RS_DONE: applied, the last; RS_REJECTED: the
+// first step's angles were too large, nothing was changed; RS_DIVERGED: a
+// later step's were, V is not to be used
+enum { RS_ACTIVE = 0, RS_DONE = 1, RS_REJECTED = 2, RS_DIVERGED = 3 };
+struct RefineStep {
+  int n, N;
+  const double* C;
+  int ldc;
+  const double* V;  // N*N: eigenvectors so far (zero rows and columns n.. or the identity's)
+  double* Vn;       // the step's result
+  double* S;        // V^T C V: given to the first step, made by the others
+  double *Th, *X, *T;  // N*N scratch
+  double *part, *dsum, *dv, *evals;
+  const double* scale;
+  int *ctl, *flags;
+  int par;     // the step's number mod 2
+  bool first;  // S is given and V taken as orthogonal
+};
+hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
+// the warm start: S = V^T C V, both triangles (uses n, N, C, V, S and T)
+hipError_t launch_refine_start(hipStream_t st, const RefineStep& a, KTimer* kt);
 // Queue the warm start and the first convergence test; the host then
 // synchronises the stream and calls eigen_step until it reports done (each
 // call queues one more sweep, or the finishing kernels).
@@ -261,7 +304,7 @@ int eigen_begin(hipStream_t st, int n, const double* C, int ldc, const double* B
 void eigen_begin_host(EigWork& w);
 // ahead = true: queue the first batch of sweeps of a warm-started solve
 // without reading the flags (no synchronisation needed; a no-op otherwise)
-int eigen_step(hipStream_t st, int n, double* B, int ldb, double* D, void* BD, bool fp64_bd, int ldbd, EigWork& w,
+int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int ldb, double* D, void* BD, bool fp64_bd, int ldbd, EigWork& w,
                DevScalars* sc, int max_sweeps, KTimer* kt, bool use_graph, bool* done, bool ahead = false);
 // release the captured sweep graphs (the stream or the buffers change)
 void eigen_drop_graphs(EigWork& w);

@@ -1,0 +1,559 @@
+// Refinement of the eigendecomposition C = B D^2 B^T (Sec. 2.1) by products.
+//
+// A warm-started solve begins with eigenvectors V of the previous covariance,
+// so S = V^T C V is nearly diagonal.  One step rotates every index pair at
+// once: with R = I - V^T V (V's distance from orthogonality) and d_i =
+// S_ii / (V^T V)_ii, the angle of the pair (i, j) is that of its own 2 x 2
+// problem in the basis made orthogonal to first order,
+//   s_ij = S_ij + R_ij (d_i + d_j) / 2,   theta_ij = atan(2 s_ij / (d_j - d_i)) / 2,
+// clipped at kClip, and
+//   V <- V X,   X = I + Theta + R / 2 + Theta^2 / 2 + Theta^3 / 6
+// (Theta antisymmetric).  To first order this is the refinement of Ogita and
+// Aishima ("Iterative refinement for symmetric eigenvalue decomposition",
+// Japan J. Indust. Appl. Math. 35, 2018): it converges quadratically in both
+// the off-diagonal part and the orthogonality, and since every step starts
+// again from C, neither the rounding of the steps before it nor a drift of B
+// from one solve to the next stays in the result.  The second and third order
+// terms, Jacobi's angle in place of the quotient and the clip let it start
+// from angles that are not small (||Theta||_F^2 up to kThLimit n).
+//
+// A step takes five float64 products (two of them, and the two powers of
+// Theta, of lower tiles only); a block-Jacobi sweep reduces off(A) about as
+// far in N/16 - 1 dependent rounds.  At n = 1000 a step takes a quarter of a
+// sweep's time.
+//
+// Whether a step is applied, and whether it was the last, is decided on the
+// device by every workgroup alike from the same partial sums, so several
+// steps can be queued behind one another; the host reads the outcome once.
+//
+// Measured at n = 1000 (us): C V 41.7, S and G 49.7, Theta 8.4, Theta^2 (with X
+// on most steps) 29.9, Theta^3 and X 23.7, V X 41.0, so about 180 a step against
+// 730 a sweep of 63 rounds; 48 TFLOP/s in the whole products (a library's
+// 1000^3 product takes 37.1), bound by the float64 matrix cores and, at one or
+// two tiles per CU, by the start of each tile's loads and the sum over the
+// waves.  At n = 200: 4.1, 4.3, 5.7, 5.9, 5.2 and 4.1, bound by latency; a sweep
+// of 13 rounds takes 150.
+#include "internal.h"
+
+namespace cmx {
+
+namespace {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// largest ||Theta||_F^2 / n and ||R||_F^2 / n a step is applied at
+constexpr double kThLimit = 1.0;
+constexpr double kRLimit = 0.1;
+constexpr double kClip = 0.35;
+// a step is the last one once ||Theta||_F and ||R||_F are below this: what it
+// leaves is of the order of their squares
+constexpr double kDone = 1e-6;
+// Theta^3 / 6 is left out once ||Theta||_F is below this
+constexpr double kCubeFrom = 1e-3;
+
+// ---- products.  A workgroup computes a square tile of MB x MB MFMA blocks
+// (16 x 16); every one of its NW waves computes the whole tile over its own
+// part of k, and the partial sums meet in LDS.  v_mfma_f64_16x16x4 takes 64
+// cycles for 2 x 64 operand values, so a wave that holds the whole tile needs
+// few bytes per cycle and reads its operands straight from global memory into
+// the fragment registers: no LDS and no barrier in the k-loop, two chunks of 16
+// k in flight.  Both operands are read along k with 16-byte loads: lane (i = l
+// & 15, g = l >> 4) holds k = 16 c + 8 h + 2 g + s of row i (h, s = 0, 1), so
+// the four lanes of a row read 64 consecutive bytes, and instruction (h, s) of
+// a chunk multiplies those k of all four g.  TA = false reads A(m, k) along m
+// instead.  The operands change roles in the instruction, so that 16
+// consecutive lanes of a result are 16 consecutive rows.
+// MB = 3, NW = 4: two workgroups per CU; at n = 1000 a whole product is 441
+// tiles and two lower triangles are 462, both just under the 512 the chip
+// holds (41 us for a whole product; with 64 x 64 tiles of 32 x 32 per wave, 256
+// and 272 tiles, 50 and 120 us).  The smaller tiles give more workgroups and a
+// shorter k-loop each: at n = 200 a product takes 4.1 us with MB = 1, NW = 4
+// against 7.4-8.5 with MB = 2, NW = 8, at n = 333 7.5-9.0 against 9.9-12.2.
+template <int MB_, int NW_>
+struct Tile {
+  static constexpr int MB = MB_, NW = NW_;
+  static constexpr int T = 16 * MB;
+  static constexpr int THREADS = 64 * NW;
+  static constexpr int PER = T * T / THREADS;  // elements per thread
+  static constexpr int PS = T + 1;             // LDS column stride
+  static constexpr int LDS = NW * T * PS;      // doubles
+  static_assert(PER * THREADS == T * T, "elements must split evenly");
+
+  struct Frag {
+    double a[MB][4], b[MB][4];
+  };
+
+  // the tile at (m0, n0) of op(A) B over kc chunks of 16 k, partial sums in
+  // lds; rows and columns are clamped to rmax and cmax (their results are
+  // ignored), A's k to kmax with CLAMP (a multiple of 4: past it any stored
+  // value is read, for B's zero rows).  Nothing is computed, and false
+  // returned, unless go (uniform; tested when the first loads are under way).
+  template <bool TA, bool CLAMP>
+  __device__ static bool product(double* lds, const double* __restrict__ A, int lda, const double* __restrict__ B,
+                                 int ldb, int kc, int m0, int n0, int rmax, int cmax, int kmax, bool go) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    const int c0 = wave * kc / NW, c1 = (wave + 1) * kc / NW;
+    const double *pa[MB], *pb[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int row = min(m0 + 16 * i + li, rmax - 1), col = min(n0 + 16 * i + li, cmax - 1);
+      pa[i] = TA ? A + static_cast<int64_t>(row) * lda + 2 * lg : A + static_cast<int64_t>(2 * lg) * lda + row;
+      pb[i] = B + static_cast<int64_t>(col) * ldb + 2 * lg;
+    }
+    doublex4 acc[MB][MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < MB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    auto load = [&](Frag& f, int c) {
+      const int k = 16 * min(c, c1 - 1);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if constexpr (TA) {
+            int o = k + 8 * h;
+            if constexpr (CLAMP) o = o + 2 * lg < kmax ? o : -2 * lg;
+            const double2 x = *reinterpret_cast<const double2*>(pa[i] + o);
+            f.a[i][2 * h] = x.x;
+            f.a[i][2 * h + 1] = x.y;
+          } else {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) f.a[i][2 * h + s] = pa[i][static_cast<int64_t>(k + 8 * h + s) * lda];
+          }
+          const double2 y = *reinterpret_cast<const double2*>(pb[i] + k + 8 * h);
+          f.b[i][2 * h] = y.x;
+          f.b[i][2 * h + 1] = y.y;
+        }
+      }
+    };
+    auto compute = [&](const Frag& f) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < MB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.b[j][s], f.a[i][s], acc[i][j], 0, 0, 0);
+    };
+    if (c0 < c1) {
+      Frag f0, f1;
+      load(f0, c0);
+      load(f1, c0 + 1);
+      if (!go) return false;
+      // (no branch inside: the waits then count the loads in flight exactly)
+      int c = c0;
+      for (; c + 1 < c1; c += 2) {
+        compute(f0);
+        load(f0, c + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(f1);
+        load(f1, c + 3);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (c < c1) compute(f0);
+    } else if (!go) {
+      return false;
+    }
+    double* p = lds + wave * T * PS;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[(16 * j + lg + 4 * r) * PS + 16 * i + li] = acc[i][j][r];
+    __syncthreads();
+    return true;
+  }
+  // element (r, c) of the tile: the waves' sums in order
+  __device__ static double get(const double* lds, int r, int c) {
+    const double* p = lds + c * PS + r;
+    double v = p[0];
+#pragma unroll
+    for (int g = 1; g < NW; ++g) v += p[g * T * PS];
+    return v;
+  }
+  // the tile's transpose to out (rows n0.., columns m0..): thread values v[e]
+  // of the elements (r, c) with r + T c = threadIdx.x + THREADS e, through LDS
+  __device__ static void store_mirror(double* lds, const double (&v)[PER], double* __restrict__ out, int N, int m0,
+                                      int n0) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int idx = threadIdx.x + THREADS * e;
+      lds[(idx % T) * PS + idx / T] = v[e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int idx = threadIdx.x + THREADS * e, r = idx % T, c = idx / T;  // row n0 + r, column m0 + c
+      if (n0 + r < N && m0 + c < N) out[static_cast<int64_t>(m0 + c) * N + n0 + r] = lds[c * PS + r];
+    }
+  }
+};
+using TinyTile = Tile<1, 4>;
+using SmallTile = Tile<2, 8>;
+using LargeTile = Tile<3, 4>;
+
+__device__ __forceinline__ void lower_tile(int t, int& tm, int& tn) {
+  tm = static_cast<int>((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
+  while ((tm + 1) * (tm + 2) / 2 <= t) ++tm;
+  while (tm * (tm + 1) / 2 > t) --tm;
+  tn = t - tm * (tm + 1) / 2;
+}
+
+// workgroup b of a launch of `total` to its tile number: workgroups go to the
+// 8 XCDs in turn, and each XCD gets a contiguous run of tiles (its L2 then
+// holds the operands of that run)
+__device__ __forceinline__ int xcd_order(int b, int total) {
+  const int per = total / 8, extra = total % 8, x = b % 8, i = b / 8;
+  return x * per + min(x, extra) + i;
+}
+
+// out = op(A) B over all tiles
+template <class TL, bool TA, bool CLAMP>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_ref_full(const double* __restrict__ A, int lda,
+                                                             const double* __restrict__ B, int N, int n,
+                                                             double* __restrict__ out, int rmax, int kmax,
+                                                             const int* __restrict__ word, int mask, int want) {
+  __shared__ double lds[TL::LDS];
+  const bool go = word == nullptr || (*word & mask) == want;
+  const int side = (n + TL::T - 1) / TL::T;
+  const int t = xcd_order(blockIdx.x, gridDim.x);
+  const int m0 = (t % side) * TL::T, n0 = (t / side) * TL::T;
+  if (!TL::template product<TA, CLAMP>(lds, A, lda, B, N, (n + 15) / 16, m0, n0, rmax, N, kmax, go)) return;
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    if (m0 + r < N && n0 + c < N) out[static_cast<int64_t>(n0 + c) * N + m0 + r] = TL::get(lds, r, c);
+  }
+}
+
+// lower tiles of S = V^T T (MIRROR: both triangles) and, with twice the
+// workgroups, of G = V^T V
+template <class TL, bool MIRROR>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_ref_sg(const double* __restrict__ V, const double* __restrict__ Tm,
+                                                           int N, int n, int ntl, double* __restrict__ S,
+                                                           double* __restrict__ G, const int* __restrict__ word) {
+  __shared__ double lds[TL::LDS];
+  const bool go = word == nullptr || *word == 0;
+  int t = xcd_order(blockIdx.x, gridDim.x);
+  const bool second = t >= ntl;
+  if (second) t -= ntl;
+  int tm, tn;
+  lower_tile(t, tm, tn);
+  const int m0 = tm * TL::T, n0 = tn * TL::T;
+  if (!TL::template product<true, false>(lds, V, N, second ? V : Tm, N, (n + 15) / 16, m0, n0, N, N, N, go)) return;
+  double* out = second ? G : S;
+  double v[TL::PER];
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    v[e] = MIRROR && tm == tn && r < c ? TL::get(lds, c, r) : TL::get(lds, r, c);
+    if (MIRROR && (m0 + r >= n || n0 + c >= n)) v[e] = 0.0;  // the sweeps need zero padding
+    if (m0 + r < N && n0 + c < N) out[static_cast<int64_t>(n0 + c) * N + m0 + r] = v[e];
+  }
+  if (MIRROR && tm != tn) TL::store_mirror(lds, v, out, N, m0, n0);
+}
+
+// sums of two values over the workgroup, in a fixed order
+template <int NW>
+__device__ __forceinline__ void block_sum2(double& a, double& b, double (*red)[NW]) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    a += __shfl_xor(a, m);
+    b += __shfl_xor(b, m);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = a;
+    red[1][threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  a = red[0][0];
+  b = red[1][0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    a += red[0][w];
+    b += red[1][w];
+  }
+}
+
+// Theta from the lower tiles of S and G (null: R = 0), 32 x 32 tiles; both
+// triangles of Theta, its squared norm and R's per tile (tiles of padding are
+// zero), the first-order eigenvalues d, and per tile and row the sum over the
+// tile's columns of theta_ji s_ij, which is what rotating by Theta adds to d_i.
+// Entries at or below the sweeps' rotation threshold get no rotation.  Entries
+// at the level of the products' rounding (kNoise) are as small as they can
+// get: they do not count, and turn nothing by more than kNoiseAngle (inside
+// a multiple eigenvalue their angles are arbitrary).
+constexpr double kNoise = 8.0, kNoiseAngle = 1e-4;
+constexpr int kCT = 32;
+__global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S, const double* __restrict__ G, int N,
+                                                   int n, const double* __restrict__ scale, double* __restrict__ Th,
+                                                   double* __restrict__ part, double* __restrict__ dsum,
+                                                   double* __restrict__ dv, const int* __restrict__ word) {
+  __shared__ double tl[kCT][kCT + 1], ts[kCT][kCT + 1];
+  __shared__ double dr[kCT], dc[kCT];
+  __shared__ double red[2][4];
+  if (word && *word != 0) return;
+  int bi, bj;
+  lower_tile(blockIdx.x, bi, bj);
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
+  const int r0 = bi * kCT, c0 = bj * kCT;
+  double sv[kCT / 8], gv[kCT / 8];
+#pragma unroll
+  for (int q = 0; q < kCT / 8; ++q) {
+    const int64_t at = static_cast<int64_t>(c0 + ty + 8 * q) * N + r0 + tx;
+    sv[q] = S[at];
+    gv[q] = G ? G[at] : 0.0;
+  }
+  if (t < 2 * kCT) {
+    const int i = (t < kCT ? r0 : c0) + (t & 31);
+    const int64_t at = static_cast<int64_t>(i) * N + i;
+    double v = 0.0;
+    if (i < n) v = G ? S[at] / G[at] : S[at];
+    (t < kCT ? dr : dc)[t & 31] = v;
+    if (bi == bj && t < kCT && i < n) dv[i] = v;
+  }
+  __syncthreads();
+  const double eps = 2.2e-16 * scale[0];
+  double th2 = 0.0, r2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < kCT / 8; ++q) {
+    const int k = ty + 8 * q, r = r0 + tx, c = c0 + k;
+    double th = 0.0, w = 0.0;
+    if (r < n && c < n && r > c) {
+      const double rij = -gv[q];
+      const double a = sv[q] + 0.5 * rij * (dr[tx] + dc[k]);
+      const double g = dr[tx] - dc[k];  // d_r - d_c: the rotation of the pair (c, r), c < r
+      if (fabs(a) > eps) {
+        const double tn = 2.0 * a / (fabs(g) + sqrt(fma(g, g, 4.0 * a * a)));
+        double h = tn / fma(0.28, tn * tn, 1.0);  // atan(tn) to 0.005, exact to first order
+        h = g < 0.0 ? -h : h;
+        const bool noise = fabs(a) <= kNoise * eps;
+        if (noise && fabs(h) > kNoiseAngle) h = 0.0;
+        h = fmin(fmax(h, -kClip), kClip);
+        th = -h;  // Theta(r, c) = -Theta(c, r)
+        w = h * a;  // theta_cr s: added to d_r, taken from d_c
+        if (!noise) th2 = fma(2.0 * h, h, th2);
+      }
+      r2 = fma(2.0 * rij, rij, r2) + (a - a);  // (a - a): NaN when a is not finite
+    } else if (r < n && r == c && G) {
+      const double rii = 1.0 - gv[q];
+      r2 = fma(rii, rii, r2);
+    }
+    tl[tx][k] = th;
+    ts[tx][k] = w;
+  }
+  block_sum2<4>(th2, r2, red);  // (its barrier also covers tl and ts)
+  if (t == 0) {
+    part[2 * blockIdx.x] = th2;
+    part[2 * blockIdx.x + 1] = r2;
+  }
+#pragma unroll
+  for (int q = 0; q < kCT / 8; ++q) {
+    const int k = ty + 8 * q;
+    if (bi != bj) {
+      Th[static_cast<int64_t>(c0 + k) * N + r0 + tx] = tl[tx][k];
+      Th[static_cast<int64_t>(r0 + k) * N + c0 + tx] = -tl[k][tx];
+    } else {
+      Th[static_cast<int64_t>(c0 + k) * N + r0 + tx] = tx >= k ? tl[tx][k] : -tl[k][tx];
+    }
+  }
+  // rows: + sum over the tile's columns; columns: - sum over its rows
+  if (t < kCT) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kCT; ++k) s += ts[t][k];
+    if (bi == bj)
+#pragma unroll
+      for (int k = 0; k < kCT; ++k) s -= ts[k][t];
+    dsum[static_cast<int64_t>(bj) * N + r0 + t] = s;
+  } else if (bi != bj && t < 2 * kCT) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kCT; ++k) s -= ts[k][t - kCT];
+    dsum[static_cast<int64_t>(bi) * N + c0 + t - kCT] = s;
+  }
+}
+
+// ---- control words of a solve's refinement.  Step j reads state[j & 1]
+// (0: run) and writes state[(j + 1) & 1] and bits[j & 1], so no workgroup
+// reads a word that its own launch writes.
+enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5 };
+enum { RB_APPLY = 1, RB_CUBE = 2 };
+
+// X of one lower tile and of its mirror, in place of G (X and G share a
+// buffer; useg false: R = 0): lower(r, c) and its transpose from the symmetric
+// and antisymmetric parts.  sq(e, at): Theta^2 of element e, cube(r, c): Theta^3.
+// The workgroups of the diagonal tiles also sum up the eigenvalues.
+template <class TL, class Square, class Cube>
+__device__ __forceinline__ void make_x(double* lds, const double* __restrict__ Th, int N, int n, int tm, int tn,
+                                       bool useg, double* __restrict__ X, const double* __restrict__ dsum,
+                                       const double* __restrict__ dv, double* __restrict__ evals, Square sq,
+                                       Cube cube) {
+  const int m0 = tm * TL::T, n0 = tn * TL::T;
+  double v[TL::PER];
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    const int gr = m0 + r, gc = n0 + c;
+    v[e] = 0.0;
+    if (gr >= N || gc >= N) continue;
+    const int64_t at = static_cast<int64_t>(gc) * N + gr;
+    double lower = 0.0;
+    if (gr < n && gc < n) {
+      const double id = gr == gc ? 1.0 : 0.0;
+      double sym = id + 0.5 * sq(e, at);
+      const double anti = Th[at] + cube(r, c) * (1.0 / 6.0);
+      if (useg) sym += 0.5 * (id - X[at]);
+      lower = sym + anti;
+      v[e] = sym - anti;
+    }
+    X[at] = lower;
+  }
+  if (tm != tn) {
+    TL::store_mirror(lds, v, X, N, m0, n0);
+  } else if (threadIdx.x < TL::T) {
+    const int i = m0 + threadIdx.x;
+    if (i < n) {
+      double s = dv[i];
+#pragma unroll 8
+      for (int k = 0; k < N / kCT; ++k) s += dsum[static_cast<int64_t>(k) * N + i];
+      evals[i] = s;
+    }
+  }
+}
+
+// Decision on the step whose Theta is in place, by every workgroup alike, and
+// the lower tiles of Theta^2.  While Theta^3 counts, both triangles of Theta^2
+// are stored and k_ref_cube forms X; else X is formed here.
+template <class TL>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __restrict__ Th, int N, int n,
+                                                               double* __restrict__ S2,
+                                                               const double* __restrict__ part, int count, int first,
+                                                               int par, int* __restrict__ ctl,
+                                                               int* __restrict__ flags, double* __restrict__ X,
+                                                               const double* __restrict__ dsum,
+                                                               const double* __restrict__ dv,
+                                                               double* __restrict__ evals) {
+  __shared__ double lds[TL::LDS];
+  __shared__ double red[2][TL::NW];
+  const int before = first ? 0 : ctl[RC_STATE + par];
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  double th2 = 0.0, r2 = 0.0;
+  for (int i = threadIdx.x; i < count; i += TL::THREADS) {
+    th2 += part[2 * i];
+    r2 += part[2 * i + 1];
+  }
+  int tm, tn;
+  lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
+  const int m0 = tm * TL::T, n0 = tn * TL::T;
+  // Theta^T Theta = -Theta^2
+  if (!TL::template product<true, false>(lds, Th, N, Th, N, (n + 15) / 16, m0, n0, N, N, N, before == 0)) {
+    if (lead) {  // nothing to do, nor for the steps behind this one
+      ctl[RC_STATE + (par ^ 1)] = before;
+      ctl[RC_BITS + par] = 0;
+    }
+    return;
+  }
+  block_sum2<TL::NW>(th2, r2, red);
+  const bool apply = isfinite(th2) && isfinite(r2) && th2 <= kThLimit * n && r2 <= kRLimit * n;
+  const bool last = th2 <= kDone * kDone && r2 <= kDone * kDone;
+  const int bits = !apply ? 0 : RB_APPLY | (th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
+  if (lead) {
+    const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : (last ? RS_DONE : RS_ACTIVE);
+    const int applied = (first ? 0 : ctl[RC_APPLIED]) + (apply ? 1 : 0);
+    const int small = (first ? 0 : ctl[RC_SMALL]) + (apply && th2 <= 4e-6 ? 1 : 0);
+    ctl[RC_STATE + (par ^ 1)] = state;
+    ctl[RC_BITS + par] = bits;
+    ctl[RC_APPLIED] = applied;
+    ctl[RC_SMALL] = small;
+    __hip_atomic_store(&flags[RF_STATE], state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&flags[RF_APPLIED], applied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&flags[RF_SMALL], small, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if (!apply) return;
+  double v[TL::PER];
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    v[e] = -TL::get(lds, r, c);
+  }
+  if (!(bits & RB_CUBE)) {
+    make_x<TL>(lds, Th, N, n, tm, tn, first == 0, X, dsum, dv, evals, [&](int e, int64_t) { return v[e]; },
+               [](int, int) { return 0.0; });
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    if (m0 + r < N && n0 + c < N) S2[static_cast<int64_t>(n0 + c) * N + m0 + r] = v[e];
+  }
+  if (tm != tn) TL::store_mirror(lds, v, S2, N, m0, n0);
+}
+
+// X where Theta^3 counts: the lower tiles of Theta Theta^2, then make_x
+template <class TL>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_ref_cube(const double* __restrict__ Th,
+                                                             const double* __restrict__ S2, int N, int n, int useg,
+                                                             double* __restrict__ X, const double* __restrict__ dsum,
+                                                             const double* __restrict__ dv,
+                                                             double* __restrict__ evals,
+                                                             const int* __restrict__ word) {
+  __shared__ double lds[TL::LDS];
+  const bool go = (*word & RB_CUBE) != 0;
+  int tm, tn;
+  lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
+  // Theta^T Theta^2 = -Theta^3
+  if (!TL::template product<true, false>(lds, Th, N, S2, N, (n + 15) / 16, tm * TL::T, tn * TL::T, N, N, N, go)) return;
+  make_x<TL>(lds, Th, N, n, tm, tn, useg != 0, X, dsum, dv, evals, [&](int, int64_t at) { return S2[at]; },
+             [&](int r, int c) { return -TL::get(lds, r, c); });
+}
+
+template <class TL>
+hipError_t queue_start(hipStream_t st, const RefineStep& a, KTimer* kt) {
+  const int side = ceil_div(a.n, TL::T), low = side * (side + 1) / 2;
+  timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, side * side, TL::THREADS, st, a.C, a.ldc, a.V, a.N, a.n,
+               a.T, a.n, a.ldc, nullptr, 0, 0);
+  k_ref_sg<TL, true><<<low, TL::THREADS, 0, st>>>(a.V, a.T, a.N, a.n, low, a.S, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+template <class TL>
+hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
+  const int N = a.N, side = ceil_div(a.n, TL::T), full = side * side, low = side * (side + 1) / 2;
+  const int nt = N / kCT, tiles = nt * (nt + 1) / 2;
+  int* state = a.ctl + RC_STATE + a.par;
+  int* bits = a.ctl + RC_BITS + a.par;
+  if (!a.first) {
+    timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, full, TL::THREADS, st, a.C, a.ldc, a.V, N, a.n, a.T,
+                 a.n, a.ldc, state, ~0, 0);  // C V (C is symmetric)
+    k_ref_sg<TL, false><<<2 * low, TL::THREADS, 0, st>>>(a.V, a.T, N, a.n, low, a.S, a.X, state);
+  }
+  k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.dv,
+                                     a.first ? nullptr : state);
+  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.par, a.ctl,
+                                                a.flags, a.X, a.dsum, a.dv, a.evals);
+  k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
+  timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, false, false>, full, TL::THREADS, st, a.V, N, a.X, N, a.n, a.Vn, N, N,
+               bits, static_cast<int>(RB_APPLY), static_cast<int>(RB_APPLY));
+  return hipGetLastError();
+}
+
+}  // namespace
+
+constexpr int kSmallFrom = 384, kLargeFrom = 640;
+
+hipError_t launch_refine_start(hipStream_t st, const RefineStep& a, KTimer* kt) {
+  if (a.n >= kLargeFrom) return queue_start<LargeTile>(st, a, kt);
+  return a.n >= kSmallFrom ? queue_start<SmallTile>(st, a, kt) : queue_start<TinyTile>(st, a, kt);
+}
+
+hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
+  if (a.n >= kLargeFrom) return queue_step<LargeTile>(st, a, kt);
+  return a.n >= kSmallFrom ? queue_step<SmallTile>(st, a, kt) : queue_step<TinyTile>(st, a, kt);
+}
+
+}  // namespace cmx
