@@ -173,6 +173,12 @@ struct cmaes {
   size_t split_cap = 0;
   double* u = nullptr;
   EigWork ew{};
+  // the vectors and scalars of cmaes_state / cmaes_set_state pass through this
+  // pinned, mapped host block, one kernel for all of them (dxfer: its device
+  // address); both calls end with the stream drained
+  uint32_t* xfer = nullptr;
+  uint32_t* dxfer = nullptr;
+  size_t xfer_words = 0;
   // small n: the eigensolve runs as a grouped solve of this one descent
   // (convergence tested on the device, several short sweeps per host wait)
   GroupEig ge1{};
@@ -301,6 +307,9 @@ void free_all(cmaes* h) {
   if (h->ew.hflags) (void)hipHostFree(h->ew.hflags);
   h->ew.hflags = nullptr;
   h->ew.dflags = nullptr;
+  if (h->xfer) (void)hipHostFree(h->xfer);
+  h->xfer = h->dxfer = nullptr;
+  h->xfer_words = 0;
   h->hstop = nullptr;
   h->dstop = nullptr;
   h->stop_pending = false;
@@ -335,6 +344,47 @@ int alloc_split(cmaes* h) {
   return 0;
 }
 
+// words of the state block: scalars, five n-vectors, f and the order
+size_t xfer_need(const cmaes* h) {
+  return sizeof(DevScalars) / 4 + 2ull * 5 * h->n + 3ull * h->lam;
+}
+
+int alloc_xfer(cmaes* h) {
+  const size_t need = xfer_need(h);
+  if (need <= h->xfer_words) return 0;
+  if (h->st) (void)hipStreamSynchronize(h->st);
+  if (h->xfer) (void)hipHostFree(h->xfer);
+  h->xfer = h->dxfer = nullptr;
+  h->xfer_words = 0;
+  void *hp = nullptr, *dp = nullptr;
+  if (hipHostMalloc(&hp, 4 * need, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+    return fail(CMAES_ENOMEM, "hipHostMalloc failed");
+  h->xfer = static_cast<uint32_t*>(hp);
+  if (hipHostGetDevicePointer(&dp, hp, 0) != hipSuccess) return fail(CMAES_EDEVICE, "hipHostGetDevicePointer failed");
+  h->dxfer = static_cast<uint32_t*>(dp);
+  h->xfer_words = need;
+  return 0;
+}
+
+// n x n matrices between the caller's packed columns and the device's (leading
+// dimension ldn): one plain copy, through `pack` (n x n doubles of device
+// scratch) and a kernel where the two differ.  A two-dimensional copy from or
+// to pageable memory goes row by row (8 ms for n = 1000 against 1 ms).
+int copy_in(cmaes* h, double* dst, const double* src, double* pack) {
+  const int n = h->n;
+  const bool same = h->ldn == n;
+  CMX_HIP(hipMemcpyAsync(same ? dst : pack, src, 8ull * n * n, hipMemcpyHostToDevice, h->st));
+  if (!same) CMX_HIP(launch_to_precision(h->st, true, pack, n, dst, h->ldn, n, n));
+  return 0;
+}
+int copy_out(cmaes* h, double* dst, const double* src, double* pack) {
+  const int n = h->n;
+  const bool same = h->ldn == n;
+  if (!same) CMX_HIP(launch_to_precision(h->st, true, src, h->ldn, pack, n, n, n));
+  CMX_HIP(hipMemcpyAsync(dst, same ? src : pack, 8ull * n * n, hipMemcpyDeviceToHost, h->st));
+  return 0;
+}
+
 // population-size dependent buffers
 int alloc_pop(cmaes* h) {
   const int n = h->n, ldn = h->ldn, lam = h->lam;
@@ -343,6 +393,7 @@ int alloc_pop(cmaes* h) {
   const int mu = active ? lam : h->hp.kp.mu;
   if (lam <= h->cap_lam && mu <= h->cap_mu && hist_len_for(n, lam) <= h->hist_cap) return alloc_split(h);
   drop_graphs(h);
+  if (int rc0 = alloc_xfer(h)) return rc0;
   free_pop_buffers(h);
   const size_t e = esz(h);
   int rc = 0;
@@ -428,9 +479,9 @@ int upload_objective_derived(cmaes* h);
 
 int upload_objective(cmaes* h) {
   const int n = h->n;
-  if (h->have_R)
-    CMX_HIP(hipMemcpy2DAsync(h->Rd, 8ull * h->ldn, h->R_host.data(), 8ull * n, 8ull * n, n, hipMemcpyHostToDevice,
-                             h->st));
+  if (h->have_R) {
+    if (int rc = copy_in(h, h->Rd, h->R_host.data(), h->ew.X1)) return rc;
+  }
   if (h->have_xstar)
     CMX_HIP(hipMemcpyAsync(h->xstar, h->xstar_host.data(), 8ull * n, hipMemcpyHostToDevice, h->st));
   return upload_objective_derived(h);  // synchronises the stream
@@ -852,12 +903,6 @@ int front(cmaes* h) {
   return 0;
 }
 
-int read_scalars(const cmaes* h, DevScalars* s) {
-  CMX_HIP(hipMemcpyAsync(s, h->sc, sizeof(*s), hipMemcpyDeviceToHost, h->st));
-  CMX_HIP(hipStreamSynchronize(h->st));
-  return 0;
-}
-
 // The stop bits and f_best after everything queued on the handle's stream,
 // read from the mapped host copy: one stream synchronisation (none with
 // sync = false, for a caller that has already waited for that work) and no
@@ -1083,6 +1128,14 @@ extern "C" {
 
 namespace {
 
+// a vector of cmaes_state: the caller's buffer (null: not asked for), the
+// device's, its size in 4-byte words
+struct XferItem {
+  void* host;
+  const void* dev;
+  int words;
+};
+
 // the sampling step of an ask, then x_k = m + sigma y_k staged in dX (n * lam
 // float64 device memory) and copied into the caller's X
 int ask_into(cmaes* h, double* X, double* dX) {
@@ -1196,11 +1249,12 @@ int cmaes_ipop_run(cmaes_t* h, int* descents) {
   for (;;) {
     const int grc = cmaes_generation(h);
     if (grc != CMAES_OK && grc != CMAES_ENUMERIC) return grc;  // ENUMERIC: stop bits are set
-    DevScalars s;
-    if (int rc = read_scalars(h, &s)) return rc;
+    uint32_t stop = 0;
+    double f_best = HUGE_VAL;
+    if (int rc = read_stop_best(h, &stop, &f_best)) return rc;
     const bool budget = h->opt.max_evals > 0 && h->total_evals >= h->opt.max_evals;
-    if (s.stop || budget) {
-      if (s.f_best < h->opt.f_target || budget) break;
+    if (stop || budget) {
+      if (f_best < h->opt.f_target || budget) break;
       const int rc = cmaes_restart_ipop(h);
       if (rc == CMAES_EKMAX) break;
       if (rc) return rc;
@@ -1216,9 +1270,33 @@ int cmaes_state(const cmaes_t* hc, cmaes_state_t* out) {
   if (!out) return fail(CMAES_EINVAL, "null state");
   cmaes_t* h = const_cast<cmaes_t*>(hc);
   if (int rc = ensure_ready(h)) return rc;
+  const int n = h->n;
+  const XferItem items[] = {{out->m, h->m, 2 * n},       {out->p_sigma, h->ps, 2 * n}, {out->p_c, h->pc, 2 * n},
+                            {out->D, h->D, 2 * n},       {out->x_best, h->x_best, 2 * n},
+                            {out->f, h->f, 2 * h->lam},  {out->order, h->order, h->lam}};
+  XferArgs a{};
+  a.dev[0] = h->sc;
+  a.words[0] = sizeof(DevScalars) / 4;
+  a.count = 1;
+  for (const XferItem& it : items)
+    if (it.host) {
+      a.dev[a.count] = it.dev;
+      a.words[a.count++] = it.words;
+    }
+  CMX_HIP(launch_xfer_out(h->st, a, h->dxfer));
+  if (out->C)
+    if (int rc = copy_out(h, out->C, h->C, h->ew.X1)) return rc;
+  if (out->B)
+    if (int rc = copy_out(h, out->B, h->B, h->ew.X2)) return rc;
+  CMX_HIP(hipStreamSynchronize(h->st));
   DevScalars s;
-  if (int rc = read_scalars(h, &s)) return rc;
-  const int n = h->n, ldn = h->ldn;
+  std::memcpy(&s, h->xfer, sizeof(s));
+  const uint32_t* w = h->xfer + a.words[0];
+  for (const XferItem& it : items)
+    if (it.host) {
+      std::memcpy(it.host, w, 4ull * it.words);
+      w += it.words;
+    }
   out->n = n;
   out->lambda = h->lam;
   out->mu = h->hp.kp.mu;
@@ -1232,22 +1310,6 @@ int cmaes_state(const cmaes_t* hc, cmaes_state_t* out) {
   out->kappa = h->hp.kp.kappa;
   out->eig_sweeps = s.jac_sweeps;
   out->eig_corrections = s.jac_corr;
-  auto vec = [&](double* dst, const double* src) -> int {
-    if (dst) CMX_HIP(hipMemcpyAsync(dst, src, 8ull * n, hipMemcpyDeviceToHost, h->st));
-    return 0;
-  };
-  auto mat = [&](double* dst, const double* src) -> int {
-    if (dst) CMX_HIP(hipMemcpy2DAsync(dst, 8ull * n, src, 8ull * ldn, 8ull * n, n, hipMemcpyDeviceToHost, h->st));
-    return 0;
-  };
-  int rc;
-  if ((rc = vec(out->m, h->m)) || (rc = vec(out->p_sigma, h->ps)) || (rc = vec(out->p_c, h->pc)) ||
-      (rc = vec(out->D, h->D)) || (rc = vec(out->x_best, h->x_best)) || (rc = mat(out->C, h->C)) ||
-      (rc = mat(out->B, h->B)))
-    return rc;
-  if (out->f) CMX_HIP(hipMemcpyAsync(out->f, h->f, 8ull * h->lam, hipMemcpyDeviceToHost, h->st));
-  if (out->order) CMX_HIP(hipMemcpyAsync(out->order, h->order, 4ull * h->lam, hipMemcpyDeviceToHost, h->st));
-  CMX_HIP(hipStreamSynchronize(h->st));
   return CMAES_OK;
 }
 
@@ -1257,31 +1319,29 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
   if (in->n != h->n || in->lambda != h->lam) return fail(CMAES_EINVAL, "n / lambda do not match the handle");
   if (!(in->sigma > 0.0) || in->gen < 0) return fail(CMAES_EINVAL, "sigma must be > 0 and gen >= 0");
   if (int rc = ensure_ready(h)) return rc;
-  const int n = h->n, ldn = h->ldn;
-  DevScalars s;
-  CMX_HIP(hipMemcpyAsync(&s, h->sc, sizeof(s), hipMemcpyDeviceToHost, h->st));
-  CMX_HIP(hipStreamSynchronize(h->st));  // also: nothing in flight still writes the state
-  s.sigma = in->sigma;
-  s.gen = in->gen;
-  s.stop = 0;
-  s.hist_count = 0;
-  s.eig_ok = 1;
-  // every copy below is ordered on the handle's stream and has completed
-  // before the call returns (the caller's buffers are then no longer read)
-  CMX_HIP(hipMemcpyAsync(h->sc, &s, sizeof(s), hipMemcpyHostToDevice, h->st));
-  h->gen = in->gen;
-  auto vec_in = [&](double* dst, const double* src) -> int {
-    if (src) CMX_HIP(hipMemcpyAsync(dst, src, 8ull * n, hipMemcpyHostToDevice, h->st));
-    return 0;
+  const int n = h->n;
+  // every copy below is ordered on the handle's stream, behind whatever still
+  // writes the state, and has completed before the call returns (the caller's
+  // buffers are then no longer read)
+  XferArgs a{};
+  uint32_t* w = h->xfer;
+  auto vec_in = [&](double* dst, const double* src) {
+    if (!src) return;
+    std::memcpy(w, src, 8ull * n);
+    a.dev[a.count] = dst;
+    a.words[a.count++] = 2 * n;
+    w += 2 * n;
   };
-  int rc;
-  if ((rc = vec_in(h->m, in->m)) || (rc = vec_in(h->ps, in->p_sigma)) || (rc = vec_in(h->pc, in->p_c)) ||
-      (rc = vec_in(h->D, in->D)))
-    return rc;
+  vec_in(h->m, in->m);
+  vec_in(h->ps, in->p_sigma);
+  vec_in(h->pc, in->p_c);
+  vec_in(h->D, in->D);
+  CMX_HIP(launch_xfer_in(h->st, a, h->dxfer, h->sc, in->sigma, in->gen));
+  h->gen = in->gen;
   if (in->C)
-    CMX_HIP(hipMemcpy2DAsync(h->C, 8ull * ldn, in->C, 8ull * n, 8ull * n, n, hipMemcpyHostToDevice, h->st));
+    if (int rc = copy_in(h, h->C, in->C, h->ew.X1)) return rc;
   if (in->B) {
-    CMX_HIP(hipMemcpy2DAsync(h->B, 8ull * ldn, in->B, 8ull * n, 8ull * n, n, hipMemcpyHostToDevice, h->st));
+    if (int rc = copy_in(h, h->B, in->B, h->ew.X2)) return rc;
     CMX_HIP(hipMemsetAsync(h->ew.gctl, 0, 4ull * GC_WORDS, h->st));  // no previous solve
     h->reorth_sweeps = 0;  // taken as orthogonal
     h->eig_uncounted = false;
@@ -1289,20 +1349,10 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
   }
-  if (in->B || in->D) {
-    // B D in the sampling precision
-    std::vector<double> Bh(static_cast<size_t>(n) * n), Dh(n);
-    CMX_HIP(hipMemcpy2DAsync(Bh.data(), 8ull * n, h->B, 8ull * ldn, 8ull * n, n, hipMemcpyDeviceToHost, h->st));
-    CMX_HIP(hipMemcpyAsync(Dh.data(), h->D, 8ull * n, hipMemcpyDeviceToHost, h->st));
-    CMX_HIP(hipStreamSynchronize(h->st));
-    for (int c = 0; c < n; ++c)
-      for (int r = 0; r < n; ++r) Bh[static_cast<size_t>(c) * n + r] *= Dh[c];
-    CMX_HIP(hipMemcpy2DAsync(h->ew.T, 8ull * ldn, Bh.data(), 8ull * n, 8ull * n, n, hipMemcpyHostToDevice, h->st));
-    CMX_HIP(launch_to_precision(h->st, h->fp64, h->ew.T, ldn, h->BD, ldn, n, n));
-  }
+  if (in->B || in->D)  // B D in the sampling precision
+    CMX_HIP(launch_scale_columns(h->st, h->fp64, n, h->B, h->ldn, h->D, h->BD, h->ldn));
   CMX_HIP(hipStreamSynchronize(h->st));
-  *h->hstop = 0;  // the stop bits were cleared
-  *host_fbest(h) = s.f_best;
+  *h->hstop = 0;  // the stop bits were cleared (f_best stays)
   h->stop_pending = false;
   h->ask_pending = false;
   return CMAES_OK;

@@ -509,6 +509,20 @@ hipError_t launch_sep_eigen(hipStream_t st, bool fp64, int n, const double* C, i
                             DevScalars* sc);
 
 // misc
+// up to 8 device arrays to or from consecutive words of a pinned, mapped host
+// block (device address), one launch for all of them; in: also the scalars a
+// new state sets
+struct XferArgs {
+  const void* dev[8];
+  int words[8];
+  int count;
+};
+hipError_t launch_xfer_out(hipStream_t st, const XferArgs& a, uint32_t* block);
+hipError_t launch_xfer_in(hipStream_t st, const XferArgs& a, const uint32_t* block, DevScalars* sc, double sigma,
+                          int64_t gen);
+// out[:, j] = B[:, j] D_j in the sampling precision
+hipError_t launch_scale_columns(hipStream_t st, bool fp64, int n, const double* B, int ldb, const double* D, void* out,
+                                int ldo);
 // B <- (3 B - T) / 2 with T = B (B^T B) (Newton-Schulz step, rows < n)
 hipError_t launch_polar_step(hipStream_t st, int n, double* B, int ldb, const double* T, int ldt);
 hipError_t launch_set_identity(hipStream_t st, double* A, int n, int ld);

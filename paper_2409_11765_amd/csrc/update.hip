@@ -420,8 +420,70 @@ __global__ void k_convert(const double* __restrict__ s, int lds, T* __restrict__
   d[static_cast<int64_t>(c) * ldd + r] = static_cast<T>(s[static_cast<int64_t>(c) * lds + r]);
 }
 
+// word i of the block belongs to the array whose run of words holds it
+__device__ __forceinline__ uint32_t* xfer_word(const XferArgs& a, int i) {
+  for (int k = 0; k < a.count; ++k) {
+    if (i < a.words[k]) return static_cast<uint32_t*>(const_cast<void*>(a.dev[k])) + i;
+    i -= a.words[k];
+  }
+  return nullptr;
+}
+__global__ void __launch_bounds__(256) k_xfer_out(XferArgs a, uint32_t* __restrict__ block) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t* p = xfer_word(a, i);
+  if (p) block[i] = *p;
+}
+__global__ void __launch_bounds__(256) k_xfer_in(XferArgs a, const uint32_t* __restrict__ block,
+                                                 DevScalars* __restrict__ sc, double sigma, int64_t gen) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  uint32_t* p = xfer_word(a, i);
+  if (p) *p = block[i];
+  if (i == 0) {
+    sc->sigma = sigma;
+    sc->gen = gen;
+    sc->stop = 0;
+    sc->hist_count = 0;
+    sc->eig_ok = 1;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_scale_columns(int n, const double* __restrict__ B, int ldb,
+                                                       const double* __restrict__ D, T* __restrict__ out, int ldo) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y;
+  if (r < n) out[static_cast<int64_t>(c) * ldo + r] = static_cast<T>(B[static_cast<int64_t>(c) * ldb + r] * D[c]);
+}
+
 }  // namespace
 
+namespace {
+int xfer_blocks(const XferArgs& a) {
+  int total = 1;
+  for (int k = 0; k < a.count; ++k) total += a.words[k];
+  return ceil_div(total, 256);
+}
+}  // namespace
+
+hipError_t launch_xfer_out(hipStream_t st, const XferArgs& a, uint32_t* block) {
+  k_xfer_out<<<xfer_blocks(a), 256, 0, st>>>(a, block);
+  return hipGetLastError();
+}
+
+hipError_t launch_xfer_in(hipStream_t st, const XferArgs& a, const uint32_t* block, DevScalars* sc, double sigma,
+                          int64_t gen) {
+  k_xfer_in<<<xfer_blocks(a), 256, 0, st>>>(a, block, sc, sigma, gen);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_columns(hipStream_t st, bool fp64, int n, const double* B, int ldb, const double* D, void* out,
+                                int ldo) {
+  const dim3 grid(ceil_div(n, 256), n);
+  if (fp64)
+    k_scale_columns<double><<<grid, 256, 0, st>>>(n, B, ldb, D, static_cast<double*>(out), ldo);
+  else
+    k_scale_columns<float><<<grid, 256, 0, st>>>(n, B, ldb, D, static_cast<float*>(out), ldo);
+  return hipGetLastError();
+}
 
 // the rank work area (int32 elements): sorted keys (double, 2 words each),
 // their indices, then the per-group counts
