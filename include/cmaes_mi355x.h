@@ -313,7 +313,9 @@ int cmaes_enable_graphs(cmaes_t* h, int on);
  * 1); max_angle_norm in [0, 2e-3] (default 2e-3).  CMAES_EINVAL outside that
  * range.  cmaes_state() reports the sweeps (with the steps before the closing
  * ones) and corrections (rejected ones included) of the last eigensolve.
- * Concurrent descents (cmaes_batch_*, cmaes_krep_*) sweep only. */
+ * Concurrent descents (cmaes_batch_*, cmaes_krep_*) of n > 64 sweep only; up
+ * to n = 64 every descent is solved whole in one workgroup, whatever the
+ * setting, and its sweeps and steps are reported together. */
 int cmaes_set_eigen_correction(cmaes_t* h, int on, double max_angle_norm);
 int cmaes_enable_kernel_timing(cmaes_t* h, int on);
 int cmaes_kernel_times(const cmaes_t* h, double* total_us, int64_t* calls);

@@ -291,6 +291,7 @@ void free_all(cmaes* h) {
   dev_free(h, h->ew.X1);
   dev_free(h, h->ew.X2);
   dev_free(h, h->ew.X3);
+  dev_free(h, h->ew.V2);
   dev_free(h, h->ew.dsum);
   dev_free(h, h->ew.dv);
   dev_free(h, h->ew.rctl);
@@ -441,7 +442,8 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.Q, 8ull * (N / 32) * 32 * 32)) || (rc = dev_alloc(h, &h->ew.T, 8 * nn)) ||
       (rc = dev_alloc(h, &h->ew.A2, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.Q2, 8ull * (N / 32) * 32 * 32)) ||
       (rc = dev_alloc(h, &h->ew.X1, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.X2, 8ull * N * N)) ||
-      (rc = dev_alloc(h, &h->ew.X3, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.dsum, 8ull * (N / 32) * N)) ||
+      (rc = dev_alloc(h, &h->ew.X3, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.V2, 8ull * N * N)) ||
+      (rc = dev_alloc(h, &h->ew.dsum, 8ull * (N / 32) * N)) ||
       (rc = dev_alloc(h, &h->ew.dv, 8ull * N)) || (rc = dev_alloc(h, &h->ew.rctl, 4ull * 8)) ||
       (rc = dev_alloc(h, &h->ew.evals, 8ull * N)) || (rc = dev_alloc(h, &h->ew.perm, 4ull * N)) ||
       (rc = dev_alloc(h, &h->ew.sign, 8ull * N)) || (rc = dev_alloc(h, &h->ew.scale, 16)) ||
@@ -449,7 +451,7 @@ int alloc_fixed(cmaes* h) {
     return rc;
   {
     const int q = N / 32;
-    if ((rc = dev_alloc(h, &h->ew.part, 8ull * 3 * std::max(n, q * (q + 1) / 2)))) return rc;
+    if ((rc = dev_alloc(h, &h->ew.part, 8ull * 4 * std::max(n, q * (q + 1) / 2)))) return rc;
   }
   // convergence flags (words 0-3), the stop bits (word 4), f_best (words 6-7)
   // and the refinement's outcome (words 8-10): pinned, mapped host memory the
@@ -536,6 +538,8 @@ int init_descent(cmaes* h, bool fresh) {
   h->ew.last_sweeps = 0;
   h->ew.last_closed = false;
   h->ew.last_steps = 0;
+  h->ew.hold = 0;
+  h->ew.backoff = 2;
   refresh_stop_params(h);
   return 0;
 }
@@ -686,7 +690,7 @@ int phase_update_pre(cmaes* h) {
     kt_end(&h->kt);
     CMX_HIP(launch_polar_step(h->st, n, h->B, ldn, h->ew.T, ldn));
   }
-  if (h->ew.N == kWholeSolveN) {  // the single-workgroup solve forms its own warm start
+  if (h->ew.N <= kWholeSolveN) {  // the single-workgroup solve forms its own warm start
     eigen_begin_host(h->ew);
     return 0;
   }
@@ -717,13 +721,14 @@ void advance_counters(cmaes* h) {
   h->total_evals += h->lam;
 }
 
+constexpr int kMaxSweeps = 40;  // of one eigensolve
 // one step of the eigensolve in flight (the stream must have been
 // synchronised since the last call); *done once the decomposition is final
 int eigen_advance(cmaes* h, bool* done, bool ahead = false) {
   // a decomposition that does not converge within the sweep limit (or meets
   // non-finite values) clears eig_ok on the device, which raises the
   // ConditionCov stop bit
-  return eigen_step(h->st, h->n, h->C, h->ldn, h->B, h->ldn, h->D, h->BD, h->fp64, h->ldn, h->ew, h->sc, 40, &h->kt,
+  return eigen_step(h->st, h->n, h->C, h->ldn, h->B, h->ldn, h->D, h->BD, h->fp64, h->ldn, h->ew, h->sc, kMaxSweeps, &h->kt,
                     h->graphs && h->st != nullptr && !h->timing, done, ahead);
 }
 // the eigensolve of the generation just queued: its first batch of sweeps
@@ -738,10 +743,8 @@ int eigen_run(cmaes* h) {
   return 0;
 }
 
-// stop tests, then fold the optional timers
+// behind the stop tests: their event, then the optional timers
 int phase_update_post(cmaes* h) {
-  CMX_HIP(launch_stop(h->st, h->hp.kp, h->sp, h->m, h->C, h->ldn, h->B, h->ldn, h->D, h->pc, h->hist, h->sc,
-                      h->dstop));
   CMX_HIP(hipEventRecord(h->ev_stop, h->st));
   h->stop_pending = true;
   rec(h, 6);
@@ -775,48 +778,61 @@ int numeric_failure(const cmaes* h) {
 
 GEigDesc eig_desc(cmaes* h);
 
-// the eigensolve of the generation just queued, as a grouped solve of this
-// descent (no closing correction); *nonfinite when it met non-finite values
-int eigen_run_small(cmaes* h, bool* nonfinite) {
-  if (h->ge1_epoch != h->epoch || h->ge1.count != 1) {
-    if (int rc = group_eig_build(h->st, h->ge1, std::vector<GEigDesc>{eig_desc(h)})) return rc;
-    h->ge1_epoch = h->epoch;
-  }
-  GroupDueMask due{};
-  due.w[0] = 1u;
-  const int last = h->ew.last_sweeps;
-  int sweeps = 0, code = 1;
-  if (int rc = group_eig_solve(h->st, h->ge1, due, 40, last >= 2 ? last - 1 : 0, &sweeps, &code)) return rc;
-  h->ew.sweeps = sweeps;
-  h->ew.corrections = 0;
-  h->ew.last_sweeps = sweeps;
-  h->ew.last_closed = false;
-  h->ew.last_steps = 0;
-  h->ew.refined = false;
-  h->ew.pending = false;
-  *nonfinite = code == 3;
+// the device table of a single-workgroup eigensolve (n <= 64), loaded once per
+// set of buffers; outside any capture
+int small_ready(cmaes* h) {
+  if (h->ew.N > kWholeSolveN || h->ew.grouped || (h->ge1_epoch == h->epoch && h->ge1.count == 1)) return 0;
+  if (int rc = group_eig_build(h->st, h->ge1, std::vector<GEigDesc>{eig_desc(h)})) return rc;
+  h->ge1_epoch = h->epoch;
   return 0;
 }
+
+// the end of a generation that needs no decision of the host's: the
+// single-workgroup eigensolve, if one is due, and the stop tests
+int queue_tail(cmaes* h) {
+  if (h->eig_due) {
+    GroupDueMask due{};
+    due.w[0] = 1u;
+    CMX_HIP(group_eig_whole(h->st, h->ge1, due, kMaxSweeps));
+  }
+  CMX_HIP(launch_stop(h->st, h->hp.kp, h->sp, h->m, h->C, h->ldn, h->B, h->ldn, h->D, h->pc, h->hist, h->sc,
+                      h->dstop));
+  return 0;
+}
+// whether a generation ends so (a group's descents are solved and tested with it)
+bool tail_queued(const cmaes* h) { return !h->ew.grouped && (!h->eig_due || h->ew.N <= kWholeSolveN); }
 
 // the rest of a generation after its front: the eigensolve if due, then the
 // stop tests
 int finish_generation(cmaes* h) {
   bool nonfinite = false;
-  if (h->eig_due) {
-    if (h->ew.N <= kSmallEigenN) {
-      if (int rc = eigen_run_small(h, &nonfinite)) return rc;
-    } else {
-      if (int rc = eigen_run(h)) return rc;
-      nonfinite = h->ew.hflags[1] != 0;
-    }
+  if (!tail_queued(h)) {
+    if (int rc = eigen_run(h)) return rc;
+    nonfinite = h->ew.hflags[1] != 0;
+    CMX_HIP(launch_stop(h->st, h->hp.kp, h->sp, h->m, h->C, h->ldn, h->B, h->ldn, h->D, h->pc, h->hist, h->sc,
+                        h->dstop));
   }
   if (int rc = phase_update_post(h)) return rc;
+  if (h->eig_due && h->ew.N <= kWholeSolveN) {
+    CMX_HIP(hipStreamSynchronize(h->st));
+    h->stop_pending = false;
+    h->ew.sweeps = h->ew.last_sweeps = __atomic_load_n(&h->ge1.hflags[1], __ATOMIC_ACQUIRE);
+    nonfinite = __atomic_load_n(&h->ge1.hflags[1 + kGroupMax], __ATOMIC_ACQUIRE) == 3;
+    h->ew.corrections = 0;
+    h->ew.last_closed = false;
+    h->ew.last_steps = 0;
+    h->ew.refined = true;
+    h->ew.pending = false;
+  }
   return nonfinite ? numeric_failure(h) : 0;
 }
 
 int phase_update(cmaes* h) {
   set_due(h);
+  if (int rc = small_ready(h)) return rc;
   if (int rc = phase_update_pre(h)) return rc;
+  if (tail_queued(h))
+    if (int rc = queue_tail(h)) return rc;
   advance_counters(h);
   return finish_generation(h);
 }
@@ -858,19 +874,24 @@ uint64_t front_key(const cmaes* h, bool due) {
   for (int i = 0; i < G32_NUM_SITES; ++i) mix(static_cast<uint64_t>(h->gcfg[i]));
   mix(due ? 1u : 0u);
   mix(h->reorth_due ? 1u : 0u);
-  mix(h->ew.refines() ? 3u : 5u);
+  mix((h->ew.refines() ? 3u : 5u) + (h->ew.grouped ? 8u : 0u));
   return k | 1u;  // never 0 (0 marks an empty slot)
 }
 
-// the launches of a generation up to the eigensolve set-up, eagerly or by
+// the launches of a generation up to the eigensolve set-up (or to its end, see
+// queue_tail), eagerly or by
 // replaying a captured graph; then the host counters
 int front(cmaes* h) {
   set_due(h);
+  if (int rc = small_ready(h)) return rc;
+  const bool tail = tail_queued(h);
   const bool can_graph = h->graphs && h->st != nullptr && !h->timing && !h->kt.on;
   if (!can_graph) {
     if (int rc = phase_sample(h, nullptr)) return rc;
     if (int rc = phase_fitness(h)) return rc;
     if (int rc = phase_update_pre(h)) return rc;
+    if (tail)
+      if (int rc = queue_tail(h)) return rc;
     advance_counters(h);
     return 0;
   }
@@ -884,6 +905,7 @@ int front(cmaes* h) {
     int rc = phase_sample(h, nullptr);
     if (!rc) rc = phase_fitness(h);
     if (!rc) rc = phase_update_pre(h);
+    if (!rc && tail) rc = queue_tail(h);
     hipGraph_t g = nullptr;
     const hipError_t ce = hipStreamEndCapture(h->st, &g);
     if (rc) {
@@ -1348,6 +1370,8 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     h->ew.last_sweeps = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
+    h->ew.hold = 0;
+    h->ew.backoff = 2;
   }
   if (in->B || in->D)  // B D in the sampling precision
     CMX_HIP(launch_scale_columns(h->st, h->fp64, n, h->B, h->ldn, h->D, h->BD, h->ldn));
@@ -1846,7 +1870,7 @@ int grouped_front(LockstepGroup& g, const std::vector<cmaes*>& hs, const GroupDu
   bool any_begin = false;
   for (int i = 0; i < count; ++i)
     if (due_mask_bit(due, i)) {
-      if (hs[i]->ew.N == kWholeSolveN)
+      if (hs[i]->ew.N <= kWholeSolveN)
         begin.w[i >> 5] &= ~(1u << (i & 31));
       else
         any_begin = true;
@@ -1950,7 +1974,7 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
           CMX_HIP(hipStreamWaitEvent(g.st, g.ev[i], 0));
         }
     g.sweeps.assign(count, 0);
-    if (int rc = group_eig_solve(g.st, g.ge, due, 40, ahead, g.sweeps.data(), nullptr)) return rc;
+    if (int rc = group_eig_solve(g.st, g.ge, due, kMaxSweeps, ahead, g.sweeps.data(), nullptr)) return rc;
     if (!grouped) CMX_HIP(hipEventRecord(g.done, g.st));
     for (int i = 0; i < count; ++i)
       if (hs[i]->eig_due) {
@@ -1961,7 +1985,7 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
         h->ew.last_sweeps = g.sweeps[i];
         h->ew.last_closed = false;
         h->ew.last_steps = 0;
-        h->ew.refined = false;
+        h->ew.refined = h->ew.N <= kWholeSolveN;
         h->ew.pending = false;
       }
   }
@@ -1983,8 +2007,11 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     return 0;
   }
   g.synced = false;
-  for (cmaes* h : hs)
+  for (cmaes* h : hs) {
+    CMX_HIP(launch_stop(h->st, h->hp.kp, h->sp, h->m, h->C, h->ldn, h->B, h->ldn, h->D, h->pc, h->hist, h->sc,
+                        h->dstop));
     if (int rc = phase_update_post(h)) return rc;
+  }
   return 0;
 }
 

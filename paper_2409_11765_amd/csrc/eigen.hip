@@ -36,11 +36,13 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <functional>
 #include <vector>
 
 #include "internal.h"
+#include "refine.h"
 
 namespace cmx {
 
@@ -54,36 +56,11 @@ constexpr double kOffTol = 1e-13;
 // the angles satisfy ||Theta||_F <= EigWork::corr_max_theta (at most 2e-3)
 constexpr double kCorrOff = 1e-8;
 constexpr int kMaxCorrections = 4;  // per solve
-constexpr int kMaxSteps = 16;  // refinement steps per solve before it is done by sweeps
+constexpr int kMaxSteps = 24;  // refinement steps before more sweeps
+constexpr int kMaxBackoff = 32;
+constexpr int kMaxRecoveries = 3;  // per solve, before it is done by sweeps alone
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-// Jacobi rotation J = [[c, s], [-s, c]] on (a, b) that annihilates (J^T S J)_ab
-// up to the accuracy of t (Golub & Van Loan, sym.schur2): t = sign(delta) 2 d /
-// (|delta| + sqrt(delta^2 + 4 d^2)) with delta = S_bb - S_aa, d = S_ab;
-// c = 1/sqrt(1 + t^2), s = t c; the identity when |d| <= thr.
-// t only decides how far the entry is reduced, so it is formed in float32 from
-// the entries scaled by inv = 1/max|a_ii| (relative error ~1e-7: the entry
-// drops to ~1e-7 of itself and later rotations remove the rest).  c is then
-// refined to float64 precision from that t by two Newton steps, because
-// c^2 (1 + t^2) = 1 is what keeps each rotation, and so Q, orthogonal.
-// Branch free, so the callers' loads issue up front and two rotations
-// interleave.
-__device__ __forceinline__ void jacobi_rotation(double saa, double sbb, double d, double thr, double inv, double& c,
-                                                double& s) {
-  const double dd = fabs(d) > thr ? d : 0.0;
-  const float df = static_cast<float>(dd * inv);
-  const float delta = static_cast<float>((sbb - saa) * inv);
-  const float h = __builtin_amdgcn_sqrtf(fmaf(delta, delta, 4.0f * df * df));
-  // |delta| + h >= 2 |df| > 0 whenever df != 0; the floor only guards 0 / 0
-  const float tf = (delta >= 0.0f ? 2.0f : -2.0f) * df * __builtin_amdgcn_rcpf(fmaxf(fabsf(delta) + h, 1e-30f));
-  const double t = static_cast<double>(tf);
-  const double x = fma(t, t, 1.0);
-  double y = static_cast<double>(__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.0f)));
-  y = y * fma(-0.5 * x * y, y, 1.5);
-  c = y * fma(-0.5 * x * y, y, 1.5);
-  s = t * c;
-}
 
 // round-robin (circle method) pairing of `p` players, round r, pair k
 __device__ __forceinline__ void rr_pair(int p, int r, int k, int& a, int& b) {
@@ -967,7 +944,7 @@ __global__ void __launch_bounds__(256) kg_start(const GEigDesc* __restrict__ g, 
   __shared__ int cnt[256];
   int act = 0;
   for (int i = threadIdx.x; i < count; i += 256) {
-    if (g[i].N == kS) continue;  // N = 32: kg_small_solve
+    if (g[i].N <= kWholeSolveN) continue;  // solved whole by a workgroup of its own
     int* c = g[i].ctl;
     const int d = due_bit(due, i) ? 1 : 0;
     c[GC_DUE] = d;
@@ -1112,211 +1089,6 @@ __global__ void __launch_bounds__(256) kg_round(const GEigDesc* __restrict__ g, 
                  rl == p - 2 ? e.part : nullptr, lds);
 }
 
-// ---- whole solve of a descent with N = 32 (n <= 32) in one workgroup, from
-// the warm start to the canonical B, D and B D.  The warm start A = B_old^T C
-// B_old and V = B_old are formed in LDS, and whether to sweep at all is decided
-// from A's off-diagonal norm and the previous solve's sweep count as kg_start
-// decides it.  With two blocks there is a single block pair, so a sweep is one
-// pair solve on the whole matrix: the rotations of rotate_pair (intra-block
-// rounds, then cross rounds) give Q, then A <- Q^T A Q and V <- V Q are formed
-// on the float64 matrix cores, and the off-diagonal norm decides on the next
-// sweep, all inside the kernel.  The stopping rule, the rotation threshold
-// (from the previous max |a_ii|) and the sweep accounting are those of
-// kg_round; the finishing steps (ranks, column signs, canonical B, D and B D)
-// follow in the same workgroup.  Later launches of a mixed group skip the
-// descent (kg_start leaves it alone, its due word is cleared).
-
-// P = X Y for 32 x 32 matrices in LDS (row stride kLD), X given as X(r, k) =
-// xs[r * kLD + k] or, with XT, as xs[k * kLD + r]; each of the four waves
-// forms one 16 x 16 block of P (mfma_k32 layout)
-template <bool XT>
-__device__ __forceinline__ doublex4 small_product(const double* xs, const double* ys, int bi, int bj) {
-  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  double a[8], b[8];
-#pragma unroll
-  for (int s2 = 0; s2 < 8; ++s2) {
-    const int k = 4 * s2 + lk;
-    a[s2] = XT ? xs[k * kLD + bi * kNB + li] : xs[(bi * kNB + li) * kLD + k];
-    b[s2] = ys[k * kLD + bj * kNB + li];
-  }
-  return mfma_k32(a, b);
-}
-
-// off-diagonal / total squared norms over the n x n part of Aw and max
-// |a_ii|: one column per thread, then the columns in order by thread 0, which
-// gets the flags (as offnorm_flags) and the new scale in red[2][0]
-__device__ __forceinline__ void small_offnorm(const double* Aw, int n, double (*red)[kS], int& more, int& nonfin) {
-  const int t = threadIdx.x;
-  if (t < kS) {
-    double off = 0.0, tot = 0.0;
-    for (int r = 0; r < n; ++r) {
-      const double v = Aw[r * kLD + t];
-      tot += v * v;
-      if (r != t) off += v * v;
-    }
-    red[0][t] = t < n ? off : 0.0;
-    red[1][t] = t < n ? tot : 0.0;
-    red[2][t] = t < n ? fabs(Aw[t * kLD + t]) : 0.0;
-  }
-  __syncthreads();
-  if (t == 0) {
-    double off = 0.0, tot = 0.0, dmax = 0.0;
-    for (int k = 0; k < kS; ++k) {
-      off += red[0][k];
-      tot += red[1][k];
-      dmax = fmax(dmax, red[2][k]);
-    }
-    red[2][0] = dmax;
-    int small;
-    offnorm_flags(off, tot, more, nonfin, small);
-  }
-}
-
-__global__ void __launch_bounds__(256) kg_small_solve(const GEigDesc* __restrict__ g, int count, GroupDueMask due,
-                                                      int max_sweeps, int* __restrict__ hsweeps) {
-  __shared__ double Aw[kS * kLD], S0[kS * kLD], S1[kS * kLD], Q[kS * kLD], Vw[kS * kLD], T[kS * kLD];
-  __shared__ double red[3][kS];
-  __shared__ double ev[kS], sgn[kS];
-  __shared__ int perm[kS];
-  __shared__ int go;
-  const int i = blockIdx.x;
-  if (i >= count) return;
-  const GEigDesc& e = g[i];
-  if (e.N != kS) return;
-  int* c = e.ctl;
-  const int n = e.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int li = lane & 15, lk = lane >> 4, bi = w & 1, bj = w >> 1;
-  if (!due_mask_bit(due, i)) {
-    if (t == 0) c[GC_DUE] = 0;
-    return;
-  }
-  // warm start: C and V = B_old padded with zeros / the identity; T = C V,
-  // then A = V^T T (mirrored from its lower half)
-  for (int idx = t; idx < kS * kS; idx += 256) {
-    const int r = idx % kS, cc = idx / kS;
-    const bool in = r < n && cc < n;
-    S0[r * kLD + cc] = in ? e.C[static_cast<int64_t>(cc) * e.ldc + r] : 0.0;
-    Vw[r * kLD + cc] = in ? e.B[static_cast<int64_t>(cc) * e.ldb + r] : (r == cc ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  {
-    const doublex4 cv = small_product<false>(S0, Vw, bi, bj);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) T[(bi * kNB + lk + 4 * rr) * kLD + bj * kNB + li] = cv[rr];
-    __syncthreads();
-    const doublex4 vt = small_product<true>(Vw, T, bi, bj);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) Aw[(bi * kNB + lk + 4 * rr) * kLD + bj * kNB + li] = vt[rr];
-    __syncthreads();
-    for (int idx = t; idx < kS * kS; idx += 256) {
-      const int r = idx / kS, cc = idx % kS;
-      if (r < cc) Aw[r * kLD + cc] = Aw[cc * kLD + r];
-    }
-    __syncthreads();
-  }
-  int done = 0, more = 0, nonfin = 0;
-  small_offnorm(Aw, n, red, more, nonfin);
-  // whether to sweep (kg_start): at least last - 1 sweeps after a solve of
-  // `last` sweeps, else only while the warm start is not diagonal enough
-  const int last = c[GC_LAST];
-  const int mins = last >= 2 ? min(last - 1, max_sweeps) : 0;
-  if (t == 0) go = (mins > 0 || (more && !nonfin)) ? 1 : 0;
-  __syncthreads();
-  const bool active = go != 0;
-  double scale = red[2][0];
-  __syncthreads();
-  while (active) {
-    for (int idx = t; idx < kS * kS; idx += 256) S0[(idx / kS) * kLD + idx % kS] = Aw[(idx / kS) * kLD + idx % kS];
-    __syncthreads();
-    rotate_pair(S0, S1, Q, 2.2e-16 * scale, scale > 0.0 ? 1.0 / scale : 0.0, true, nullptr, false, kNB >= n);
-    // T = A Q and V Q (into S1), then A = Q^T T, mirrored from its lower half
-    const doublex4 aq = small_product<false>(Aw, Q, bi, bj);
-    const doublex4 vq = small_product<false>(Vw, Q, bi, bj);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      T[(bi * kNB + lk + 4 * rr) * kLD + bj * kNB + li] = aq[rr];
-      S1[(bi * kNB + lk + 4 * rr) * kLD + bj * kNB + li] = vq[rr];
-    }
-    __syncthreads();
-    const doublex4 qt = small_product<true>(Q, T, bi, bj);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) Aw[(bi * kNB + lk + 4 * rr) * kLD + bj * kNB + li] = qt[rr];
-    __syncthreads();
-    for (int idx = t; idx < kS * kS; idx += 256) {
-      const int r = idx / kS, cc = idx % kS;
-      if (r < cc) Aw[r * kLD + cc] = Aw[cc * kLD + r];
-      Vw[r * kLD + cc] = S1[r * kLD + cc];
-    }
-    __syncthreads();
-    small_offnorm(Aw, n, red, more, nonfin);
-    if (t == 0) {
-      ++done;
-      go = (done < max_sweeps && (done < mins || (more && !nonfin))) ? 1 : 0;
-    }
-    __syncthreads();
-    scale = red[2][0];
-    if (!go) break;
-    __syncthreads();
-  }
-  if (t == 0) {
-    int* st = e.status;
-    st[0] = nonfin ? 3 : (more ? 2 : 1);
-    st[1] = done;
-    st[2] = 0;
-    c[GC_LAST] = done;
-    c[GC_STOPR] = 0;
-    c[GC_DUE] = 0;
-    __hip_atomic_store(&hsweeps[i], done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&hsweeps[kGroupMax + i], st[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  // finishing steps, as kg_rank / kg_colsign / kg_permute: ascending
-  // eigenvalues (ties by index), each column's largest-magnitude entry (first
-  // on ties) positive, then B, D and B D in that order
-  if (t < kS) {
-    ev[t] = Aw[t * kLD + t];
-    perm[t] = t;  // (non-finite eigenvalues can leave ranks unassigned)
-  }
-  __syncthreads();
-  if (t < n) {
-    const double vi = ev[t];
-    int cnt = 0;
-    for (int j = 0; j < n; ++j) cnt += (ev[j] < vi) || (ev[j] == vi && j < t);
-    perm[cnt] = t;
-    e.perm[cnt] = t;
-    e.evals[t] = vi;
-    double best = -1.0;
-    int arg = 0;
-    for (int r = 0; r < n; ++r) {
-      const double v = fabs(Vw[r * kLD + t]);
-      if (v > best) {
-        best = v;
-        arg = r;
-      }
-    }
-    sgn[t] = Vw[arg * kLD + t] < 0.0 ? -1.0 : 1.0;
-    e.sign[t] = sgn[t];
-    if (cnt == 0) {
-      const int* st = e.status;
-      e.sc->eig_ok = (vi > 0.0 && st[0] == 1) ? 1 : 0;
-      e.sc->jac_sweeps = st[1];
-      e.sc->jac_corr = st[2];
-    }
-  }
-  __syncthreads();
-  for (int idx = t; idx < n * n; idx += 256) {
-    const int r = idx / n, row = idx % n;  // output column r, row
-    const int cc = min(max(perm[r], 0), n - 1);
-    const double d = sqrt(fmax(ev[cc], 0.0));
-    const double v = sgn[cc] * Vw[row * kLD + cc];
-    if (row == 0) e.D[r] = d;
-    e.B[static_cast<int64_t>(r) * e.ldb + row] = v;
-    if (e.bd64)
-      static_cast<double*>(e.BD)[static_cast<int64_t>(r) * e.ldbd + row] = v * d;
-    else
-      static_cast<float*>(e.BD)[static_cast<int64_t>(r) * e.ldbd + row] = static_cast<float>(v * d);
-  }
-}
-
 // the finishing steps of every descent that solved: eigenvalue ranks, column
 // signs, then the canonical B, D and B D (A and V as left by its last round)
 __global__ void __launch_bounds__(256) kg_rank(const GEigDesc* __restrict__ g, const int* __restrict__ off,
@@ -1372,7 +1144,7 @@ void eigen_begin_host(EigWork& w) {
   w.corr_blocked = false;
   w.pending = true;
   w.steps = 0;
-  w.refine_blocked = false;
+  w.recoveries = 0;
   w.refined = false;
 }
 
@@ -1432,7 +1204,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
   const int N = w.N;
   const int p = N / kNB, q = p / 2;
   const int ntiles = q * (q + 1) / 2;
-  const bool refine = w.refines() && !w.refine_blocked;
+  const bool refine = w.refines() && w.recoveries <= kMaxRecoveries;
   // ahead: the first batch of a warm-started solve, queued behind the warm
   // start before its flags are read (a solve after one that took several
   // sweeps needs at least that batch; on a converged or non-finite warm
@@ -1500,10 +1272,11 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
     }
     return 0;
   };
-  // `count` refinement steps behind what is queued.  The eigenvectors
-  // alternate between V and Anext with the step's parity; A holds S.  A first
-  // step that the device rejects leaves A, V and the pair solves carried over
-  // from the last sweep as they are, and the steps behind it return at once.
+  // `count` refinement steps behind what is queued.  The eigenvectors after j
+  // steps are in refined(j) (V itself stays as the sweeps left it); A holds S.  A
+  // first step that the device rejects leaves A, V and the pair solves carried
+  // over from the last sweep as they are, and the steps behind it return at once.
+  auto refined = [&](int j) { return j == 0 ? w.V : j & 1 ? w.Anext : w.V2; };
   auto steps = [&](int count) -> int {
     for (int i = 0; i < count; ++i, ++w.steps) {
       const int par = w.steps & 1;
@@ -1512,8 +1285,8 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.N = N;
       a.C = C;
       a.ldc = ldc;
-      a.V = par ? w.Anext : w.V;
-      a.Vn = par ? w.V : w.Anext;
+      a.V = refined(w.steps);
+      a.Vn = refined(w.steps + 1);
       a.S = w.Acur;
       a.Th = w.X2;
       a.X = w.X1;
@@ -1527,9 +1300,11 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.flags = w.dflags;
       a.par = par;
       a.first = w.steps == 0;
+      const bool careful = a.first && (w.recoveries > 0 || w.hold > 0);
+      a.thmax = (careful ? kThCareful : kThLimit) * n;
       const int in2 = w.Acur == w.A ? 0 : 1;
-      if (const int rc = run(a.first ? 6 + in2 : 8 + 2 * in2 + par, [&] { return launch_refine_step(st, a, kt); }))
-        return rc;
+      const int slot = !a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2;
+      if (const int rc = run(slot, [&] { return launch_refine_step(st, a, kt); })) return rc;
     }
     return 0;
   };
@@ -1552,6 +1327,35 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
     return 0;
   };
 
+  // The steps went astray or do not get there: sweeps go on from V, from its
+  // V^T C V formed afresh, and steps wait for small angles; after
+  // kMaxRecoveries the solve starts over without any.
+  auto recover = [&]() -> int {
+    const int count = ++w.recoveries;
+    if (count > kMaxRecoveries) {
+      const int rc = eigen_begin(st, n, C, ldc, B, ldb, w, kt);
+      w.recoveries = count;
+      return rc;
+    }
+    RefineStep a{};
+    a.n = n;
+    a.N = N;
+    a.C = C;
+    a.ldc = ldc;
+    a.T = w.X3;
+    a.V = w.V;
+    a.S = w.Acur;
+    CMX_HIP(launch_refine_start(st, a, kt));
+    k_offnorm_cols<<<n, 256, 0, st>>>(w.Acur, N, n, w.part);
+    k_offnorm_final<<<1, 256, 0, st>>>(w.part, n, w.dflags, w.scale, w.gctl);
+    CMX_HIP(hipGetLastError());
+    w.fresh = true;
+    w.steps = 0;
+    if (w.sweeps < max_sweeps)
+      if (const int rc = sweeps(1)) return rc;
+    return steps(1);
+  };
+
   if (refine) {
     if (ahead) {
       // the spectrum spreads from one generation to the next, so a solve
@@ -1571,7 +1375,15 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
         w.last_steps = applied;
         w.last_closed = false;
         w.refined = true;
-        return finish(applied & 1 ? w.Anext : w.V, w.evals, 1, 1, w.sweeps + applied - small, small);
+        if (w.recoveries > 0) {
+          w.hold = w.backoff;
+          w.backoff = std::min(2 * w.backoff, kMaxBackoff);
+        } else if (w.hold > 0) {
+          --w.hold;
+        } else {
+          w.backoff = 2;
+        }
+        return finish(refined(applied), w.evals, 1, 1, w.sweeps + applied - small, small);
       }
       if (state == RS_ACTIVE && applied < kMaxSteps)
         return steps(applied == 1 ? std::max(2, std::min(w.last_steps, kMaxSteps) - 1) : 1);
@@ -1580,12 +1392,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
         w.steps = 0;
         return steps(1);
       }
-      if (state == RS_ACTIVE || state == RS_DIVERGED) {
-        // from the start again, by sweeps
-        if (const int rc = eigen_begin(st, n, C, ldc, B, ldb, w, kt)) return rc;
-        w.refine_blocked = true;
-        return 0;
-      }
+      if (state == RS_ACTIVE || state == RS_DIVERGED) return recover();
     }
     // a converged warm start, non-finite values, or sweeps that went all the way
     w.last_sweeps = w.sweeps;
@@ -1691,11 +1498,12 @@ int group_eig_build(hipStream_t st, GroupEig& ge, const std::vector<GEigDesc>& d
                                   ceil_div(e.n, 256) * e.n};
     for (int k = 0; k < kGroupKinds; ++k) off[k * (count + 1) + i + 1] = off[k * (count + 1) + i] + wgs[k];
   }
-  int pmax = 2, nsmall = 0;
+  int pmax = 2, n32 = 0, n64 = 0;
   bool uniform = true;  // every descent has the same padded size
   for (const auto& e : descs) {
     pmax = std::max(pmax, e.N / kNB);
-    nsmall += e.N == kS ? 1 : 0;
+    n32 += e.N == 32 ? 1 : 0;
+    n64 += e.N == 64 ? 1 : 0;
     uniform = uniform && e.N == descs[0].N;
   }
   const size_t tab_bytes = sizeof(GEigDesc) * count, off_bytes = sizeof(int) * off.size();
@@ -1719,7 +1527,8 @@ int group_eig_build(hipStream_t st, GroupEig& ge, const std::vector<GEigDesc>& d
   }
   ge.count = count;
   ge.pmax = pmax;
-  ge.nsmall = nsmall;
+  ge.n32 = n32;
+  ge.n64 = n64;
   {
     const int q = descs[0].N / kNB / 2;
     ge.uq = uniform ? q : 0;
@@ -1732,6 +1541,11 @@ int group_eig_build(hipStream_t st, GroupEig& ge, const std::vector<GEigDesc>& d
                          hipMemcpyHostToDevice, st));
   CMX_HIP(hipStreamSynchronize(st));
   return 0;
+}
+
+hipError_t group_eig_whole(hipStream_t st, const GroupEig& ge, const GroupDueMask& due, int max_sweeps) {
+  return launch_group_whole(st, static_cast<const GEigDesc*>(ge.dtab), ge.count, due, max_sweeps, ge.dflags + 1,
+                            ge.n32 > 0, ge.n64 > 0);
 }
 
 int group_eig_solve(hipStream_t st, GroupEig& ge, const GroupDueMask& due, int max_sweeps, int ahead,
@@ -1751,11 +1565,10 @@ int group_eig_solve(hipStream_t st, GroupEig& ge, const GroupDueMask& due, int m
         if (code_out) code_out[i] = __atomic_load_n(&ge.hflags[1 + kGroupMax + i], __ATOMIC_ACQUIRE);
       }
   };
-  // descents with N = 32 solve whole in one workgroup each, warm start
-  // included, to completion
-  if (ge.nsmall > 0) kg_small_solve<<<count, 256, 0, st>>>(tab, count, due, max_sweeps, hsweeps);
-  if (ge.nsmall == count) {
-    CMX_HIP(hipGetLastError());
+  // small descents solve whole in one workgroup each, warm start included, to
+  // completion
+  CMX_HIP(group_eig_whole(st, ge, due, max_sweeps));
+  if (ge.n32 + ge.n64 == count) {
     CMX_HIP(hipStreamSynchronize(st));
     read_out();
     return 0;
@@ -1769,11 +1582,7 @@ int group_eig_solve(hipStream_t st, GroupEig& ge, const GroupDueMask& due, int m
   // test) are queued before the host first waits; then one batch per wait
   // until no descent sweeps any more.  Rounds of descents that have stopped
   // return at once.
-  // With short sweeps (small n) several are queued per wait, about kWaitRounds
-  // rounds, since a round of stopped descents costs little and a wait much.
-  constexpr int kWaitRounds = 8;
   const int rounds = ge.pmax - 1;
-  const int per_wait = std::max(1, kWaitRounds / rounds);
   int rg = 0;
   auto queue_rounds = [&](int nr) -> int {
     for (int r = 0; r < nr; ++r, ++rg)
@@ -1787,16 +1596,16 @@ int group_eig_solve(hipStream_t st, GroupEig& ge, const GroupDueMask& due, int m
   // at the start of the round after it, so every wait then follows the
   // decision on the last sweep queued before it.
   int queued = 0;
-  for (; queued < std::min(std::max(ahead, per_wait), max_sweeps); ++queued)
+  for (; queued < std::min(std::max(ahead, 1), max_sweeps); ++queued)
     if (int rc = queue_batch()) return rc;
   if (int rc = queue_rounds(1)) return rc;
   for (;;) {
     CMX_HIP(hipStreamSynchronize(st));
     if (__atomic_load_n(&ge.hflags[0], __ATOMIC_ACQUIRE) <= 0) break;
-    if (queued >= max_sweeps + per_wait)
+    if (queued >= max_sweeps + 1)
       return fail(-3, "grouped eigensolve: descents still sweeping past the sweep limit");
-    for (int b = 0; b < per_wait; ++b, ++queued)
-      if (int rc = queue_batch()) return rc;
+    if (int rc = queue_batch()) return rc;
+    ++queued;
   }
   kg_rank<<<wgs_of(2), 256, 0, st>>>(tab, off_of(2), count);
   kg_colsign<<<wgs_of(3), 256, 0, st>>>(tab, off_of(3), count);

@@ -215,10 +215,9 @@ hipError_t launch_dgemm2(hipStream_t st, int M, int N, int K, const double* A0, 
                          int lda1, const double* B, int ldb, double* C0, int ldc0, double* C1, int ldc1);
 
 // eigensolver
-// padded size up to which a descent's eigensolve runs as a grouped solve of
-// one descent: a sweep is one to three rounds there, so several are queued
-// per host wait
-constexpr int kSmallEigenN = 64;
+// padded size up to which a descent's eigensolve, warm start included, runs
+// whole in one workgroup (small.hip): no other launch is queued for it
+constexpr int kWholeSolveN = 64;
 struct EigWork {
   int N = 0;      // padded size (multiple of 32)
   int* gctl = nullptr;   // control block of a grouped solve (GC_WORDS ints, device memory)
@@ -231,13 +230,14 @@ struct EigWork {
   double* X1 = nullptr;  // N*N: angles, then the correction's rotation
   double* X2 = nullptr;  // N*N: products of the correction
   double* X3 = nullptr;  // N*N: products of the refinement
+  double* V2 = nullptr;  // N*N: eigenvectors after an even number of its steps
   double* dsum = nullptr;  // (N/32) * N: the refinement's second-order eigenvalue terms
   double* dv = nullptr;    // N: its first-order eigenvalues
   int* rctl = nullptr;     // its control words (8 ints, device memory)
   double* evals = nullptr;  // N
   int32_t* perm = nullptr;  // N
   double* sign = nullptr;   // N
-  double* part = nullptr;   // 3 * max(n, tiles) partial sums
+  double* part = nullptr;   // 4 * max(n, tiles) partial sums
   double* scale = nullptr;  // max |a_ii|
   int* status = nullptr;  // [0] 1 converged, 2 sweep limit, 3 non-finite; [1] sweeps; [2] corrections
   int* hflags = nullptr;  // pinned host memory: [0] more sweeps needed, [1] non-finite,
@@ -259,16 +259,20 @@ struct EigWork {
   // whether products refine what the sweeps leave: a caller that narrows the
   // closing correction's bound gets sweeps closed by corrections within it
   bool grouped = false;  // the descent's eigensolves run in a group's (sweeps only)
-  bool refines() const { return correct_on && corr_max_theta >= 2e-3 && N > kSmallEigenN && !grouped; }
+  bool refines() const { return correct_on && corr_max_theta >= 2e-3 && N > kWholeSolveN && !grouped; }
   bool pending = false;
   int steps = 0;         // refinement steps queued so far since the last sweep
   int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
-  bool refine_blocked = false;  // a refinement diverged: sweeps only for the rest of this solve
+  int recoveries = 0;    // refinements of this solve that went astray
+  // careful solves (first steps from small angles only) after one whose steps
+  // went astray, twice as many each time until a solve's steps do not
+  int hold = 0, backoff = 2;
   bool refined = false;  // the last solve ended with a refinement (B is orthogonal to rounding)
   // captured steps: [0] sweep from A, [1] from A2, [2] first sweep from A,
   // [3] from A2, [4] correction from A, [5] from A2, [6] first refinement step
-  // from A, [7] from A2, [8 + 2 (S in A2) + parity] a later one
-  hipGraphExec_t gx[12] = {};
+  // from A, [7] from A2, [8 + 2 (S in A2) + parity] a later one, [12] a careful
+  // first one from A, [13] from A2
+  hipGraphExec_t gx[14] = {};
   hipStream_t gstream = nullptr;
 };
 // ---- refinement of a nearly diagonal solve by products (refine.hip)
@@ -276,8 +280,8 @@ struct EigWork {
 // convergence flags, the stop bits and f_best)
 enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, kHostFlagWords = 16 };
 // RS_ACTIVE: applied, more to do; RS_DONE: applied, the last; RS_REJECTED: the
-// first step's angles were too large, nothing was changed; RS_DIVERGED: a
-// later step's were, V is not to be used
+// first step's angles were too large, RS_DIVERGED: a later step's were, or V is
+// too far from orthogonal (neither is applied)
 enum { RS_ACTIVE = 0, RS_DONE = 1, RS_REJECTED = 2, RS_DIVERGED = 3 };
 struct RefineStep {
   int n, N;
@@ -290,10 +294,12 @@ struct RefineStep {
   double *part, *dsum, *dv, *evals;
   const double* scale;
   int *ctl, *flags;
+  double thmax;  // largest ||Theta||_F^2 applied
   int par;     // the step's number mod 2
   bool first;  // S is given and V taken as orthogonal
 };
 hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
+// one Newton-Schulz step on V's orthogonality, Vn = V (3 I - V^T V) / 2 (uses n, N, V, Vn, X and T)
 // the warm start: S = V^T C V, both triangles (uses n, N, C, V, S and T)
 hipError_t launch_refine_start(hipStream_t st, const RefineStep& a, KTimer* kt);
 // Queue the warm start and the first convergence test; the host then
@@ -312,9 +318,6 @@ void eigen_drop_graphs(EigWork& w);
 // ---- grouped eigensolve: the sweeps of many descents in one launch per
 // round, convergence decided per descent on the device (see eigen.hip)
 constexpr int kGroupMax = 1024;  // descents per group
-// padded size whose eigensolve, warm start included, runs whole in one
-// workgroup (n <= 32): no separate warm-start launches are queued for it
-constexpr int kWholeSolveN = 32;
 constexpr int kGroupKinds = 5;   // launch kinds with per-descent workgroups
 // words of a descent's control block (EigWork::gctl); k_offnorm_final of the
 // warm start writes GC_MORE and GC_NONFIN
@@ -348,7 +351,7 @@ struct GroupEig {
   int* dflags = nullptr;  // device address of hflags
   int* dactive = nullptr; // device memory: descents still sweeping (the last to stop zeroes hflags[0])
   int cap = 0, count = 0, pmax = 2;
-  int nsmall = 0;         // descents with N = kWholeSolveN (solved whole by one workgroup each)
+  int n32 = 0, n64 = 0;   // descents with N = 32 and N = 64 (solved whole by one workgroup each)
   int uq = 0, ur = 0;     // all descents of one size: pair-solve and tile / V workgroups each (else 0)
   std::vector<int> off;   // host copy of the offsets (kGroupKinds x (count + 1))
 };
@@ -361,6 +364,11 @@ int group_eig_build(hipStream_t st, GroupEig& ge, const std::vector<GEigDesc>& d
 int group_eig_solve(hipStream_t st, GroupEig& ge, const GroupDueMask& due, int max_sweeps, int ahead,
                     int* sweeps_out, int* code_out);
 void group_eig_release(GroupEig& ge);
+// the due descents with N <= kWholeSolveN, one workgroup each (sweeps and
+// status to the host words that group_eig_solve reads)
+hipError_t group_eig_whole(hipStream_t st, const GroupEig& ge, const GroupDueMask& due, int max_sweeps);
+hipError_t launch_group_whole(hipStream_t st, const GEigDesc* g, int count, const GroupDueMask& due, int max_sweeps,
+                              int* hsweeps, bool any32, bool any64);
 
 // workgroup w of a grouped launch belongs to entry i with off[i] <= w < off[i + 1]
 // (the last entry with off[i] <= w).  First guess: the entry w would fall in

@@ -1,0 +1,78 @@
+// What the eigensolve's parts share: block-Jacobi sweeps (eigen.hip), the
+// refinement by products over the whole GPU (refine.hip) and the whole solve in
+// one workgroup (small.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace cmx {
+
+// Largest ||Theta||_F^2 / n and ||R||_F^2 / n a step is applied at.  Angles that
+// are independent of one another turn by far less than ||Theta||_F together; in
+// a multiple eigenvalue they can all pull the same way, and a step then
+// overshoots.  A solve in which that happened, and a few after it, take their
+// first step from angles up to kThCareful only.
+constexpr double kThLimit = 0.7;
+constexpr double kThCareful = 0.05;
+constexpr double kRLimit = 0.1;
+constexpr double kClip = 0.35;
+// a step is the last one once ||Theta||_F and ||R||_F are below these (what it
+// leaves of each is of the order of ||R||_F times either), or once the angles
+// no longer shrink (||Theta||_F^2 by less than kStall a step) and the off-diagonal
+// norm would end a solve by sweeps, kOffDone of the whole: rounding against
+// rounding inside a close cluster of eigenvalues
+constexpr double kDone = 2e-7;
+constexpr double kDoneR = 1e-7;
+constexpr double kOffDone = 1e-13;
+constexpr double kStall = 0.1;
+// Theta^3 / 6 is left out once ||Theta||_F is below this
+constexpr double kCubeFrom = 1e-3;
+// Entries at or below the sweeps' rotation threshold (eps = 2.2e-16 max d) get
+// no rotation.  Entries at the level of the products' rounding (0.7 sqrt(n) eps
+// each as measured for V far from the identity at n = 1000; counted up to 4
+// sqrt(n) eps) are as small as they can get: they do not count, and turn
+// nothing by more than kNoiseAngle (inside a multiple eigenvalue their angles
+// are arbitrary, and X is orthogonal only while they are small).
+constexpr double kNoiseAngle = 1e-6;
+__device__ __forceinline__ double noise_level(int n, double eps) { return fmax(16.0, 4.0 * sqrt(static_cast<double>(n))) * eps; }
+
+// angle of the rotation of a pair with off-diagonal entry a and eigenvalue
+// difference g; counts: whether it is above the noise
+__device__ __forceinline__ double refine_angle(double a, double g, double eps, double noise, bool& counts) {
+  counts = fabs(a) > noise;
+  if (!(fabs(a) > eps)) return 0.0;
+  const double t = 2.0 * a / (fabs(g) + sqrt(fma(g, g, 4.0 * a * a)));
+  double h = t / fma(0.28, t * t, 1.0);  // atan(t) to 0.005, exact to first order
+  h = g < 0.0 ? -h : h;
+  if (!counts && fabs(h) > kNoiseAngle) h = 0.0;
+  return fmin(fmax(h, -kClip), kClip);
+}
+
+// Jacobi rotation J = [[c, s], [-s, c]] on (a, b) that annihilates (J^T S J)_ab
+// up to the accuracy of t (Golub & Van Loan, sym.schur2): t = sign(delta) 2 d /
+// (|delta| + sqrt(delta^2 + 4 d^2)) with delta = S_bb - S_aa, d = S_ab;
+// c = 1/sqrt(1 + t^2), s = t c; the identity when |d| <= thr.
+// t only decides how far the entry is reduced, so it is formed in float32 from
+// the entries scaled by inv = 1/max|a_ii| (relative error ~1e-7: the entry
+// drops to ~1e-7 of itself and later rotations remove the rest).  c is then
+// refined to float64 precision from that t by two Newton steps, because
+// c^2 (1 + t^2) = 1 is what keeps each rotation, and so Q, orthogonal.
+// Branch free, so the callers' loads issue up front and two rotations
+// interleave.
+__device__ __forceinline__ void jacobi_rotation(double saa, double sbb, double d, double thr, double inv, double& c,
+                                                double& s) {
+  const double dd = fabs(d) > thr ? d : 0.0;
+  const float df = static_cast<float>(dd * inv);
+  const float delta = static_cast<float>((sbb - saa) * inv);
+  const float h = __builtin_amdgcn_sqrtf(fmaf(delta, delta, 4.0f * df * df));
+  // |delta| + h >= 2 |df| > 0 whenever df != 0; the floor only guards 0 / 0
+  const float tf = (delta >= 0.0f ? 2.0f : -2.0f) * df * __builtin_amdgcn_rcpf(fmaxf(fabsf(delta) + h, 1e-30f));
+  const double t = static_cast<double>(tf);
+  const double x = fma(t, t, 1.0);
+  double y = static_cast<double>(__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.0f)));
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  c = y * fma(-0.5 * x * y, y, 1.5);
+  s = t * c;
+}
+
+}  // namespace cmx

@@ -34,22 +34,13 @@
 // waves.  At n = 200: 4.1, 4.3, 5.7, 5.9, 5.2 and 4.1, bound by latency; a sweep
 // of 13 rounds takes 150.
 #include "internal.h"
+#include "refine.h"
 
 namespace cmx {
 
 namespace {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-// largest ||Theta||_F^2 / n and ||R||_F^2 / n a step is applied at
-constexpr double kThLimit = 1.0;
-constexpr double kRLimit = 0.1;
-constexpr double kClip = 0.35;
-// a step is the last one once ||Theta||_F and ||R||_F are below this: what it
-// leaves is of the order of their squares
-constexpr double kDone = 1e-6;
-// Theta^3 / 6 is left out once ||Theta||_F is below this
-constexpr double kCubeFrom = 1e-3;
 
 // ---- products.  A workgroup computes a square tile of MB x MB MFMA blocks
 // (16 x 16); every one of its NW waves computes the whole tile over its own
@@ -257,37 +248,29 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_sg(const double* __restr
   if (MIRROR && tm != tn) TL::store_mirror(lds, v, out, N, m0, n0);
 }
 
-// sums of two values over the workgroup, in a fixed order
+// sums of four values over the workgroup, in a fixed order
 template <int NW>
-__device__ __forceinline__ void block_sum2(double& a, double& b, double (*red)[NW]) {
+__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[4]) {
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    a += __shfl_xor(a, m);
-    b += __shfl_xor(b, m);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = a;
-    red[1][threadIdx.x >> 6] = b;
-  }
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v[q] += __shfl_xor(v[q], m);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[threadIdx.x >> 6][q] = v[q];
   __syncthreads();
-  a = red[0][0];
-  b = red[1][0];
 #pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    a += red[0][w];
-    b += red[1][w];
+  for (int q = 0; q < 4; ++q) {
+    v[q] = red[0][q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v[q] += red[w][q];
   }
 }
 
 // Theta from the lower tiles of S and G (null: R = 0), 32 x 32 tiles; both
-// triangles of Theta, its squared norm and R's per tile (tiles of padding are
-// zero), the first-order eigenvalues d, and per tile and row the sum over the
+// triangles of Theta; per tile the squared norms of Theta, R, s and d (tiles
+// of padding are zero); the first-order eigenvalues d, and per tile and row the sum over the
 // tile's columns of theta_ji s_ij, which is what rotating by Theta adds to d_i.
-// Entries at or below the sweeps' rotation threshold get no rotation.  Entries
-// at the level of the products' rounding (kNoise) are as small as they can
-// get: they do not count, and turn nothing by more than kNoiseAngle (inside
-// a multiple eigenvalue their angles are arbitrary).
-constexpr double kNoise = 8.0, kNoiseAngle = 1e-4;
 constexpr int kCT = 32;
 __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S, const double* __restrict__ G, int N,
                                                    int n, const double* __restrict__ scale, double* __restrict__ Th,
@@ -295,7 +278,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
                                                    double* __restrict__ dv, const int* __restrict__ word) {
   __shared__ double tl[kCT][kCT + 1], ts[kCT][kCT + 1];
   __shared__ double dr[kCT], dc[kCT];
-  __shared__ double red[2][4];
+  __shared__ double red[4][4];
   if (word && *word != 0) return;
   int bi, bj;
   lower_tile(blockIdx.x, bi, bj);
@@ -317,8 +300,8 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
     if (bi == bj && t < kCT && i < n) dv[i] = v;
   }
   __syncthreads();
-  const double eps = 2.2e-16 * scale[0];
-  double th2 = 0.0, r2 = 0.0;
+  const double eps = 2.2e-16 * scale[0], noise = noise_level(n, eps);
+  double th2 = 0.0, r2 = 0.0, off2 = 0.0, tot2 = 0.0;
 #pragma unroll
   for (int q = 0; q < kCT / 8; ++q) {
     const int k = ty + 8 * q, r = r0 + tx, c = c0 + k;
@@ -327,30 +310,24 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
       const double rij = -gv[q];
       const double a = sv[q] + 0.5 * rij * (dr[tx] + dc[k]);
       const double g = dr[tx] - dc[k];  // d_r - d_c: the rotation of the pair (c, r), c < r
-      if (fabs(a) > eps) {
-        const double tn = 2.0 * a / (fabs(g) + sqrt(fma(g, g, 4.0 * a * a)));
-        double h = tn / fma(0.28, tn * tn, 1.0);  // atan(tn) to 0.005, exact to first order
-        h = g < 0.0 ? -h : h;
-        const bool noise = fabs(a) <= kNoise * eps;
-        if (noise && fabs(h) > kNoiseAngle) h = 0.0;
-        h = fmin(fmax(h, -kClip), kClip);
-        th = -h;  // Theta(r, c) = -Theta(c, r)
-        w = h * a;  // theta_cr s: added to d_r, taken from d_c
-        if (!noise) th2 = fma(2.0 * h, h, th2);
-      }
+      bool counts;
+      const double h = refine_angle(a, g, eps, noise, counts);
+      th = -h;  // Theta(r, c) = -Theta(c, r)
+      w = h * a;  // theta_cr s: added to d_r, taken from d_c
+      if (counts) th2 = fma(2.0 * h, h, th2);
       r2 = fma(2.0 * rij, rij, r2) + (a - a);  // (a - a): NaN when a is not finite
-    } else if (r < n && r == c && G) {
-      const double rii = 1.0 - gv[q];
+      off2 = fma(2.0 * a, a, off2);
+    } else if (r < n && r == c) {
+      const double rii = G ? 1.0 - gv[q] : 0.0;
       r2 = fma(rii, rii, r2);
+      tot2 = fma(dr[tx], dr[tx], tot2);
     }
     tl[tx][k] = th;
     ts[tx][k] = w;
   }
-  block_sum2<4>(th2, r2, red);  // (its barrier also covers tl and ts)
-  if (t == 0) {
-    part[2 * blockIdx.x] = th2;
-    part[2 * blockIdx.x + 1] = r2;
-  }
+  double sums[4] = {th2, r2, off2, tot2};
+  block_sum4<4>(sums, red);  // (its barrier also covers tl and ts)
+  if (t < 4) part[4 * blockIdx.x + t] = t == 0 ? sums[0] : t == 1 ? sums[1] : t == 2 ? sums[2] : sums[3];
 #pragma unroll
   for (int q = 0; q < kCT / 8; ++q) {
     const int k = ty + 8 * q;
@@ -381,16 +358,16 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
 // ---- control words of a solve's refinement.  Step j reads state[j & 1]
 // (0: run) and writes state[(j + 1) & 1] and bits[j & 1], so no workgroup
 // reads a word that its own launch writes.
-enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5 };
+enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5, RC_TH2 = 6 };
 enum { RB_APPLY = 1, RB_CUBE = 2 };
 
 // X of one lower tile and of its mirror, in place of G (X and G share a
-// buffer; useg false: R = 0): lower(r, c) and its transpose from the symmetric
-// and antisymmetric parts.  sq(e, at): Theta^2 of element e, cube(r, c): Theta^3.
+// buffer; useg false: R = 0; plain: Theta = 0): lower(r, c) and its transpose
+// from the symmetric and antisymmetric parts.  sq(e, at): Theta^2 of element e, cube(r, c): Theta^3.
 // The workgroups of the diagonal tiles also sum up the eigenvalues.
 template <class TL, class Square, class Cube>
 __device__ __forceinline__ void make_x(double* lds, const double* __restrict__ Th, int N, int n, int tm, int tn,
-                                       bool useg, double* __restrict__ X, const double* __restrict__ dsum,
+                                       bool useg, bool plain, double* __restrict__ X, const double* __restrict__ dsum,
                                        const double* __restrict__ dv, double* __restrict__ evals, Square sq,
                                        Cube cube) {
   const int m0 = tm * TL::T, n0 = tn * TL::T;
@@ -405,8 +382,8 @@ __device__ __forceinline__ void make_x(double* lds, const double* __restrict__ T
     double lower = 0.0;
     if (gr < n && gc < n) {
       const double id = gr == gc ? 1.0 : 0.0;
-      double sym = id + 0.5 * sq(e, at);
-      const double anti = Th[at] + cube(r, c) * (1.0 / 6.0);
+      double sym = id + (plain ? 0.0 : 0.5 * sq(e, at));
+      const double anti = plain ? 0.0 : Th[at] + cube(r, c) * (1.0 / 6.0);
       if (useg) sym += 0.5 * (id - X[at]);
       lower = sym + anti;
       v[e] = sym - anti;
@@ -419,8 +396,9 @@ __device__ __forceinline__ void make_x(double* lds, const double* __restrict__ T
     const int i = m0 + threadIdx.x;
     if (i < n) {
       double s = dv[i];
+      const int terms = plain ? 0 : N / kCT;
 #pragma unroll 8
-      for (int k = 0; k < N / kCT; ++k) s += dsum[static_cast<int64_t>(k) * N + i];
+      for (int k = 0; k < terms; ++k) s += dsum[static_cast<int64_t>(k) * N + i];
       evals[i] = s;
     }
   }
@@ -433,20 +411,20 @@ template <class TL>
 __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __restrict__ Th, int N, int n,
                                                                double* __restrict__ S2,
                                                                const double* __restrict__ part, int count, int first,
-                                                               int par, int* __restrict__ ctl,
+                                                               double thmax, int par, int* __restrict__ ctl,
                                                                int* __restrict__ flags, double* __restrict__ X,
                                                                const double* __restrict__ dsum,
                                                                const double* __restrict__ dv,
                                                                double* __restrict__ evals) {
   __shared__ double lds[TL::LDS];
-  __shared__ double red[2][TL::NW];
+  __shared__ double red[TL::NW][4];
   const int before = first ? 0 : ctl[RC_STATE + par];
+  const float th2_before = first ? 0.0f : __int_as_float(ctl[RC_TH2 + par]);
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-  double th2 = 0.0, r2 = 0.0;
-  for (int i = threadIdx.x; i < count; i += TL::THREADS) {
-    th2 += part[2 * i];
-    r2 += part[2 * i + 1];
-  }
+  double sums[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < count; i += TL::THREADS)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sums[q] += part[4 * i + q];
   int tm, tn;
   lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
   const int m0 = tm * TL::T, n0 = tn * TL::T;
@@ -458,10 +436,14 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     }
     return;
   }
-  block_sum2<TL::NW>(th2, r2, red);
-  const bool apply = isfinite(th2) && isfinite(r2) && th2 <= kThLimit * n && r2 <= kRLimit * n;
-  const bool last = th2 <= kDone * kDone && r2 <= kDone * kDone;
-  const int bits = !apply ? 0 : RB_APPLY | (th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
+  block_sum4<TL::NW>(sums, red);
+  const double th2 = sums[0], r2 = sums[1];
+  const bool small_th = th2 <= kDone * kDone;
+  // rounding is left as it is, whatever its angles are: the step only takes out R
+  const bool plain = !small_th && !first && th2 > kStall * th2_before && sums[2] <= kOffDone * kOffDone * sums[3];
+  const bool last = (small_th || plain) && r2 <= kDoneR * kDoneR;
+  const bool apply = isfinite(th2) && isfinite(r2) && (plain || th2 <= thmax) && r2 <= kRLimit * n;
+  const int bits = !apply ? 0 : RB_APPLY | (!plain && th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
   if (lead) {
     const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : (last ? RS_DONE : RS_ACTIVE);
     const int applied = (first ? 0 : ctl[RC_APPLIED]) + (apply ? 1 : 0);
@@ -469,6 +451,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     ctl[RC_STATE + (par ^ 1)] = state;
     ctl[RC_BITS + par] = bits;
     ctl[RC_APPLIED] = applied;
+    ctl[RC_TH2 + (par ^ 1)] = __float_as_int(static_cast<float>(th2));
     ctl[RC_SMALL] = small;
     __hip_atomic_store(&flags[RF_STATE], state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_APPLIED], applied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -482,7 +465,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     v[e] = -TL::get(lds, r, c);
   }
   if (!(bits & RB_CUBE)) {
-    make_x<TL>(lds, Th, N, n, tm, tn, first == 0, X, dsum, dv, evals, [&](int e, int64_t) { return v[e]; },
+    make_x<TL>(lds, Th, N, n, tm, tn, first == 0, plain, X, dsum, dv, evals, [&](int e, int64_t) { return v[e]; },
                [](int, int) { return 0.0; });
     return;
   }
@@ -508,7 +491,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_cube(const double* __res
   lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
   // Theta^T Theta^2 = -Theta^3
   if (!TL::template product<true, false>(lds, Th, N, S2, N, (n + 15) / 16, tm * TL::T, tn * TL::T, N, N, N, go)) return;
-  make_x<TL>(lds, Th, N, n, tm, tn, useg != 0, X, dsum, dv, evals, [&](int, int64_t at) { return S2[at]; },
+  make_x<TL>(lds, Th, N, n, tm, tn, useg != 0, false, X, dsum, dv, evals, [&](int, int64_t at) { return S2[at]; },
              [&](int r, int c) { return -TL::get(lds, r, c); });
 }
 
@@ -534,7 +517,7 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
   }
   k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.dv,
                                      a.first ? nullptr : state);
-  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.par, a.ctl,
+  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.thmax, a.par, a.ctl,
                                                 a.flags, a.X, a.dsum, a.dv, a.evals);
   k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, false, false>, full, TL::THREADS, st, a.V, N, a.X, N, a.n, a.Vn, N, N,

@@ -82,3 +82,16 @@ def test_refinement_removes_the_drift_of_an_inexact_basis(P):
     st = synth.random_state(n, lam, seed=5, cond=100.0)
     st["B"] = st["B"] + 1e-8 * synth.rng(9).standard_normal((n, n))
     check_decomposition(decompose(P, st, lam))
+
+
+@pytest.mark.parametrize("n,lam", [(100, 17), (400, 24)])
+def test_refinement_from_the_identity(P, n, lam):
+    """The first generations of a search, C = I plus ever more outer products:
+    steps are refused, go astray and are recovered from, and wait their turn."""
+    print(f"case refine from the identity n={n}", flush=True)
+    R, xstar = synth.problem(n, 1)
+    with P.CMAES(n, lam, 2.0, seed=5, precision="mixed", objective="rastrigin", R=R, xstar=xstar, f_target=0.0,
+                 eigen_interval=1) as es:
+        for _ in range(14):
+            es.generation()
+            check_decomposition(es.state())
