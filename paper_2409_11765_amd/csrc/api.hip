@@ -293,6 +293,7 @@ void free_all(cmaes* h) {
   dev_free(h, h->ew.X3);
   dev_free(h, h->ew.V2);
   dev_free(h, h->ew.dsum);
+  dev_free(h, h->ew.rsum);
   dev_free(h, h->ew.dv);
   dev_free(h, h->ew.rctl);
   dev_free(h, h->ew.Q2);
@@ -428,6 +429,7 @@ int alloc_fixed(cmaes* h) {
   const size_t nn = static_cast<size_t>(ldn) * n;
   const int N = round_up(n, 32);
   h->ew.N = N;
+  h->ew.narrow = h->opt.precision != CMAES_FP64;
   int rc = 0;
   if ((rc = dev_alloc(h, &h->sc, sizeof(DevScalars))) || (rc = dev_alloc(h, &h->m, 8ull * ldn)) ||
       (rc = dev_alloc(h, &h->ps, 8ull * ldn)) || (rc = dev_alloc(h, &h->pc, 8ull * ldn)) ||
@@ -444,7 +446,8 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.X1, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.X2, 8ull * N * N)) ||
       (rc = dev_alloc(h, &h->ew.X3, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.V2, 8ull * N * N)) ||
       (rc = dev_alloc(h, &h->ew.dsum, 8ull * (N / 32) * N)) ||
-      (rc = dev_alloc(h, &h->ew.dv, 8ull * N)) || (rc = dev_alloc(h, &h->ew.rctl, 4ull * 8)) ||
+      (rc = dev_alloc(h, &h->ew.rsum, 8ull * (N / 32) * N)) ||
+      (rc = dev_alloc(h, &h->ew.dv, 8ull * N)) || (rc = dev_alloc(h, &h->ew.rctl, 4ull * 16)) ||
       (rc = dev_alloc(h, &h->ew.evals, 8ull * N)) || (rc = dev_alloc(h, &h->ew.perm, 4ull * N)) ||
       (rc = dev_alloc(h, &h->ew.sign, 8ull * N)) || (rc = dev_alloc(h, &h->ew.scale, 16)) ||
       (rc = dev_alloc(h, &h->ew.status, 16)) || (rc = dev_alloc(h, &h->ew.gctl, 4ull * GC_WORDS)))
@@ -538,8 +541,7 @@ int init_descent(cmaes* h, bool fresh) {
   h->ew.last_sweeps = 0;
   h->ew.last_closed = false;
   h->ew.last_steps = 0;
-  h->ew.hold = 0;
-  h->ew.backoff = 2;
+  h->ew.last_long = kManySteps;
   refresh_stop_params(h);
   return 0;
 }
@@ -821,6 +823,7 @@ int finish_generation(cmaes* h) {
     h->ew.corrections = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
+    h->ew.last_long = kManySteps;
     h->ew.refined = true;
     h->ew.pending = false;
   }
@@ -1370,8 +1373,7 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     h->ew.last_sweeps = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
-    h->ew.hold = 0;
-    h->ew.backoff = 2;
+    h->ew.last_long = kManySteps;
   }
   if (in->B || in->D)  // B D in the sampling precision
     CMX_HIP(launch_scale_columns(h->st, h->fp64, n, h->B, h->ldn, h->D, h->BD, h->ldn));
@@ -1985,6 +1987,7 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
         h->ew.last_sweeps = g.sweeps[i];
         h->ew.last_closed = false;
         h->ew.last_steps = 0;
+        h->ew.last_long = kManySteps;
         h->ew.refined = h->ew.N <= kWholeSolveN;
         h->ew.pending = false;
       }

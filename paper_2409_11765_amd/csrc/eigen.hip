@@ -56,8 +56,7 @@ constexpr double kOffTol = 1e-13;
 // the angles satisfy ||Theta||_F <= EigWork::corr_max_theta (at most 2e-3)
 constexpr double kCorrOff = 1e-8;
 constexpr int kMaxCorrections = 4;  // per solve
-constexpr int kMaxSteps = 24;  // refinement steps before more sweeps
-constexpr int kMaxBackoff = 32;
+constexpr int kMaxSteps = 64;  // refinement steps before more sweeps
 constexpr int kMaxRecoveries = 3;  // per solve, before it is done by sweeps alone
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -1293,6 +1292,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.T = w.X3;
       a.part = w.part;
       a.dsum = w.dsum;
+      a.rsum = w.rsum;
       a.dv = w.dv;
       a.evals = w.evals;
       a.scale = w.scale;
@@ -1300,10 +1300,13 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.flags = w.dflags;
       a.par = par;
       a.first = w.steps == 0;
-      const bool careful = a.first && (w.recoveries > 0 || w.hold > 0);
-      a.thmax = (careful ? kThCareful : kThLimit) * n;
+      const bool careful = a.first && w.recoveries > 0;
+      a.thmax = (careful ? kThCareful : kThLimit) * n;  // of a first step
       const int in2 = w.Acur == w.A ? 0 : 1;
-      const int slot = !a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2;
+      // as many steps as had long rows in the previous solve look for them; beyond
+      // that while the last step known had some (3-4 us saved in each other one)
+      a.damp = !careful && (w.steps < w.last_long || (w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED]));
+      const int slot = (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) + (a.damp || careful ? 0 : 8);
       if (const int rc = run(slot, [&] { return launch_refine_step(st, a, kt); })) return rc;
     }
     return 0;
@@ -1332,6 +1335,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
   // kMaxRecoveries the solve starts over without any.
   auto recover = [&]() -> int {
     const int count = ++w.recoveries;
+    if (count == 1) w.lead = w.sweeps;
     if (count > kMaxRecoveries) {
       const int rc = eigen_begin(st, n, C, ldc, B, ldb, w, kt);
       w.recoveries = count;
@@ -1371,18 +1375,11 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       const int state = w.hflags[RF_STATE], applied = w.hflags[RF_APPLIED];
       if (state == RS_DONE) {
         const int small = std::min(w.hflags[RF_SMALL], kMaxCorrections);
-        w.last_sweeps = w.sweeps;
+        w.last_sweeps = w.recoveries > 0 ? w.lead : w.sweeps;
         w.last_steps = applied;
+        w.last_long = w.recoveries > 0 ? kManySteps : w.hflags[RF_LONG];
         w.last_closed = false;
         w.refined = true;
-        if (w.recoveries > 0) {
-          w.hold = w.backoff;
-          w.backoff = std::min(2 * w.backoff, kMaxBackoff);
-        } else if (w.hold > 0) {
-          --w.hold;
-        } else {
-          w.backoff = 2;
-        }
         return finish(refined(applied), w.evals, 1, 1, w.sweeps + applied - small, small);
       }
       if (state == RS_ACTIVE && applied < kMaxSteps)

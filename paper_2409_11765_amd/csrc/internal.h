@@ -218,6 +218,15 @@ hipError_t launch_dgemm2(hipStream_t st, int M, int N, int K, const double* A0, 
 // padded size up to which a descent's eigensolve, warm start included, runs
 // whole in one workgroup (small.hip): no other launch is queued for it
 constexpr int kWholeSolveN = 64;
+constexpr int kManySteps = 1 << 20;
+// padded size up to which a float32 descent beyond that ends its sweeps with
+// the closing correction: refined eigenvectors are more accurate (3e-14 against
+// 3e-13 at n = 134), so the last bit of some float32 elements of B D differs, and a
+// seed leaves the trajectory that it had by 1e-8 (one seed in eight at n = 100,
+// lambda = 272, none of 40 at n = 200, lambda = 1216, where the spectrum is tighter).
+// Up to here that costs 460 against 290 us a generation (n = 100, lambda = 272); at
+// n = 200 it would cost 730 against 370.
+constexpr int kNarrowSweepN = 128;
 struct EigWork {
   int N = 0;      // padded size (multiple of 32)
   int* gctl = nullptr;   // control block of a grouped solve (GC_WORDS ints, device memory)
@@ -232,8 +241,9 @@ struct EigWork {
   double* X3 = nullptr;  // N*N: products of the refinement
   double* V2 = nullptr;  // N*N: eigenvectors after an even number of its steps
   double* dsum = nullptr;  // (N/32) * N: the refinement's second-order eigenvalue terms
+  double* rsum = nullptr;  // (N/32) * N: squared row lengths of its angles
   double* dv = nullptr;    // N: its first-order eigenvalues
-  int* rctl = nullptr;     // its control words (8 ints, device memory)
+  int* rctl = nullptr;     // its control words (16 ints, device memory)
   double* evals = nullptr;  // N
   int32_t* perm = nullptr;  // N
   double* sign = nullptr;   // N
@@ -243,7 +253,7 @@ struct EigWork {
   int* hflags = nullptr;  // pinned host memory: [0] more sweeps needed, [1] non-finite,
                   // [2] off(A) small enough for a closing correction, [3] the last
                   // correction was rejected (its rotation was not small),
-                  // [RF_STATE .. RF_SMALL] the refinement's outcome
+                  // [RF_STATE .. RF_LONG] the refinement's outcome
   int* dflags = nullptr;  // device address of hflags (written by the convergence test)
   // progress of the eigensolve in flight
   double *Acur = nullptr, *Anext = nullptr, *Qcur = nullptr, *Qnext = nullptr;
@@ -259,26 +269,28 @@ struct EigWork {
   // whether products refine what the sweeps leave: a caller that narrows the
   // closing correction's bound gets sweeps closed by corrections within it
   bool grouped = false;  // the descent's eigensolves run in a group's (sweeps only)
-  bool refines() const { return correct_on && corr_max_theta >= 2e-3 && N > kWholeSolveN && !grouped; }
+  bool narrow = false;   // B D is kept in float32
+  bool refines() const {
+    return correct_on && corr_max_theta >= 2e-3 && N > (narrow ? kNarrowSweepN : kWholeSolveN) && !grouped;
+  }
   bool pending = false;
   int steps = 0;         // refinement steps queued so far since the last sweep
   int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
+  int last_long = kManySteps;  // how many of them had long rows (kManySteps: unknown)
   int recoveries = 0;    // refinements of this solve that went astray
-  // careful solves (first steps from small angles only) after one whose steps
-  // went astray, twice as many each time until a solve's steps do not
-  int hold = 0, backoff = 2;
+  int lead = 0;          // sweeps before the first of them
   bool refined = false;  // the last solve ended with a refinement (B is orthogonal to rounding)
   // captured steps: [0] sweep from A, [1] from A2, [2] first sweep from A,
   // [3] from A2, [4] correction from A, [5] from A2, [6] first refinement step
   // from A, [7] from A2, [8 + 2 (S in A2) + parity] a later one, [12] a careful
-  // first one from A, [13] from A2
-  hipGraphExec_t gx[14] = {};
+  // first one from A, [13] from A2, [14 ..] those of [6 .. 11] that leave long rows
+  hipGraphExec_t gx[20] = {};
   hipStream_t gstream = nullptr;
 };
 // ---- refinement of a nearly diagonal solve by products (refine.hip)
 // outcome of the last step that ran (host flags; the words follow the
 // convergence flags, the stop bits and f_best)
-enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, kHostFlagWords = 16 };
+enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, RF_LONG = 11, kHostFlagWords = 16 };
 // RS_ACTIVE: applied, more to do; RS_DONE: applied, the last; RS_REJECTED: the
 // first step's angles were too large, RS_DIVERGED: a later step's were, or V is
 // too far from orthogonal (neither is applied)
@@ -291,12 +303,13 @@ struct RefineStep {
   double* Vn;       // the step's result
   double* S;        // V^T C V: given to the first step, made by the others
   double *Th, *X, *T;  // N*N scratch
-  double *part, *dsum, *dv, *evals;
+  double *part, *dsum, *rsum, *dv, *evals;
   const double* scale;
   int *ctl, *flags;
-  double thmax;  // largest ||Theta||_F^2 applied
+  double thmax;  // largest ||Theta||_F^2 of a first step
   int par;     // the step's number mod 2
   bool first;  // S is given and V taken as orthogonal
+  bool damp;   // shorten long rows of Theta
 };
 hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
 // one Newton-Schulz step on V's orthogonality, Vn = V (3 I - V^T V) / 2 (uses n, N, V, Vn, X and T)

@@ -7,14 +7,26 @@
 
 namespace cmx {
 
-// Largest ||Theta||_F^2 / n and ||R||_F^2 / n a step is applied at.  Angles that
-// are independent of one another turn by far less than ||Theta||_F together; in
-// a multiple eigenvalue they can all pull the same way, and a step then
-// overshoots.  A solve in which that happened, and a few after it, take their
-// first step from angles up to kThCareful only.
-constexpr double kThLimit = 0.7;
+// Largest ||Theta||_F^2 / n of a solve's first step (the sweep that comes first
+// beyond it lowers a large one faster than the three to four steps of its time do;
+// below it the steps are faster), and of the first step after steps that went
+// astray; largest ||R||_F^2 / n of any step.
+constexpr double kThLimit = 4.0;
 constexpr double kThCareful = 0.05;
-constexpr double kRLimit = 0.1;
+constexpr double kRLimit = 0.01;
+// Longest row of Theta; the entries of longer ones are scaled down.  The angles
+// of a row are right one by one, but in a cluster of eigenvalues they act on the
+// same few dimensions and together overshoot.  The shorter the rows, the more
+// clusters converge, and the slower all else does, so the length follows how
+// much ||Theta||_F^2 fell in the step before (before = 0: the first step).
+// Without it steps went astray from ||Theta||_F^2 = 0.7 n on and left 6-14 sweeps to
+// the first generations of a search.
+__device__ __forceinline__ double longest_row(double th2, double before, int n) {
+  if (before == 0.0) return th2 > 2.0 * n ? 0.5 : 0.75;
+  return th2 > 0.9 * before ? 0.4 : th2 > 0.8 * before ? 0.55 : 0.75;
+}
+// ||Theta||_F^2 / n beyond which some row may be longer than that
+constexpr double kLong = 0.05;
 constexpr double kClip = 0.35;
 // a step is the last one once ||Theta||_F and ||R||_F are below these (what it
 // leaves of each is of the order of ||R||_F times either), or once the angles

@@ -14,8 +14,9 @@
 // the off-diagonal part and the orthogonality, and since every step starts
 // again from C, neither the rounding of the steps before it nor a drift of B
 // from one solve to the next stays in the result.  The second and third order
-// terms, Jacobi's angle in place of the quotient and the clip let it start
-// from angles that are not small (||Theta||_F^2 up to kThLimit n).
+// terms, Jacobi's angle in place of the quotient, the clip and a bound on the
+// length of Theta's rows let it start from angles that are not small
+// (||Theta||_F^2 up to kThLimit n).
 //
 // A step takes five float64 products (two of them, and the two powers of
 // Theta, of lower tiles only); a block-Jacobi sweep reduces off(A) about as
@@ -275,7 +276,8 @@ constexpr int kCT = 32;
 __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S, const double* __restrict__ G, int N,
                                                    int n, const double* __restrict__ scale, double* __restrict__ Th,
                                                    double* __restrict__ part, double* __restrict__ dsum,
-                                                   double* __restrict__ dv, const int* __restrict__ word) {
+                                                   double* __restrict__ rsum, double* __restrict__ dv,
+                                                   const int* __restrict__ word) {
   __shared__ double tl[kCT][kCT + 1], ts[kCT][kCT + 1];
   __shared__ double dr[kCT], dc[kCT];
   __shared__ double red[4][4];
@@ -338,28 +340,73 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
       Th[static_cast<int64_t>(c0 + k) * N + r0 + tx] = tx >= k ? tl[tx][k] : -tl[k][tx];
     }
   }
-  // rows: + sum over the tile's columns; columns: - sum over its rows
-  if (t < kCT) {
-    double s = 0.0;
+  // rows: + sum over the tile's columns; columns: - sum over its rows (the
+  // first wave; the second the same for theta^2, which has no sign)
+  if (t < 128) {
+    const int i = t & 31;
+    const bool sq = t >= 64, cols = (t & 32) != 0;
+    if (cols && bi == bj) return;
+    double (*m)[kCT + 1] = sq ? tl : ts;
+    double s = 0.0, o = 0.0;
 #pragma unroll
-    for (int k = 0; k < kCT; ++k) s += ts[t][k];
+    for (int k = 0; k < kCT; ++k) {
+      const double v = cols ? m[k][i] : m[i][k];
+      s += sq ? v * v : v;
+    }
     if (bi == bj)
 #pragma unroll
-      for (int k = 0; k < kCT; ++k) s -= ts[k][t];
-    dsum[static_cast<int64_t>(bj) * N + r0 + t] = s;
-  } else if (bi != bj && t < 2 * kCT) {
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < kCT; ++k) s -= ts[k][t - kCT];
-    dsum[static_cast<int64_t>(bi) * N + c0 + t - kCT] = s;
+      for (int k = 0; k < kCT; ++k) o += sq ? m[k][i] * m[k][i] : m[k][i];
+    const double sum = sq ? s + o : (cols ? -s : s - o);
+    (sq ? rsum : dsum)[static_cast<int64_t>(cols ? bi : bj) * N + (cols ? c0 : r0) + i] = sum;
   }
 }
 
 // ---- control words of a solve's refinement.  Step j reads state[j & 1]
 // (0: run) and writes state[(j + 1) & 1] and bits[j & 1], so no workgroup
 // reads a word that its own launch writes.
-enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5, RC_TH2 = 6 };
+enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5, RC_TH2 = 6, RC_LONG = 8 };
 enum { RB_APPLY = 1, RB_CUBE = 2 };
+
+// Theta damped where a row of it is long: theta_ij times min(1, c / |row i|,
+// c / |row j|), c = longest_row, 32 x 32 tiles as in k_ref_theta.  A tile whose
+// rows and columns are all short, which is every tile in the last steps, is left
+// alone.
+__global__ void __launch_bounds__(256) k_ref_damp(double* __restrict__ Th, int N, int n,
+                                                  const double* __restrict__ part, const double* __restrict__ rsum,
+                                                  const int* __restrict__ ctl, int par, int first) {
+  __shared__ double f[2 * kCT];
+  __shared__ double red[4];
+  if (!first && ctl[RC_STATE + par] != 0) return;
+  const float before = first ? 0.0f : __int_as_float(ctl[RC_TH2 + par]);
+  double th2 = 0.0;
+  for (int i = threadIdx.x; i < gridDim.x; i += 256) th2 += part[4 * i];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) th2 += __shfl_xor(th2, m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = th2;
+  __syncthreads();
+  th2 = red[0] + red[1] + red[2] + red[3];
+  const double row = longest_row(th2, before, n);
+  int bi, bj;
+  lower_tile(blockIdx.x, bi, bj);
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
+  const int r0 = bi * kCT, c0 = bj * kCT;
+  bool damp = false;
+  if (t < 2 * kCT) {
+    const int i = (t < kCT ? r0 : c0) + tx;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < N / kCT; ++k) s += rsum[static_cast<int64_t>(k) * N + i];
+    damp = s > row * row;
+    f[t] = damp ? row / sqrt(s) : 1.0;
+  }
+  if (!__syncthreads_or(damp)) return;
+#pragma unroll
+  for (int q = 0; q < kCT / 8; ++q) {
+    const int k = ty + 8 * q;
+    Th[static_cast<int64_t>(c0 + k) * N + r0 + tx] *= fmin(f[tx], f[kCT + k]);
+    if (bi != bj) Th[static_cast<int64_t>(r0 + k) * N + c0 + tx] *= fmin(f[kCT + tx], f[k]);
+  }
+}
 
 // X of one lower tile and of its mirror, in place of G (X and G share a
 // buffer; useg false: R = 0; plain: Theta = 0): lower(r, c) and its transpose
@@ -442,7 +489,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
   // rounding is left as it is, whatever its angles are: the step only takes out R
   const bool plain = !small_th && !first && th2 > kStall * th2_before && sums[2] <= kOffDone * kOffDone * sums[3];
   const bool last = (small_th || plain) && r2 <= kDoneR * kDoneR;
-  const bool apply = isfinite(th2) && isfinite(r2) && (plain || th2 <= thmax) && r2 <= kRLimit * n;
+  const bool apply = isfinite(th2) && isfinite(r2) && (!first || th2 <= thmax) && r2 <= kRLimit * n;
   const int bits = !apply ? 0 : RB_APPLY | (!plain && th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
   if (lead) {
     const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : (last ? RS_DONE : RS_ACTIVE);
@@ -455,6 +502,9 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     ctl[RC_SMALL] = small;
     __hip_atomic_store(&flags[RF_STATE], state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_APPLIED], applied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const int longs = th2 > kLong * n ? applied : first ? 0 : ctl[RC_LONG];
+    ctl[RC_LONG] = longs;
+    __hip_atomic_store(&flags[RF_LONG], longs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_SMALL], small, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   if (!apply) return;
@@ -515,8 +565,9 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
                  a.n, a.ldc, state, ~0, 0);  // C V (C is symmetric)
     k_ref_sg<TL, false><<<2 * low, TL::THREADS, 0, st>>>(a.V, a.T, N, a.n, low, a.S, a.X, state);
   }
-  k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.dv,
+  k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.rsum, a.dv,
                                      a.first ? nullptr : state);
+  if (a.damp) k_ref_damp<<<tiles, 256, 0, st>>>(a.Th, N, a.n, a.part, a.rsum, a.ctl, a.par, a.first ? 1 : 0);
   k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.thmax, a.par, a.ctl,
                                                 a.flags, a.X, a.dsum, a.dv, a.evals);
   k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);

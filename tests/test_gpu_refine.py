@@ -90,8 +90,20 @@ def test_refinement_from_the_identity(P, n, lam):
     steps are refused, go astray and are recovered from, and wait their turn."""
     print(f"case refine from the identity n={n}", flush=True)
     R, xstar = synth.problem(n, 1)
-    with P.CMAES(n, lam, 2.0, seed=5, precision="mixed", objective="rastrigin", R=R, xstar=xstar, f_target=0.0,
+    with P.CMAES(n, lam, 2.0, seed=5, precision="fp64", objective="rastrigin", R=R, xstar=xstar, f_target=0.0,
                  eigen_interval=1) as es:
         for _ in range(14):
             es.generation()
             check_decomposition(es.state())
+
+
+@pytest.mark.parametrize("n", [65, 96, 130, 383, 385, 641])
+def test_refinement_damps_long_rows(P, n):
+    """B turned away from C's eigenvectors by angles whose rows are longer than a
+    step takes: their tiles are scaled, in both triangles, before they are applied."""
+    print(f"case refine with long rows n={n}", flush=True)
+    st = synth.random_state(n, 2 * n, seed=n, cond=30.0)
+    K = synth.rng(n + 1).standard_normal((n, n))
+    q, r = np.linalg.qr(np.eye(n) + 0.5 * (K - K.T) / np.sqrt(n))
+    st["B"] = st["B"] @ (q * np.sign(np.diag(r)))
+    check_decomposition(decompose(P, st, 2 * n))
