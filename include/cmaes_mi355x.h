@@ -301,13 +301,13 @@ int cmaes_phase_times(const cmaes_t* h, double* out);
  * or on the legacy null stream. */
 int cmaes_enable_graphs(cmaes_t* h, int on);
 /* How an eigensolve (C = B D^2 B^T, Sec. 2.1) ends.  Block-Jacobi sweeps run
- * while the angles that remain are large; once they are not (n > 64, n > 128
+ * while the angles that remain are large; once they are not (n > 64, n > 192
  * in the mixed precisions), steps that rotate every index pair at once by
  * float64 products finish the solve, each taking the off-diagonal part and
  * B's distance from orthogonality to the order of their squares.  The last
  * ones, with ||Theta||_F <= 2e-3, are its closing corrections.  on = 0: sweeps
  * only, until off(A) <= 1e-13 ||A||_F.  on = 1 with max_angle_norm below 2e-3,
- * or in the mixed precisions with 64 < n <= 128: sweeps until off(A) <= 1e-8
+ * or in the mixed precisions with 64 < n <= 192: sweeps until off(A) <= 1e-8
  * ||A||_F, then one rotation of every pair in place of the last sweep; one
  * whose angles exceed the bound leaves A unchanged and the solve finishes with
  * sweeps (0 rejects every one that would rotate).  on: 0 or 1 (default 1);

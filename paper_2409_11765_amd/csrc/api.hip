@@ -12,6 +12,7 @@
 
 #include "../../include/cmaes_mi355x.h"
 #include "internal.h"
+#include "vector.h"
 
 namespace cmx {
 
@@ -161,7 +162,7 @@ struct cmaes {
   double *m = nullptr, *ps = nullptr, *pc = nullptr, *C = nullptr, *B = nullptr, *D = nullptr;
   double *w = nullptr, *sqrtw = nullptr, *x_best = nullptr, *hist = nullptr, *d = nullptr;
   double *xstar = nullptr, *Rd = nullptr, *yw = nullptr, *zw = nullptr;
-  double *part_yw = nullptr, *part_zw = nullptr, *part_bz = nullptr, *f = nullptr, *X = nullptr;
+  double *part_yw = nullptr, *part_zw = nullptr, *bz = nullptr, *f = nullptr, *X = nullptr;
   int32_t* order = nullptr;
   int32_t* rank_work = nullptr;  // partial rank counts
   // sampling-precision buffers
@@ -171,7 +172,6 @@ struct cmaes {
   void* syrk_work = nullptr;
   void* split = nullptr;  // bf16 hi / lo operands of the bf16 x 3 sampling product
   size_t split_cap = 0;
-  double* u = nullptr;
   EigWork ew{};
   // the vectors and scalars of cmaes_state / cmaes_set_state pass through this
   // pinned, mapped host block, one kernel for all of them (dxfer: its device
@@ -274,12 +274,11 @@ void free_all(cmaes* h) {
   dev_free(h, h->D);
   dev_free(h, h->x_best);
   dev_free(h, h->d);
-  dev_free(h, h->u);
   dev_free(h, h->xstar);
   dev_free(h, h->Rd);
   dev_free(h, h->yw);
   dev_free(h, h->zw);
-  dev_free(h, h->part_bz);
+  dev_free(h, h->bz);
   dev_free(h, h->BD);
   dev_free(h, h->Rt);
   dev_free(h, h->coef);
@@ -435,10 +434,9 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ps, 8ull * ldn)) || (rc = dev_alloc(h, &h->pc, 8ull * ldn)) ||
       (rc = dev_alloc(h, &h->C, 8 * nn)) || (rc = dev_alloc(h, &h->B, 8 * nn)) || (rc = dev_alloc(h, &h->D, 8ull * ldn)) ||
       (rc = dev_alloc(h, &h->x_best, 8ull * ldn)) || (rc = dev_alloc(h, &h->d, 8ull * ldn)) ||
-      (rc = dev_alloc(h, &h->u, 8ull * ldn)) ||
       (rc = dev_alloc(h, &h->xstar, 8ull * ldn)) || (rc = dev_alloc(h, &h->Rd, 8 * nn)) ||
       (rc = dev_alloc(h, &h->yw, 8ull * ldn)) || (rc = dev_alloc(h, &h->zw, 8ull * ldn)) ||
-      (rc = dev_alloc(h, &h->part_bz, 8ull * ceil_div(n, 64) * n)) || (rc = dev_alloc(h, &h->BD, e * nn)) ||
+      (rc = dev_alloc(h, &h->bz, 8ull * ceil_div(n, 64) * n)) || (rc = dev_alloc(h, &h->BD, e * nn)) ||
       (rc = dev_alloc(h, &h->Rt, e * nn)) || (rc = dev_alloc(h, &h->coef, e * ldn)) ||
       (rc = dev_alloc(h, &h->ew.A, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.V, 8ull * N * N)) ||
       (rc = dev_alloc(h, &h->ew.Q, 8ull * (N / 32) * 32 * 32)) || (rc = dev_alloc(h, &h->ew.T, 8 * nn)) ||
@@ -567,7 +565,12 @@ void rec(cmaes* h, int i) {
   if (h->timing) (void)hipEventRecord(h->ev[i], h->st);
 }
 
-int phase_sample(cmaes* h, const double* Zhost) {
+ShiftArgs shift_args(const cmaes* h) {
+  return ShiftArgs{h->n, h->have_R ? h->Rd : nullptr, h->ldn, h->m, h->have_xstar ? h->xstar : nullptr, h->d, h->bz};
+}
+
+// shift: the fitness's m - x* is formed beside the normals
+int phase_sample(cmaes* h, const double* Zhost, bool shift = false) {
   const int n = h->n, lam = h->lam, ldn = h->ldn;
   rec(h, 0);
   if (Zhost) {
@@ -584,7 +587,9 @@ int phase_sample(cmaes* h, const double* Zhost) {
     }
   } else {
     kt_begin(&h->kt, KID_NORMALS);
-    CMX_HIP(launch_normals(h->st, h->Z, h->fp64, ldn, n, lam, h->seed, static_cast<uint32_t>(h->restart), h->sc));
+    const ShiftArgs sa = shift_args(h);
+    CMX_HIP(launch_normals(h->st, h->Z, h->fp64, ldn, n, lam, h->seed, static_cast<uint32_t>(h->restart), h->sc,
+                           shift ? &sa : nullptr));
     kt_end(&h->kt);
   }
   // the float32 and bf16 x 3 products time themselves (their dispatches' own
@@ -608,12 +613,12 @@ int phase_sample(cmaes* h, const double* Zhost) {
   return 0;
 }
 
-int phase_fitness(cmaes* h) {
+// the fitness of every point as *row_tiles partial sums, which the ranking adds up
+int phase_fitness(cmaes* h, int* row_tiles, bool shifted) {
   const int n = h->n, lam = h->lam, ldn = h->ldn;
-  CMX_HIP(launch_shift(h->st, n, h->have_R ? h->Rd : nullptr, ldn, h->m, h->have_xstar ? h->xstar : nullptr, h->u,
-                       h->part_bz, h->d));
+  if (!shifted) CMX_HIP(launch_shift(h->st, shift_args(h)));
   FitnessArgs fa{h->obj_kind, h->d, h->coef, h->sc, h->partial, lam};
-  int tiles = 0;
+  int& tiles = *row_tiles;
   const bool g32 = h->have_R && !h->fp64;  // the float32 tile launch times itself
   if (!g32) kt_begin(&h->kt, KID_FITNESS);
   if (g32) {
@@ -627,27 +632,26 @@ int phase_fitness(cmaes* h) {
   else
     CMX_HIP(launch_fitness_direct(h->st, h->fp64, n, lam, h->Y, ldn, fa, &tiles));
   if (!g32) kt_end(&h->kt);
-  CMX_HIP(launch_fitness_reduce(h->st, h->fp64, h->obj_kind, n, lam, h->partial, lam, tiles, h->f));
   return 0;
 }
 
 // ranking, recombination, paths / sigma and the covariance update; the
 // eigensolve (if due) is begun here and finished by eigen_drive or the
 // batch driver
-int phase_update_pre(cmaes* h) {
+int phase_update_pre(cmaes* h, int tiles) {
   const int n = h->n, lam = h->lam, ldn = h->ldn, mu = h->hp.kp.mu;
   rec(h, 2);
   kt_begin(&h->kt, KID_RANK);
-  CMX_HIP(launch_rank(h->st, h->f, lam, h->order, h->rank_work));
+  CMX_HIP(launch_rank(h->st, h->fp64,
+                      RankArgs{n, lam, h->partial, tiles, h->f, h->order, h->rank_work, h->Y, ldn, h->m, h->x_best,
+                               h->hist, h->sp.hist_len, h->sc}));
   kt_end(&h->kt);
-  CMX_HIP(launch_best(h->st, h->fp64, n, lam, h->f, h->order, h->Y, ldn, h->m, h->x_best, h->hist, h->sp.hist_len, h->sc));
   rec(h, 3);
-  int nch = 0, nchb = 0;
+  int nch = 0, bz_chunks = 1;
   CMX_HIP(launch_recombine(h->st, h->fp64, n, lam, mu, h->Y, h->Z, ldn, h->order, h->w, h->sqrtw, h->Ysel, ldn,
                            h->part_yw, h->part_zw, &nch));
-  CMX_HIP(launch_reduce_yz(h->st, n, nch, h->part_yw, h->part_zw, h->yw, h->zw));
-  CMX_HIP(launch_matvec(h->st, n, h->B, ldn, h->zw, h->part_bz, &nchb));
-  CMX_HIP(launch_vec_update(h->st, h->hp.kp, nchb, h->part_bz, h->yw, h->m, h->ps, h->pc, h->sc));
+  CMX_HIP(launch_bz(h->st, n, h->B, ldn, nch, h->part_yw, h->part_zw, h->yw, h->zw, h->bz, &bz_chunks));
+  CMX_HIP(launch_vec_update(h->st, h->hp.kp, h->bz, bz_chunks, h->yw, h->m, h->ps, h->pc, h->sc));
   rec(h, 4);
   const int variant = h->opt.variant;
   // the rank-mu operands: mu columns, or all lam ranks with signed copies (active)
@@ -830,10 +834,10 @@ int finish_generation(cmaes* h) {
   return nonfinite ? numeric_failure(h) : 0;
 }
 
-int phase_update(cmaes* h) {
+int phase_update(cmaes* h, int tiles = 0) {
   set_due(h);
   if (int rc = small_ready(h)) return rc;
-  if (int rc = phase_update_pre(h)) return rc;
+  if (int rc = phase_update_pre(h, tiles)) return rc;
   if (tail_queued(h))
     if (int rc = queue_tail(h)) return rc;
   advance_counters(h);
@@ -890,9 +894,10 @@ int front(cmaes* h) {
   const bool tail = tail_queued(h);
   const bool can_graph = h->graphs && h->st != nullptr && !h->timing && !h->kt.on;
   if (!can_graph) {
-    if (int rc = phase_sample(h, nullptr)) return rc;
-    if (int rc = phase_fitness(h)) return rc;
-    if (int rc = phase_update_pre(h)) return rc;
+    int tiles = 0;
+    if (int rc = phase_sample(h, nullptr, true)) return rc;
+    if (int rc = phase_fitness(h, &tiles, true)) return rc;
+    if (int rc = phase_update_pre(h, tiles)) return rc;
     if (tail)
       if (int rc = queue_tail(h)) return rc;
     advance_counters(h);
@@ -905,9 +910,10 @@ int front(cmaes* h) {
     h->gx[slot] = nullptr;
     h->gkey[slot] = 0;
     CMX_HIP(hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal));
-    int rc = phase_sample(h, nullptr);
-    if (!rc) rc = phase_fitness(h);
-    if (!rc) rc = phase_update_pre(h);
+    int tiles = 0;
+    int rc = phase_sample(h, nullptr, true);
+    if (!rc) rc = phase_fitness(h, &tiles, true);
+    if (!rc) rc = phase_update_pre(h, tiles);
     if (!rc && tail) rc = queue_tail(h);
     hipGraph_t g = nullptr;
     const hipError_t ce = hipStreamEndCapture(h->st, &g);
@@ -1128,8 +1134,9 @@ int cmaes_generation_with_z(cmaes_t* h, const double* Z) {
   if (int rc = ensure_ready(h)) return rc;
   if (int rc = check_running(h)) return rc;
   if (int rc = phase_sample(h, Z)) return rc;
-  if (int rc = phase_fitness(h)) return rc;
-  return phase_update(h);
+  int tiles = 0;
+  if (int rc = phase_fitness(h, &tiles, false)) return rc;
+  return phase_update(h, tiles);
 }
 
 }  // extern "C"
@@ -1475,7 +1482,8 @@ int cmaes_autotune(cmaes_t* h, int reps, double* us, int32_t* chosen) {
     const int n = h->n, lam = h->lam, ldn = h->ldn, mu = h->hp.kp.mu;
     // operands with the next generation's statistics: its own normals and the
     // current B D; the next generation redraws Z and rewrites Y, Ysel
-    CMX_HIP(launch_normals(h->st, h->Z, false, ldn, n, lam, h->seed, static_cast<uint32_t>(h->restart), h->sc));
+    CMX_HIP(launch_normals(h->st, h->Z, false, ldn, n, lam, h->seed, static_cast<uint32_t>(h->restart), h->sc,
+                           nullptr));
     CMX_HIP(hipMemcpyAsync(h->Y, h->Z, 4ull * ldn * lam, hipMemcpyDeviceToDevice, h->st));
     CMX_HIP(hipMemcpyAsync(h->Ysel, h->Z, 4ull * ldn * mu, hipMemcpyDeviceToDevice, h->st));
     hipEvent_t e0, e1;
@@ -1725,8 +1733,6 @@ int build_front_tables(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     e.Rd = h->Rd;
     e.m = h->m;
     e.xstar = h->have_xstar ? h->xstar : nullptr;
-    e.u = h->u;
-    e.part_bz = h->part_bz;
     e.d = h->d;
     e.kind = h->obj_kind;
     e.fit_tiles = g32_row_tiles(ft.cfg[G32_FITNESS], n);
@@ -1746,6 +1752,7 @@ int build_front_tables(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     e.part_zw = h->part_zw;
     e.yw = h->yw;
     e.zw = h->zw;
+    e.bz = h->bz;
     e.B = h->B;
     e.D = h->D;
     e.ps = h->ps;
@@ -1776,18 +1783,14 @@ int build_front_tables(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     const int nb256 = ceil_div(n, 256);
     wgs[GF_NORMALS] = static_cast<int>((static_cast<int64_t>((n + 3) / 4) * lam + 255) / 256);
     wgs[GF_SAMPLE] = g32_tiles(ft.cfg[G32_SAMPLE], n, lam);
-    wgs[GF_SUB] = nb256;
-    wgs[GF_RMATVEC] = nb256 * ceil_div(n, 64);
-    wgs[GF_RVEC] = nb256;
+    wgs[GF_SHIFT] = shift_blocks(n, true);
     wgs[GF_FITNESS] = g32_tiles(ft.cfg[G32_FITNESS], n, lam);
-    wgs[GF_FREDUCE] = ceil_div(lam, 256);
-    wgs[GF_RANK] = rank_chunks(lam);
+    wgs[GF_SORT] = rank_chunks(lam);
     wgs[GF_MERGE] = rank_merge_wgs(lam);
-    wgs[GF_SCATTER] = rank_chunks(lam);
-    wgs[GF_BEST] = 1;
-    wgs[GF_RECOMB] = nb256 * ceil_div(mu, 64);
-    wgs[GF_REDYZ] = nb256;
-    wgs[GF_BMATVEC] = nb256 * ceil_div(n, 64);
+    wgs[GF_SCATTER] = rank_scatter_wgs(lam);
+    wgs[GF_RECOMB] = recombine_wgs(n, mu);
+    wgs[GF_REDYZ] = reduce_yz_wgs(n, mu);
+    wgs[GF_BZ] = shift_blocks(n, true);
     wgs[GF_VECUPD] = 1;
     syrk32_group_wgs(ft.cfg[G32_SYRK], n, mu, &wgs[GF_SYRK], &wgs[GF_SYRKEPI]);
     wgs[GF_INIT] = static_cast<int>((static_cast<int64_t>(N) * N + 255) / 256);
@@ -1851,11 +1854,9 @@ int grouped_front(LockstepGroup& g, const std::vector<cmaes*>& hs, const GroupDu
   (void)hs;
   CMX_HIP(launch_group_normals(st, tab, off(GF_NORMALS), count, wgs(GF_NORMALS)));
   CMX_HIP(launch_group_g32(st, ft.cfg[G32_SAMPLE], G32_SAMPLE, tab, off(GF_SAMPLE), count, wgs(GF_SAMPLE)));
-  for (int k : {GF_SUB, GF_RMATVEC, GF_RVEC})
-    CMX_HIP(launch_group_update(st, k, tab, off(k), count, wgs(k), nullptr));
+  CMX_HIP(launch_group_update(st, GF_SHIFT, tab, off(GF_SHIFT), count, wgs(GF_SHIFT), nullptr));
   CMX_HIP(launch_group_g32(st, ft.cfg[G32_FITNESS], G32_FITNESS, tab, off(GF_FITNESS), count, wgs(GF_FITNESS)));
-  CMX_HIP(launch_group_fitness_reduce(st, tab, off(GF_FREDUCE), count, wgs(GF_FREDUCE)));
-  for (int k : {GF_RANK, GF_MERGE, GF_SCATTER, GF_BEST, GF_RECOMB, GF_REDYZ, GF_BMATVEC, GF_VECUPD})
+  for (int k : {GF_SORT, GF_MERGE, GF_SCATTER, GF_RECOMB, GF_REDYZ, GF_BZ, GF_VECUPD})
     CMX_HIP(launch_group_update(st, k, tab, off(k), count, wgs(k), nullptr));
   CMX_HIP(launch_group_syrk(st, ft.cfg[G32_SYRK], tab, off(GF_SYRK), wgs(GF_SYRK), off(GF_SYRKEPI), wgs(GF_SYRKEPI),
                             count));

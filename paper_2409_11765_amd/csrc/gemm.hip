@@ -560,30 +560,6 @@ __global__ void __launch_bounds__(256) k_fitness_direct(int n, int lam, const T*
   epi.partial[static_cast<int64_t>(m0 / C::BM) * epi.ldp + col] = sum;
 }
 
-template <typename T>
-__device__ __forceinline__ void fitness_reduce_body(int bx, int lam, const T* __restrict__ partial, int ldp,
-                                                    int tiles, double add, double* __restrict__ f) {
-  const int k = bx * blockDim.x + threadIdx.x;
-  if (k >= lam) return;
-  double s = 0.0;
-#pragma unroll 16
-  for (int t = 0; t < tiles; ++t) s += static_cast<double>(partial[static_cast<int64_t>(t) * ldp + k]);
-  f[k] = s + add;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_fitness_reduce(int lam, const T* __restrict__ partial, int ldp,
-                                                        int tiles, double add, double* __restrict__ f) {
-  fitness_reduce_body<T>(blockIdx.x, lam, partial, ldp, tiles, add, f);
-}
-
-__global__ void __launch_bounds__(256) kg_fitness_reduce(const GFront* __restrict__ g, const int* __restrict__ off,
-                                                         int count) {
-  const int i = group_find(off, count, blockIdx.x);
-  const GFront& e = g[i];
-  fitness_reduce_body<float>(blockIdx.x - off[i], e.lam, e.partial, e.lam, e.fit_tiles, 0.0, e.f);
-}
-
 }  // namespace
 
 hipError_t launch_sample_gemm_f64(hipStream_t st, int n, int lam, const double* BD, int ldbd, const double* Z,
@@ -616,20 +592,6 @@ hipError_t launch_fitness_direct(hipStream_t st, bool fp64, int n, int lam, cons
     const int tiles = *row_tiles * ceil_div(lam, C::BN);
     k_fitness_direct<float><<<tiles, 256, 0, st>>>(n, lam, static_cast<const float*>(Y), ldy, e);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_fitness_reduce(hipStream_t st, bool fp64, int kind, int n, int lam,
-                                 const void* partial, int ld_partial, int row_tiles, double* f) {
-  (void)kind;
-  (void)n;
-  const int blocks = ceil_div(lam, 256);
-  if (fp64)
-    k_fitness_reduce<double><<<blocks, 256, 0, st>>>(lam, static_cast<const double*>(partial),
-                                                     ld_partial, row_tiles, 0.0, f);
-  else
-    k_fitness_reduce<float><<<blocks, 256, 0, st>>>(lam, static_cast<const float*>(partial), ld_partial,
-                                                    row_tiles, 0.0, f);
   return hipGetLastError();
 }
 
@@ -666,11 +628,6 @@ hipError_t launch_dgemm(hipStream_t st, bool ta, bool tb, int M, int N, int K, c
   else if (ta && !tb) k_dgemm_kg<true, false><<<tiles, 512, 0, st>>>(M, N, K, A, lda, B, ldb, e);
   else if (!ta && tb) k_dgemm_kg<false, true><<<tiles, 512, 0, st>>>(M, N, K, A, lda, B, ldb, e);
   else k_dgemm_kg<true, true><<<tiles, 512, 0, st>>>(M, N, K, A, lda, B, ldb, e);
-  return hipGetLastError();
-}
-
-hipError_t launch_group_fitness_reduce(hipStream_t st, const GFront* g, const int* off, int count, int wgs) {
-  if (wgs > 0) kg_fitness_reduce<<<wgs, 256, 0, st>>>(g, off, count);
   return hipGetLastError();
 }
 

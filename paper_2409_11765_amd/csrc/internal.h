@@ -112,8 +112,10 @@ inline int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
 // ---- launchers (each queues work on `st` and returns a hipError_t) --------
 // random numbers
+// (shift, may be null: d = R (m - x*) is formed beside them)
+struct ShiftArgs;
 hipError_t launch_normals(hipStream_t st, void* Z, bool fp64, int ldz, int n, int lam,
-                          uint64_t seed, uint32_t restart, const DevScalars* sc);
+                          uint64_t seed, uint32_t restart, const DevScalars* sc, const ShiftArgs* shift);
 hipError_t launch_init_mean(hipStream_t st, double* m, int n, double lo, double hi,
                             uint64_t seed, uint32_t restart);
 
@@ -139,13 +141,26 @@ hipError_t launch_fitness_gemm_f64(hipStream_t st, int n, int lam, const double*
                                    const FitnessArgs& fa, int* row_tiles);
 hipError_t launch_fitness_direct(hipStream_t st, bool fp64, int n, int lam, const void* Y, int ldy,
                                  const FitnessArgs& fa, int* row_tiles);
-hipError_t launch_fitness_reduce(hipStream_t st, bool fp64, int kind, int n, int lam,
-                                 const void* partial, int ld_partial, int row_tiles, double* f);
 
 // ranking
-// order[r] = index of rank r (ascending f, ties by index, NaN last); work
-// holds rank_work_elems(lam) int32: the sorted chunks and partial counts
-hipError_t launch_rank(hipStream_t st, const double* f, int lam, int32_t* order, int32_t* work);
+// order[r] = index of rank r (ascending f, ties by index, NaN last), with f
+// summed up first from `tiles` partial sums a point (0: f is given), and the
+// best point and the f history brought up to date; work holds
+// rank_work_elems(lam) int32: the sorted chunks and partial counts
+struct RankArgs {
+  int n, lam;
+  const void* partial;  // tiles x lam, in the type of Y
+  int tiles;
+  double* f;
+  int32_t *order, *work;
+  const void* Y;
+  int ldy;
+  const double* m;
+  double *x_best, *hist;
+  int hist_len;
+  DevScalars* sc;
+};
+hipError_t launch_rank(hipStream_t st, bool fp64, const RankArgs& r);
 size_t rank_work_elems(int lam);
 
 // recombination and vector updates
@@ -153,15 +168,12 @@ hipError_t launch_recombine(hipStream_t st, bool fp64, int n, int lam, int mu, c
                             const void* Z, int ld, const int32_t* order, const double* w,
                             const double* sqrtw, void* Ysel, int ldsel, double* part_yw,
                             double* part_zw, int* nchunks);
-hipError_t launch_reduce_yz(hipStream_t st, int n, int nchunks, const double* part_yw,
-                            const double* part_zw, double* yw, double* zw);
-hipError_t launch_matvec(hipStream_t st, int n, const double* B, int ldb, const double* x,
-                         double* part, int* nchunks);
-hipError_t launch_vec_update(hipStream_t st, const KParams& kp, int nchunks, const double* part_bz,
-                             const double* yw, double* m, double* ps, double* pc, DevScalars* sc);
-hipError_t launch_best(hipStream_t st, bool fp64, int n, int lam, const double* f,
-                       const int32_t* order, const void* Y, int ldy, const double* m,
-                       double* x_best, double* hist, int hist_len, DevScalars* sc);
+// bz = B z_w (*bz_chunks partial sums of n each, at most ceil(n / 64)), with y_w
+// (and z_w, scratch) from the sums of their nchunks
+hipError_t launch_bz(hipStream_t st, int n, const double* B, int ldb, int nchunks, const double* part_yw,
+                     const double* part_zw, double* yw, double* zw, double* bz, int* bz_chunks);
+hipError_t launch_vec_update(hipStream_t st, const KParams& kp, const double* bz, int bz_chunks, const double* yw,
+                             double* m, double* ps, double* pc, DevScalars* sc);
 
 // FP64 path covariance update C <- a C + c1 pc pc^T + cmu Ysel Ysel^T (lower
 // tiles + mirror); the mixed paths use g32_syrk
@@ -224,9 +236,9 @@ constexpr int kManySteps = 1 << 20;
 // 3e-13 at n = 134), so the last bit of some float32 elements of B D differs, and a
 // seed leaves the trajectory that it had by 1e-8 (one seed in eight at n = 100,
 // lambda = 272, none of 40 at n = 200, lambda = 1216, where the spectrum is tighter).
-// Up to here that costs 460 against 290 us a generation (n = 100, lambda = 272); at
-// n = 200 it would cost 730 against 370.
-constexpr int kNarrowSweepN = 128;
+// Up to here that costs 460 against 290 us a generation (n = 100, lambda = 272; n =
+// 177, lambda = 68: 560 against 290); at n = 200 it would cost 730 against 370.
+constexpr int kNarrowSweepN = 192;
 struct EigWork {
   int N = 0;      // padded size (multiple of 32)
   int* gctl = nullptr;   // control block of a grouped solve (GC_WORDS ints, device memory)
@@ -415,9 +427,8 @@ __device__ __forceinline__ int group_find(const int* __restrict__ off, int count
 // mixed precision with a rotated fused objective, one launch per step for all
 // of them (workgroups split over the descents by prefix sums, kind by kind)
 enum GroupFrontKind {
-  GF_NORMALS = 0, GF_SAMPLE, GF_SUB, GF_RMATVEC, GF_RVEC, GF_FITNESS, GF_FREDUCE, GF_RANK, GF_MERGE, GF_SCATTER,
-  GF_BEST,
-  GF_RECOMB, GF_REDYZ, GF_BMATVEC, GF_VECUPD, GF_SYRK, GF_SYRKEPI, GF_INIT, GF_OFFCOLS, GF_OFFFIN, GF_POLAR,
+  GF_NORMALS = 0, GF_SAMPLE, GF_SHIFT, GF_FITNESS, GF_SORT, GF_MERGE, GF_SCATTER,
+  GF_RECOMB, GF_REDYZ, GF_BZ, GF_VECUPD, GF_SYRK, GF_SYRKEPI, GF_INIT, GF_OFFCOLS, GF_OFFFIN, GF_POLAR,
   GF_STOP, GF_KINDS
 };
 struct GFront {  // one descent (device table entry)
@@ -432,8 +443,6 @@ struct GFront {  // one descent (device table entry)
   const double* Rd;
   double* m;
   const double* xstar;
-  double* u;
-  double* part_bz;
   double* d;
   // fitness
   int kind;
@@ -456,6 +465,7 @@ struct GFront {  // one descent (device table entry)
   double* part_zw;
   double* yw;
   double* zw;
+  double* bz;
   double* B;
   double* D;
   double* ps;
@@ -491,7 +501,6 @@ hipError_t launch_group_normals(hipStream_t st, const GFront* g, const int* off,
 hipError_t launch_group_g32(hipStream_t st, int cfg, int site, const GFront* g, const int* off, int count, int wgs);
 hipError_t launch_group_syrk(hipStream_t st, int cfg, const GFront* g, const int* off_syrk, int wgs_syrk,
                              const int* off_epi, int wgs_epi, int count);
-hipError_t launch_group_fitness_reduce(hipStream_t st, const GFront* g, const int* off, int count, int wgs);
 hipError_t launch_group_update(hipStream_t st, int kind, const GFront* g, const int* off, int count, int wgs,
                                const GroupDueMask* mask);
 hipError_t launch_group_dgemm(hipStream_t st, bool ta, const GDgemm* gd, const int* off_mm, int wgs_mm,
@@ -504,6 +513,9 @@ int g32_tiles(int cfg, int M, int N);
 // workgroups of the rank's chunk sort and scatter, and of its merge counts
 int rank_chunks(int lam);
 int rank_merge_wgs(int lam);
+int rank_scatter_wgs(int lam);
+int recombine_wgs(int n, int mu);
+int reduce_yz_wgs(int n, int mu);
 
 // stop tests; the bits go to sc->stop and, when hstop is not null, to that
 // word of pinned, mapped host memory (device address)
@@ -549,8 +561,6 @@ hipError_t launch_polar_step(hipStream_t st, int n, double* B, int ldb, const do
 hipError_t launch_set_identity(hipStream_t st, double* A, int n, int ld);
 hipError_t launch_to_precision(hipStream_t st, bool fp64, const double* src, int ld_src, void* dst,
                                int ld_dst, int rows, int cols);
-// d = R (m - x*) with R, x* optional; u and part are scratch (n and ceil(n/64) n)
-hipError_t launch_shift(hipStream_t st, int n, const double* R, int ldr, const double* m, const double* xstar,
-                        double* u, double* part, double* d);
+hipError_t launch_shift(hipStream_t st, const ShiftArgs& a);
 
 }  // namespace cmx

@@ -9,6 +9,7 @@
 // One thread produces one 4-row block and writes it with a single vector
 // store, so consecutive threads write consecutive 16/32-byte segments.
 #include "internal.h"
+#include "vector.h"
 
 namespace cmx {
 
@@ -80,6 +81,38 @@ __global__ void __launch_bounds__(256) k_normals(T* __restrict__ Z, int ldz, int
   normals_body<T>(blockIdx.x, Z, ldz, n, lam, k0, k1, restart, sc);
 }
 
+// The first `shifts` workgroups form d = R (m - x*) instead, which the fitness
+// will need: one launch of 4-5 us less on a generation's chain.  Its registers
+// leave the CUs four workgroups where k_normals has eight, which does not matter
+// while there are no more (kFewBlocks); with 6000, at n = 1000 and lambda = 6144,
+// the normals took 47 us instead of 24.  (Larger n have their own kernel for d.)
+constexpr int kFewBlocks = 1024;
+template <typename T>
+__global__ void __launch_bounds__(256) k_normals_shift(T* __restrict__ Z, int ldz, int n, int lam, uint32_t k0,
+                                                       uint32_t k1, uint32_t restart,
+                                                       const DevScalars* __restrict__ sc, ShiftArgs shift,
+                                                       int shifts) {
+  const int b = blockIdx.x;
+  if (b < shifts)
+    shift_body(b, shift);
+  else
+    normals_body<T>(b - shifts, Z, ldz, n, lam, k0, k1, restart, sc);
+}
+
+template <typename T>
+hipError_t normals(hipStream_t st, T* Z, int ldz, int n, int lam, uint32_t k0, uint32_t k1, uint32_t restart,
+                   const DevScalars* sc, const ShiftArgs* shift) {
+  const int blocks = static_cast<int>((static_cast<int64_t>((n + 3) / 4) * lam + 255) / 256);
+  if (shift && blocks <= kFewBlocks && n <= kMvOneMax) {
+    const int shifts = shift_blocks(shift->n, shift->R != nullptr);
+    k_normals_shift<T><<<blocks + shifts, 256, 0, st>>>(Z, ldz, n, lam, k0, k1, restart, sc, *shift, shifts);
+    return hipGetLastError();
+  }
+  k_normals<T><<<blocks, 256, 0, st>>>(Z, ldz, n, lam, k0, k1, restart, sc);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !shift ? e : launch_shift(st, *shift);
+}
+
 // the normals of every descent of a group (float32)
 __global__ void __launch_bounds__(256) kg_normals(const GFront* __restrict__ g, const int* __restrict__ off,
                                                   int count) {
@@ -102,17 +135,11 @@ __global__ void k_init_mean(double* __restrict__ m, int n, double lo, double hi,
 }  // namespace
 
 hipError_t launch_normals(hipStream_t st, void* Z, bool fp64, int ldz, int n, int lam,
-                          uint64_t seed, uint32_t restart, const DevScalars* sc) {
+                          uint64_t seed, uint32_t restart, const DevScalars* sc, const ShiftArgs* shift) {
   if ((ldz & 3) != 0) return hipErrorInvalidValue;  // vector stores need 4-aligned columns
-  const int nb = (n + 3) / 4;
-  const int64_t total = static_cast<int64_t>(nb) * lam;
-  const int blocks = static_cast<int>((total + 255) / 256);
   const uint32_t k0 = static_cast<uint32_t>(seed), k1 = static_cast<uint32_t>(seed >> 32);
-  if (fp64)
-    k_normals<double><<<blocks, 256, 0, st>>>(static_cast<double*>(Z), ldz, n, lam, k0, k1, restart, sc);
-  else
-    k_normals<float><<<blocks, 256, 0, st>>>(static_cast<float*>(Z), ldz, n, lam, k0, k1, restart, sc);
-  return hipGetLastError();
+  return fp64 ? normals(st, static_cast<double*>(Z), ldz, n, lam, k0, k1, restart, sc, shift)
+              : normals(st, static_cast<float*>(Z), ldz, n, lam, k0, k1, restart, sc, shift);
 }
 
 hipError_t launch_group_normals(hipStream_t st, const GFront* g, const int* off, int count, int wgs) {

@@ -8,6 +8,7 @@
 // All reductions use a fixed order (no floating-point atomics), so a run is
 // bitwise reproducible.
 #include "internal.h"
+#include "vector.h"
 
 namespace cmx {
 
@@ -17,60 +18,135 @@ __device__ __forceinline__ double rank_key(double v) { return v != v ? __builtin
 
 // ---- ranking by chunk sort and merge: the keys (f, index), NaN counted as
 // +inf, are cut into chunks of kSortChunk; each chunk is sorted by a bitonic
-// network in LDS (k_chunk_sort); the rank of a key is its position in its own
-// chunk plus, for every other chunk, the number of that chunk's keys below
-// it, found by binary search (k_merge_count, chunks taken kMergeGroup at a
-// time from LDS, one partial count per group); k_merge_scatter sums the
-// counts and writes order[rank] = index.  The keys are distinct, so the ranks
-// form the stable ascending permutation exactly; the counts are integers.
+// network (k_sort); the rank of a key is its position in its own chunk plus, for
+// every other chunk, the number of that chunk's keys below it, found by binary
+// search (k_merge, chunks taken kMergeGroup at a time from LDS); with more than
+// kMergeGroup chunks the counts of several groups are summed by k_scatter.
+// The keys are distinct, so the ranks form the stable ascending permutation
+// exactly; the counts are integers.  The first kernel also sums up f from the
+// fitness tiles, and the last one writes order[rank] = index and the best point:
+// one launch up to lambda = 256 and two up to 2048, where the fitness sum, the
+// sort, the counts, their scatter and the best point took four or five of 4-7 us.
 constexpr int kSortChunk = 256, kMergeGroup = 8;
 
 __device__ __forceinline__ bool key_less(double ka, int ia, double kb, int ib) {
   return ka < kb || (ka == kb && ia < ib);
 }
 
-// the sorted chunks: keys in skey (double), indices in sidx; padding entries
-// (+inf, INT_MAX) sort after every real key
-__device__ __forceinline__ void chunk_sort_body(int c, const double* __restrict__ f, int lam,
-                                                double* __restrict__ skey, int* __restrict__ sidx) {
-  __shared__ double k[kSortChunk];
-  __shared__ int ix[kSortChunk];
-  const int t = threadIdx.x, i = c * kSortChunk + t;
-  k[t] = i < lam ? rank_key(f[i]) : __builtin_inf();
-  ix[t] = i < lam ? i : 0x7fffffff;
-  for (int size = 2; size <= kSortChunk; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      __syncthreads();
-      const int u = t ^ stride;
-      if (u > t) {
-        const bool up = (t & size) == 0;
-        const double ka = k[t], kb = k[u];
-        const int ia = ix[t], ib = ix[u];
-        if (key_less(kb, ib, ka, ia) == up) {
-          k[t] = kb;
-          ix[t] = ib;
-          k[u] = ka;
-          ix[u] = ia;
-        }
-      }
-    }
+// Best-so-far point and the f-history ring, before m and sigma move: called by
+// every thread of a workgroup with its key's rank (negative: none), index and value.
+template <typename T>
+struct BestArgs {
+  int n, lam;
+  const T* Y;
+  int ldy;
+  const double* m;
+  double *x_best, *hist;
+  int hist_len;
+  DevScalars* sc;
+  int32_t* order;
+};
+template <typename T>
+__device__ __forceinline__ void place(const BestArgs<T>& a, int rank, int i, double key) {
+  __shared__ int first;
+  if (threadIdx.x == 0) first = -1;
   __syncthreads();
-  skey[i] = k[t];
-  sidx[i] = ix[t];
+  if (rank >= 0) {
+    a.order[rank] = i;
+    if (rank == a.lam - 1) a.sc->f_gen_max = key;
+    if (rank == 0) first = threadIdx.x;
+  }
+  __syncthreads();
+  if (first < 0) return;  // (uniform)
+  __shared__ double f0s;
+  __shared__ int i0s;
+  if (static_cast<int>(threadIdx.x) == first) {
+    f0s = key;
+    i0s = i;
+  }
+  __syncthreads();
+  const double f0 = f0s;
+  const bool better = f0 < a.sc->f_best;
+  if (better) {
+    const double sigma = a.sc->sigma;
+    const T* y = a.Y + static_cast<int64_t>(i0s) * a.ldy;
+    for (int q = threadIdx.x; q < a.n; q += blockDim.x) a.x_best[q] = a.m[q] + sigma * static_cast<double>(y[q]);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.hist[a.sc->hist_count % a.hist_len] = f0;
+    a.sc->hist_count += 1;
+    a.sc->f_gen_min = f0;
+    if (better) a.sc->f_best = f0;
+  }
 }
 
-__global__ void __launch_bounds__(256) k_chunk_sort(const double* __restrict__ f, int lam, double* __restrict__ skey,
-                                                    int* __restrict__ sidx) {
-  chunk_sort_body(blockIdx.x, f, lam, skey, sidx);
+// chunk c: f from `tiles` partial sums a point (tiles = 0: f is given), sorted; a
+// padding key (+inf, INT_MAX) is above every real one.  Partners in a wave
+// exchange by shuffles, and the network is no wider than the chunk's keys.  The only
+// chunk is the order itself; the sorted chunks go to skey and sidx otherwise.
+template <typename T>
+__device__ __forceinline__ void sort_body(int c, int nchunks, const T* __restrict__ partial, int tiles,
+                                          double* __restrict__ f, double* __restrict__ skey, int* __restrict__ sidx,
+                                          const BestArgs<T>& a) {
+  __shared__ double ks[kSortChunk];
+  __shared__ int is[kSortChunk];
+  const int t = threadIdx.x, i = c * kSortChunk + t, lam = a.lam;
+  double k = __builtin_inf();
+  int ix = 0x7fffffff;
+  if (i < lam) {
+    double v;
+    if (tiles > 0) {
+      v = sum_strided(partial + i, lam, tiles);
+      v += 0.0;
+      f[i] = v;
+    } else {
+      v = f[i];
+    }
+    k = rank_key(v);
+    ix = i;
+  }
+  const int keys = min(kSortChunk, lam - c * kSortChunk);
+  for (int size = 2; size < 2 * keys; size <<= 1)
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      double pk;
+      int pi;
+      if (stride >= 64) {
+        __syncthreads();
+        ks[t] = k;
+        is[t] = ix;
+        __syncthreads();
+        pk = ks[t ^ stride];
+        pi = is[t ^ stride];
+      } else {
+        pk = __shfl_xor(k, stride);
+        pi = __shfl_xor(ix, stride);
+      }
+      const bool up = (t & size) == 0, low = (t & stride) == 0;
+      const bool less = low ? key_less(pk, pi, k, ix) : key_less(k, ix, pk, pi);
+      if (less == up) {
+        k = pk;
+        ix = pi;
+      }
+    }
+  if (nchunks == 1) {
+    place(a, ix < lam ? t : -1, ix, k);
+  } else {
+    skey[i] = k;
+    sidx[i] = ix;
+  }
 }
 
 // workgroup (c, g): the keys of chunk c counted against chunks
-// [g kMergeGroup, (g + 1) kMergeGroup) other than c
-__device__ __forceinline__ void merge_count_body(int c, int g, int nchunks, const double* __restrict__ skey,
-                                                 const int* __restrict__ sidx, int lam, int32_t* __restrict__ part) {
+// [g kMergeGroup, (g + 1) kMergeGroup) other than c; the ranks, if these are
+// all chunks
+template <typename T>
+__device__ __forceinline__ void merge_body(int c, int g, int nchunks, const double* __restrict__ skey,
+                                           const int* __restrict__ sidx, int32_t* __restrict__ part,
+                                           const BestArgs<T>& a) {
   __shared__ double ok[kSortChunk];
   __shared__ int oi[kSortChunk];
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lam = a.lam;
   const double kt = skey[c * kSortChunk + t];
   const int it = sidx[c * kSortChunk + t];
   int cnt = 0;
@@ -91,55 +167,90 @@ __device__ __forceinline__ void merge_count_body(int c, int g, int nchunks, cons
     }
     cnt += lo;
   }
-  if (it < lam) part[static_cast<int64_t>(g) * lam + it] = cnt;
+  if (nchunks <= kMergeGroup)
+    place(a, it < lam ? t + cnt : -1, it, kt);
+  else if (it < lam)
+    part[static_cast<int64_t>(g) * lam + it] = cnt;
 }
 
-__global__ void __launch_bounds__(256) k_merge_count(int nchunks, const double* __restrict__ skey,
-                                                     const int* __restrict__ sidx, int lam,
-                                                     int32_t* __restrict__ part) {
-  merge_count_body(blockIdx.x, blockIdx.y, nchunks, skey, sidx, lam, part);
-}
-
-__device__ __forceinline__ void merge_scatter_body(int c, int ngroups, const int* __restrict__ sidx, int lam,
-                                                   const int32_t* __restrict__ part, int32_t* __restrict__ order) {
+template <typename T>
+__device__ __forceinline__ void scatter_body(int c, int ngroups, const double* __restrict__ skey,
+                                             const int* __restrict__ sidx, const int32_t* __restrict__ part,
+                                             const BestArgs<T>& a) {
   const int t = threadIdx.x;
   const int i = sidx[c * kSortChunk + t];
-  if (i >= lam) return;
-  int rank = t;
-  for (int g = 0; g < ngroups; ++g) rank += part[static_cast<int64_t>(g) * lam + i];
-  order[rank] = i;
+  int rank = -1;
+  if (i < a.lam) {
+    rank = t;
+    for (int g = 0; g < ngroups; ++g) rank += part[static_cast<int64_t>(g) * a.lam + i];
+  }
+  place(a, rank, i, skey[c * kSortChunk + t]);
 }
 
-__global__ void __launch_bounds__(256) k_merge_scatter(int ngroups, const int* __restrict__ sidx, int lam,
-                                                       const int32_t* __restrict__ part, int32_t* __restrict__ order) {
-  merge_scatter_body(blockIdx.x, ngroups, sidx, lam, part, order);
+template <typename T>
+__global__ void __launch_bounds__(256) k_sort(const T* __restrict__ partial, int tiles, double* __restrict__ f,
+                                              double* __restrict__ skey, int* __restrict__ sidx, BestArgs<T> a) {
+  sort_body<T>(blockIdx.x, gridDim.x, partial, tiles, f, skey, sidx, a);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_merge(const double* __restrict__ skey, const int* __restrict__ sidx,
+                                               int32_t* __restrict__ part, BestArgs<T> a) {
+  merge_body<T>(blockIdx.x, blockIdx.y, gridDim.x, skey, sidx, part, a);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_scatter(int ngroups, const double* __restrict__ skey,
+                                                 const int* __restrict__ sidx, const int32_t* __restrict__ part,
+                                                 BestArgs<T> a) {
+  scatter_body<T>(blockIdx.x, ngroups, skey, sidx, part, a);
 }
 
 // y_w = sum_{r<mu} w_r y_{order[r]}, z_w likewise (float64 accumulation), and
-// Yhat[:, r] = sqrt(w_r) y_{order[r]} for the rank-mu SYRK.  Grid: rows x
-// chunks of 64 ranks; each chunk writes its own partial sums.
+// Yhat[:, r] = sqrt(w_r) y_{order[r]} for the rank-mu SYRK.  Grid: 32 rows x
+// chunks of 64 ranks; each chunk writes its own partial sums, in rank order.
+// All of a tile's loads are under way at once, eight ranks to a thread, and the
+// sums read LDS: with a thread for a row's 64 ranks the kernel waited on a chain
+// of loads (n = 333, lambda = 1030 float64 15.7 us, now 5.4; n = 1000, lambda = 6144
+// 22.4 to 21).
+constexpr int kRecRows = 32, kRecRanks = 64;
 template <typename T>
 __device__ __forceinline__ void recombine_body(int bx, int by, int n, int mu, const T* __restrict__ Y,
                                                const T* __restrict__ Z, int ld, const int32_t* __restrict__ order,
                                                const double* __restrict__ w, const double* __restrict__ sqrtw,
                                                T* __restrict__ Ysel, int ldsel, double* __restrict__ part_yw,
                                                double* __restrict__ part_zw) {
-  const int i = bx * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int r0 = by * 64, r1 = min(mu, r0 + 64);
-  double ay = 0.0, az = 0.0;
-  // unrolled so that many loads are in flight; the sums keep rank order
-#pragma unroll 16
-  for (int r = r0; r < r1; ++r) {
-    const int64_t c = static_cast<int64_t>(order[r]) * ld;
-    const T y = Y[c + i];
-    const T z = Z[c + i];
-    ay += w[r] * static_cast<double>(y);
-    az += w[r] * static_cast<double>(z);
-    Ysel[static_cast<int64_t>(r) * ldsel + i] = static_cast<T>(sqrtw[r] * static_cast<double>(y));
+  constexpr int PER = kRecRanks * kRecRows / 256;
+  __shared__ T ys[kRecRanks][kRecRows], zs[kRecRanks][kRecRows];
+  __shared__ double ws[kRecRanks];
+  const int t = threadIdx.x, r = t & (kRecRows - 1), g = t / kRecRows;
+  const int i = min(bx * kRecRows + r, n - 1), r0 = by * kRecRanks, cnt = min(kRecRanks, mu - r0);
+  const bool mine = bx * kRecRows + r < n;
+  T y[PER], z[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int64_t c = static_cast<int64_t>(order[r0 + min(g * PER + q, cnt - 1)]) * ld;
+    y[q] = Y[c + i];
+    z[q] = Z[c + i];
   }
-  part_yw[static_cast<int64_t>(by) * n + i] = ay;
-  part_zw[static_cast<int64_t>(by) * n + i] = az;
+  if (t < cnt) ws[t] = w[r0 + t];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int k = g * PER + q;
+    ys[k][r] = y[q];
+    zs[k][r] = z[q];
+    if (mine && k < cnt)
+      Ysel[static_cast<int64_t>(r0 + k) * ldsel + i] = static_cast<T>(sqrtw[r0 + k] * static_cast<double>(y[q]));
+  }
+  __syncthreads();
+  // the first wave sums y, the second z
+  if (mine && ((t & 63) < kRecRows) && t < 128) {
+    const T(*v)[kRecRows] = t < 64 ? ys : zs;
+    double a = 0.0;
+#pragma unroll 16
+    for (int k = 0; k < cnt; ++k) a += ws[k] * static_cast<double>(v[k][r]);
+    (t < 64 ? part_yw : part_zw)[static_cast<int64_t>(by) * n + i] = a;
+  }
 }
 
 template <typename T>
@@ -153,19 +264,14 @@ __global__ void __launch_bounds__(256) k_recombine(int n, int mu, const T* __res
   recombine_body<T>(blockIdx.x, blockIdx.y, n, mu, Y, Z, ld, order, w, sqrtw, Ysel, ldsel, part_yw, part_zw);
 }
 
+// y_w and z_w from their chunks' sums, in order
 __device__ __forceinline__ void reduce_yz_body(int bx, int n, int nchunks, const double* __restrict__ py,
                                                const double* __restrict__ pz, double* __restrict__ yw,
                                                double* __restrict__ zw) {
   const int i = bx * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  double a = 0.0, b = 0.0;
-#pragma unroll 16
-  for (int c = 0; c < nchunks; ++c) {
-    a += py[static_cast<int64_t>(c) * n + i];
-    b += pz[static_cast<int64_t>(c) * n + i];
-  }
-  yw[i] = a;
-  zw[i] = b;
+  yw[i] = sum_strided(py + i, n, nchunks);
+  zw[i] = sum_strided(pz + i, n, nchunks);
 }
 
 __global__ void k_reduce_yz(int n, int nchunks, const double* __restrict__ py, const double* __restrict__ pz,
@@ -173,61 +279,90 @@ __global__ void k_reduce_yz(int n, int nchunks, const double* __restrict__ py, c
   reduce_yz_body(blockIdx.x, n, nchunks, py, pz, yw, zw);
 }
 
-// part[c][i] = sum_{j in chunk c} B[i + j ld] x[j]
-__device__ __forceinline__ void matvec_body(int bx, int by, int n, const double* __restrict__ B, int ldb,
-                                            const double* __restrict__ x, double* __restrict__ part) {
-  const int i = bx * blockDim.x + threadIdx.x;
+// part[c][i] = sum over the columns j of chunk c of M(i, j) (x_j - x0_j) (x0 null:
+// x_j)
+__global__ void __launch_bounds__(256) k_matvec(int n, const double* __restrict__ M, int ld,
+                                                const double* __restrict__ x, const double* __restrict__ x0,
+                                                double* __restrict__ part) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int j0 = by * 64, j1 = min(n, j0 + 64);
+  const int j0 = blockIdx.y * 64, j1 = min(n, j0 + 64);
   double s = 0.0;
 #pragma unroll 16
-  for (int j = j0; j < j1; ++j) s += B[static_cast<int64_t>(j) * ldb + i] * x[j];
-  part[static_cast<int64_t>(by) * n + i] = s;
+  for (int j = j0; j < j1; ++j) s += M[static_cast<int64_t>(j) * ld + i] * (x[j] - (x0 ? x0[j] : 0.0));
+  part[static_cast<int64_t>(blockIdx.y) * n + i] = s;
 }
 
-__global__ void __launch_bounds__(256) k_matvec(int n, const double* __restrict__ B, int ldb,
-                                                const double* __restrict__ x, double* __restrict__ part) {
-  matvec_body(blockIdx.x, blockIdx.y, n, B, ldb, x, part);
+// bz = B z_w; with nchunks > 0 y_w and z_w are summed up on the way, z_w by each
+// workgroup for itself (worth a launch of 4 us while that is at most kSumHere
+// loads a workgroup: n = 512 with 16 chunks; beyond it k_reduce_yz sums once)
+constexpr int kSumHere = 8192;
+__device__ __forceinline__ void bz_body(int b, int n, const double* __restrict__ B, int ldb, int nchunks,
+                                        const double* __restrict__ py, const double* __restrict__ pz,
+                                        const double* __restrict__ zw, double* __restrict__ yw,
+                                        double* __restrict__ bz) {
+  const int t = threadIdx.x;
+  const double v = matvec_rows(b * kMvRows, n, B, ldb,
+                               [&](int j) { return nchunks > 0 ? sum_strided(pz + j, n, nchunks) : zw[j]; });
+  const int i = b * kMvRows + (t & 31);
+  if (i >= n) return;
+  if (t < kMvRows)
+    bz[i] = v;
+  else if (nchunks > 0 && t >= 64 && t < 64 + kMvRows)
+    yw[i] = sum_strided(py + i, n, nchunks);
 }
 
+__global__ void __launch_bounds__(256) k_bz(int n, const double* __restrict__ B, int ldb, int nchunks,
+                                            const double* __restrict__ py, const double* __restrict__ pz,
+                                            const double* __restrict__ zw, double* __restrict__ yw,
+                                            double* __restrict__ bz) {
+  bz_body(blockIdx.x, n, B, ldb, nchunks, py, pz, zw, yw, bz);
+}
+
+// sum over NT threads as a tree of halves (thread t adds t + s, s = NT / 2 .. 1),
+// the last six levels by shuffles; the result in every thread
 template <int NT>
 __device__ double block_sum(double v, double* red) {
   red[threadIdx.x] = v;
   __syncthreads();
 #pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+  for (int s = NT / 2; s >= 64; s >>= 1) {
+    if (threadIdx.x < s) red[threadIdx.x] = v = v + red[threadIdx.x + s];
     __syncthreads();
   }
-  const double r = red[0];
+  if (threadIdx.x < 64) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+    if (threadIdx.x == 0) red[0] = v;
+  }
   __syncthreads();
-  return r;
+  return red[0];
 }
 
-// p_sigma, h_sigma, p_c, m, sigma and the covariance coefficient a.
-__device__ __forceinline__ void vec_update_body(const KParams& kp, int nchunks, const double* __restrict__ part_bz,
+// p_sigma, h_sigma, p_c, m, sigma and the covariance coefficient a, from B z_w as
+// bz_chunks partial sums.  (NT threads;
+// the sum does not depend on how many of 1024 or fewer hold no element.)
+template <int NT>
+__device__ __forceinline__ void vec_update_body(const KParams& kp, const double* __restrict__ bz, int bz_chunks,
                                                 const double* __restrict__ yw, double* __restrict__ m,
                                                 double* __restrict__ ps, double* __restrict__ pc,
                                                 DevScalars* __restrict__ sc) {
-  __shared__ double red[1024];
+  __shared__ double red[NT];
   const int n = kp.n;
   const double sigma = sc->sigma;
   const int64_t g = sc->gen;
   const double fps = sqrt(kp.cs * (2.0 - kp.cs) * kp.mueff);
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    double bz = 0.0;
-#pragma unroll 16
-    for (int c = 0; c < nchunks; ++c) bz += part_bz[static_cast<int64_t>(c) * n + i];
-    const double v = (1.0 - kp.cs) * ps[i] + fps * bz;
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const double v = (1.0 - kp.cs) * ps[i] + fps * sum_strided(bz + i, n, bz_chunks);
     ps[i] = v;
     acc += v * v;
   }
-  const double nps = sqrt(block_sum<1024>(acc, red));
   const double denom = sqrt(1.0 - pow(1.0 - kp.cs, 2.0 * static_cast<double>(g + 1)));
+  const double nps = sqrt(block_sum<NT>(acc, red));
   const double hsig = (nps / denom < (1.4 + 2.0 / (n + 1.0)) * kp.chin) ? 1.0 : 0.0;
   const double fpc = hsig * sqrt(kp.cc * (2.0 - kp.cc) * kp.mueff);
-  for (int i = threadIdx.x; i < n; i += 1024) {
+  for (int i = threadIdx.x; i < n; i += NT) {
     pc[i] = (1.0 - kp.cc) * pc[i] + fpc * yw[i];
     m[i] = m[i] + sigma * yw[i];
   }
@@ -241,66 +376,38 @@ __device__ __forceinline__ void vec_update_body(const KParams& kp, int nchunks, 
   }
 }
 
-__global__ void __launch_bounds__(1024) k_vec_update(KParams kp, int nchunks, const double* __restrict__ part_bz,
-                                                     const double* __restrict__ yw, double* __restrict__ m,
-                                                     double* __restrict__ ps, double* __restrict__ pc,
-                                                     DevScalars* __restrict__ sc) {
-  vec_update_body(kp, nchunks, part_bz, yw, m, ps, pc, sc);
+template <int NT>
+__global__ void __launch_bounds__(NT) k_vec_update(KParams kp, const double* __restrict__ bz, int bz_chunks,
+                                                   const double* __restrict__ yw, double* __restrict__ m,
+                                                   double* __restrict__ ps, double* __restrict__ pc,
+                                                   DevScalars* __restrict__ sc) {
+  vec_update_body<NT>(kp, bz, bz_chunks, yw, m, ps, pc, sc);
 }
 
-// Best-so-far point and the f-history ring; runs before m and sigma move.
-template <typename T>
-__device__ __forceinline__ void best_body(int n, int lam, const double* __restrict__ f,
-                                          const int32_t* __restrict__ order, const T* __restrict__ Y, int ldy,
-                                          const double* __restrict__ m, double* __restrict__ x_best,
-                                          double* __restrict__ hist, int hist_len, DevScalars* __restrict__ sc) {
-  const int i0 = order[0];
-  const double f0 = rank_key(f[i0]);
-  const double flast = rank_key(f[order[lam - 1]]);
-  const bool better = f0 < sc->f_best;
-  if (better) {
-    const double sigma = sc->sigma;
-    const T* y = Y + static_cast<int64_t>(i0) * ldy;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) x_best[i] = m[i] + sigma * static_cast<double>(y[i]);
+// largest of four values each over 256 threads, and the or of their flags, in
+// every thread
+__device__ __forceinline__ void block_max4_or(double (&v)[4], int& flags) {
+  __shared__ double red[4][4];
+  __shared__ int fl[4];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = fmax(v[q], __shfl_xor(v[q], m));
+    flags |= __shfl_xor(flags, m);
+  }
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[threadIdx.x >> 6][q] = v[q];
+    fl[threadIdx.x >> 6] = flags;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    hist[sc->hist_count % hist_len] = f0;
-    sc->hist_count += 1;
-    sc->f_gen_min = f0;
-    sc->f_gen_max = flast;
-    if (better) sc->f_best = f0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = fmax(v[q], red[w][q]);
+    flags |= fl[w];
   }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_best(int n, int lam, const double* __restrict__ f,
-                                              const int32_t* __restrict__ order, const T* __restrict__ Y,
-                                              int ldy, const double* __restrict__ m, double* __restrict__ x_best,
-                                              double* __restrict__ hist, int hist_len,
-                                              DevScalars* __restrict__ sc) {
-  best_body<T>(n, lam, f, order, Y, ldy, m, x_best, hist, hist_len, sc);
-}
-
-__device__ __forceinline__ int block_or(int v, int* red) {
   __syncthreads();
-  if (threadIdx.x == 0) *red = 0;
-  __syncthreads();
-  if (v) atomicOr(red, v);
-  __syncthreads();
-  return *red;
-}
-
-__device__ __forceinline__ double block_max(double v, double* red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
 }
 
 // Stopping tests evaluated after the update (reading of Sec. 2.2; thresholds
@@ -310,43 +417,42 @@ __device__ __forceinline__ void stop_body(const KParams& kp, const StopParams& s
                                           int ldb, const double* __restrict__ D, const double* __restrict__ pc,
                                           const double* __restrict__ hist, DevScalars* __restrict__ sc,
                                           uint32_t* __restrict__ hstop) {
-  __shared__ double red[256];
-  __shared__ int ired;
   const int n = kp.n;
   const double sigma = sc->sigma;
   const int64_t g = sc->gen;
   const int ax = static_cast<int>(g % n);
-  double maxsd = 0.0, maxpc = 0.0, dmax = 0.0, dmin_neg = -__builtin_inf();
-  int axis_moves = 0, coord_stuck = 0, nonfinite = 0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+  enum { AXIS_MOVES = 1, COORD_STUCK = 2, NONFINITE = 4 };
+  // largest sd, |p_c|, D and -D; of the f history largest f and -f
+  double v[4] = {0.0, 0.0, 0.0, -__builtin_inf()};
+  double hv[4] = {-__builtin_inf(), -__builtin_inf(), 0.0, 0.0};
+  int flags = 0, none = 0;
+  for (int i = threadIdx.x; i < n; i += 256) {
     const double cii = C[static_cast<int64_t>(i) * ldc + i];
     const double sd = sqrt(cii);
-    maxsd = fmax(maxsd, sd);
-    maxpc = fmax(maxpc, fabs(pc[i]));
-    dmax = fmax(dmax, D[i]);
-    dmin_neg = fmax(dmin_neg, -D[i]);
+    v[0] = fmax(v[0], sd);
+    v[1] = fmax(v[1], fabs(pc[i]));
+    v[2] = fmax(v[2], D[i]);
+    v[3] = fmax(v[3], -D[i]);
     const double mi = m[i];
-    if (mi + 0.1 * sigma * D[ax] * B[static_cast<int64_t>(ax) * ldb + i] != mi) axis_moves = 1;
-    if (mi + 0.2 * sigma * sd == mi) coord_stuck = 1;
-    if (!isfinite(mi) || !isfinite(cii) || !isfinite(pc[i]) || !isfinite(D[i])) nonfinite = 1;
+    if (mi + 0.1 * sigma * D[ax] * B[static_cast<int64_t>(ax) * ldb + i] != mi) flags |= AXIS_MOVES;
+    if (mi + 0.2 * sigma * sd == mi) flags |= COORD_STUCK;
+    if (!isfinite(mi) || !isfinite(cii) || !isfinite(pc[i]) || !isfinite(D[i])) flags |= NONFINITE;
   }
-  maxsd = block_max(maxsd, red);
-  maxpc = block_max(maxpc, red);
-  dmax = block_max(dmax, red);
-  const double dmin = -block_max(dmin_neg, red);
-  axis_moves = block_or(axis_moves, &ired);
-  coord_stuck = block_or(coord_stuck, &ired);
-  nonfinite = block_or(nonfinite, &ired);
-  if (threadIdx.x != 0) return;
-  uint32_t bits = 0;
-  const int cnt = sc->hist_count;
-  if (cnt >= sp.hist_len) {
-    double hmin = __builtin_inf(), hmax = -__builtin_inf();
-    for (int q = 0; q < sp.hist_len; ++q) {
-      const double h = hist[(cnt - 1 - q) % sp.hist_len];
-      hmin = fmin(hmin, h);
-      hmax = fmax(hmax, h);
+  // (a full ring: the last hist_len generations are all of it)
+  const bool full = sc->hist_count >= sp.hist_len;
+  if (full)
+    for (int q = threadIdx.x; q < sp.hist_len; q += 256) {
+      hv[0] = fmax(hv[0], hist[q]);
+      hv[1] = fmax(hv[1], -hist[q]);
     }
+  block_max4_or(v, flags);
+  block_max4_or(hv, none);
+  if (threadIdx.x != 0) return;
+  const double maxsd = v[0], maxpc = v[1], dmax = v[2], dmin = -v[3];
+  const bool axis_moves = flags & AXIS_MOVES, coord_stuck = flags & COORD_STUCK, nonfinite = flags & NONFINITE;
+  uint32_t bits = 0;
+  if (full) {
+    const double hmax = hv[0], hmin = -hv[1];
     if (hmax - hmin < sp.tol_hist_fun) bits |= 1u << 0;
     if (fmax(hmax, sc->f_gen_max) - fmin(hmin, sc->f_gen_min) < sp.tol_fun) bits |= 1u << 1;
   }
@@ -379,29 +485,13 @@ __global__ void __launch_bounds__(256) k_stop(KParams kp, StopParams sp, const d
   stop_body(kp, sp, m, C, ldc, B, ldb, D, pc, hist, sc, hstop);
 }
 
-// u = m - x* (x* may be null = origin)
-__device__ __forceinline__ void sub_body(int bx, int n, const double* __restrict__ m, const double* __restrict__ xs,
-                                         double* __restrict__ u) {
-  const int i = bx * blockDim.x + threadIdx.x;
-  if (i < n) u[i] = m[i] - (xs ? xs[i] : 0.0);
-}
+__global__ void __launch_bounds__(256) k_shift(ShiftArgs a) { shift_body(blockIdx.x, a); }
 
-__global__ void k_sub(int n, const double* __restrict__ m, const double* __restrict__ xs, double* __restrict__ u) {
-  sub_body(blockIdx.x, n, m, xs, u);
-}
-
-__device__ __forceinline__ void reduce_vec_body(int bx, int n, int nchunks, const double* __restrict__ part,
-                                                double* __restrict__ out) {
-  const int i = bx * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double a = 0.0;
-#pragma unroll 16
-  for (int c = 0; c < nchunks; ++c) a += part[static_cast<int64_t>(c) * n + i];
-  out[i] = a;
-}
-
-__global__ void k_reduce_vec(int n, int nchunks, const double* __restrict__ part, double* __restrict__ out) {
-  reduce_vec_body(blockIdx.x, n, nchunks, part, out);
+// out[i] = sum over the chunks of 64 columns, in order
+__global__ void __launch_bounds__(256) k_reduce_vec(int n, int nchunks, const double* __restrict__ part,
+                                                    double* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = sum_strided(part + i, n, nchunks);
 }
 
 __global__ void k_set_identity(double* A, int n, int ld) {
@@ -503,12 +593,21 @@ __host__ __device__ inline RankWork rank_work_of(int32_t* work, int lam) {
   return w;
 }
 
-hipError_t launch_rank(hipStream_t st, const double* f, int lam, int32_t* order, int32_t* work) {
-  const RankWork w = rank_work_of(work, lam);
-  k_chunk_sort<<<w.nchunks, 256, 0, st>>>(f, lam, w.skey, w.sidx);
-  if (w.nchunks > 1) k_merge_count<<<dim3(w.nchunks, w.ngroups), 256, 0, st>>>(w.nchunks, w.skey, w.sidx, lam, w.part);
-  k_merge_scatter<<<w.nchunks, 256, 0, st>>>(w.nchunks > 1 ? w.ngroups : 0, w.sidx, lam, w.part, order);
+namespace {
+template <typename T>
+hipError_t rank(hipStream_t st, const RankArgs& r) {
+  const BestArgs<T> a{r.n,   r.lam,  static_cast<const T*>(r.Y), r.ldy,  r.m, r.x_best,
+                      r.hist, r.hist_len, r.sc, r.order};
+  const RankWork w = rank_work_of(r.work, r.lam);
+  k_sort<T><<<w.nchunks, 256, 0, st>>>(static_cast<const T*>(r.partial), r.tiles, r.f, w.skey, w.sidx, a);
+  if (w.nchunks > 1) k_merge<T><<<dim3(w.nchunks, w.ngroups), 256, 0, st>>>(w.skey, w.sidx, w.part, a);
+  if (w.ngroups > 1) k_scatter<T><<<w.nchunks, 256, 0, st>>>(w.ngroups, w.skey, w.sidx, w.part, a);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_rank(hipStream_t st, bool fp64, const RankArgs& r) {
+  return fp64 ? rank<double>(st, r) : rank<float>(st, r);
 }
 
 size_t rank_work_elems(int lam) {
@@ -520,8 +619,8 @@ hipError_t launch_recombine(hipStream_t st, bool fp64, int n, int lam, int mu, c
                             int ld, const int32_t* order, const double* w, const double* sqrtw, void* Ysel,
                             int ldsel, double* part_yw, double* part_zw, int* nchunks) {
   (void)lam;
-  *nchunks = ceil_div(mu, 64);
-  dim3 grid(ceil_div(n, 256), *nchunks);
+  *nchunks = ceil_div(mu, kRecRanks);
+  dim3 grid(ceil_div(n, kRecRows), *nchunks);
   if (fp64)
     k_recombine<double><<<grid, 256, 0, st>>>(n, mu, static_cast<const double*>(Y),
                                               static_cast<const double*>(Z), ld, order, w, sqrtw,
@@ -533,35 +632,28 @@ hipError_t launch_recombine(hipStream_t st, bool fp64, int n, int lam, int mu, c
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_yz(hipStream_t st, int n, int nchunks, const double* part_yw, const double* part_zw,
-                            double* yw, double* zw) {
-  k_reduce_yz<<<ceil_div(n, 256), 256, 0, st>>>(n, nchunks, part_yw, part_zw, yw, zw);
+hipError_t launch_bz(hipStream_t st, int n, const double* B, int ldb, int nchunks, const double* part_yw,
+                     const double* part_zw, double* yw, double* zw, double* bz, int* bz_chunks) {
+  const bool here = n <= kMvOneMax && nchunks * n <= kSumHere;
+  if (!here) k_reduce_yz<<<ceil_div(n, 256), 256, 0, st>>>(n, nchunks, part_yw, part_zw, yw, zw);
+  if (n <= kMvOneMax) {
+    k_bz<<<ceil_div(n, kMvRows), 256, 0, st>>>(n, B, ldb, here ? nchunks : 0, part_yw, part_zw, zw, yw, bz);
+    *bz_chunks = 1;
+  } else {
+    *bz_chunks = ceil_div(n, 64);
+    k_matvec<<<dim3(ceil_div(n, 256), *bz_chunks), 256, 0, st>>>(n, B, ldb, zw, nullptr, bz);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_matvec(hipStream_t st, int n, const double* B, int ldb, const double* x, double* part,
-                         int* nchunks) {
-  *nchunks = ceil_div(n, 64);
-  dim3 grid(ceil_div(n, 256), *nchunks);
-  k_matvec<<<grid, 256, 0, st>>>(n, B, ldb, x, part);
-  return hipGetLastError();
-}
-
-hipError_t launch_vec_update(hipStream_t st, const KParams& kp, int nchunks, const double* part_bz,
-                             const double* yw, double* m, double* ps, double* pc, DevScalars* sc) {
-  k_vec_update<<<1, 1024, 0, st>>>(kp, nchunks, part_bz, yw, m, ps, pc, sc);
-  return hipGetLastError();
-}
-
-hipError_t launch_best(hipStream_t st, bool fp64, int n, int lam, const double* f, const int32_t* order,
-                       const void* Y, int ldy, const double* m, double* x_best, double* hist, int hist_len,
-                       DevScalars* sc) {
-  if (fp64)
-    k_best<double><<<1, 256, 0, st>>>(n, lam, f, order, static_cast<const double*>(Y), ldy, m, x_best, hist,
-                                      hist_len, sc);
+hipError_t launch_vec_update(hipStream_t st, const KParams& kp, const double* bz, int bz_chunks, const double* yw, double* m,
+                             double* ps, double* pc, DevScalars* sc) {
+  if (kp.n <= 64)
+    k_vec_update<64><<<1, 64, 0, st>>>(kp, bz, bz_chunks, yw, m, ps, pc, sc);
+  else if (kp.n <= 256)
+    k_vec_update<256><<<1, 256, 0, st>>>(kp, bz, bz_chunks, yw, m, ps, pc, sc);
   else
-    k_best<float><<<1, 256, 0, st>>>(n, lam, f, order, static_cast<const float*>(Y), ldy, m, x_best, hist,
-                                     hist_len, sc);
+    k_vec_update<1024><<<1, 1024, 0, st>>>(kp, bz, bz_chunks, yw, m, ps, pc, sc);
   return hipGetLastError();
 }
 
@@ -572,15 +664,14 @@ hipError_t launch_stop(hipStream_t st, const KParams& kp, const StopParams& sp, 
   return hipGetLastError();
 }
 
-hipError_t launch_shift(hipStream_t st, int n, const double* R, int ldr, const double* m, const double* xstar,
-                        double* u, double* part, double* d) {
-  k_sub<<<ceil_div(n, 256), 256, 0, st>>>(n, m, xstar, R ? u : d);
-  if (R) {
-    const int nch = ceil_div(n, 64);
-    dim3 grid(ceil_div(n, 256), nch);
-    k_matvec<<<grid, 256, 0, st>>>(n, R, ldr, u, part);
-    k_reduce_vec<<<ceil_div(n, 256), 256, 0, st>>>(n, nch, part, d);
+hipError_t launch_shift(hipStream_t st, const ShiftArgs& a) {
+  if (!a.R || a.n <= kMvOneMax) {
+    k_shift<<<shift_blocks(a.n, a.R != nullptr), 256, 0, st>>>(a);
+    return hipGetLastError();
   }
+  const int nch = ceil_div(a.n, 64), rows = ceil_div(a.n, 256);
+  k_matvec<<<dim3(rows, nch), 256, 0, st>>>(a.n, a.R, a.ldr, a.m, a.xstar, a.part);
+  k_reduce_vec<<<rows, 256, 0, st>>>(a.n, nch, a.part, a.d);
   return hipGetLastError();
 }
 
@@ -690,6 +781,10 @@ __global__ void __launch_bounds__(256) k_sep_eigen(int n, const double* __restri
   }
 }
 
+__device__ __forceinline__ BestArgs<float> best_args(const GFront& e) {
+  return BestArgs<float>{e.n, e.lam, e.Y, e.ldn, e.m, e.x_best, e.hist, e.hist_len, e.sc, e.order};
+}
+
 // ---- the update steps of a grouped front (one launch per step for all
 // descents; workgroup w of descent i is local block w - off[i], split into
 // (bx, by) by the descent's own grid width)
@@ -698,33 +793,38 @@ __global__ void __launch_bounds__(256) kg_update256(int kind, const GFront* __re
   const int i = group_find(off, count, blockIdx.x);
   const GFront& e = g[i];
   const int w = blockIdx.x - off[i];
-  const int gx = (e.n + 255) / 256;
   switch (kind) {
-    case GF_SUB: sub_body(w, e.n, e.m, e.xstar, e.u); break;
-    case GF_RMATVEC: matvec_body(w % gx, w / gx, e.n, e.Rd, e.ldn, e.u, e.part_bz); break;
-    case GF_RVEC: reduce_vec_body(w, e.n, (e.n + 63) / 64, e.part_bz, e.d); break;
-    case GF_RANK: {
+    case GF_SHIFT: shift_body(w, ShiftArgs{e.n, e.Rd, e.ldn, e.m, e.xstar, e.d, nullptr}); break;
+    case GF_SORT: {
       const RankWork rw = rank_work_of(e.rank_work, e.lam);
-      chunk_sort_body(w, e.f, e.lam, rw.skey, rw.sidx);
+      sort_body<float>(w, rw.nchunks, e.partial, e.fit_tiles, e.f, rw.skey, rw.sidx, best_args(e));
       break;
     }
     case GF_MERGE: {
       const RankWork rw = rank_work_of(e.rank_work, e.lam);
-      merge_count_body(w % rw.nchunks, w / rw.nchunks, rw.nchunks, rw.skey, rw.sidx, e.lam, rw.part);
+      merge_body<float>(w % rw.nchunks, w / rw.nchunks, rw.nchunks, rw.skey, rw.sidx, rw.part, best_args(e));
       break;
     }
     case GF_SCATTER: {
       const RankWork rw = rank_work_of(e.rank_work, e.lam);
-      merge_scatter_body(w, rw.nchunks > 1 ? rw.ngroups : 0, rw.sidx, e.lam, rw.part, e.order);
+      scatter_body<float>(w, rw.ngroups, rw.skey, rw.sidx, rw.part, best_args(e));
       break;
     }
-    case GF_BEST: best_body<float>(e.n, e.lam, e.f, e.order, e.Y, e.ldn, e.m, e.x_best, e.hist, e.hist_len, e.sc); break;
-    case GF_RECOMB:
+    case GF_RECOMB: {
+      const int gx = (e.n + kRecRows - 1) / kRecRows;
       recombine_body<float>(w % gx, w / gx, e.n, e.mu, e.Y, e.Z, e.ldn, e.order, e.w, e.sqrtw, e.Ysel, e.ldn,
                             e.part_yw, e.part_zw);
       break;
-    case GF_REDYZ: reduce_yz_body(w, e.n, (e.mu + 63) / 64, e.part_yw, e.part_zw, e.yw, e.zw); break;
-    case GF_BMATVEC: matvec_body(w % gx, w / gx, e.n, e.B, e.ldn, e.zw, e.part_bz); break;
+    }
+    case GF_REDYZ:
+      reduce_yz_body(w, e.n, (e.mu + kRecRanks - 1) / kRecRanks, e.part_yw, e.part_zw, e.yw, e.zw);
+      break;
+    case GF_BZ: {
+      const int nch = (e.mu + kRecRanks - 1) / kRecRanks;
+      bz_body(w, e.n, e.B, e.ldn, static_cast<int64_t>(nch) * e.n <= kSumHere ? nch : 0, e.part_yw, e.part_zw, e.zw,
+              e.yw, e.bz);
+      break;
+    }
     case GF_POLAR:
       if (due_mask_bit(mask, i)) polar_body(w, e.n, e.B, e.ldn, e.T, e.ldn);
       break;
@@ -737,7 +837,7 @@ __global__ void __launch_bounds__(1024) kg_vec_update(const GFront* __restrict__
                                                       int count) {
   const int i = group_find(off, count, blockIdx.x);
   const GFront& e = g[i];
-  vec_update_body(e.kp, (e.n + 63) / 64, e.part_bz, e.yw, e.m, e.ps, e.pc, e.sc);
+  vec_update_body<1024>(e.kp, e.bz, 1, e.yw, e.m, e.ps, e.pc, e.sc);
 }
 
 hipError_t launch_group_update(hipStream_t st, int kind, const GFront* g, const int* off, int count, int wgs,
@@ -757,6 +857,11 @@ int rank_chunks(int lam) { return ceil_div(lam, kSortChunk); }
 int rank_merge_wgs(int lam) {
   const int nch = ceil_div(lam, kSortChunk);
   return nch > 1 ? nch * ceil_div(nch, kMergeGroup) : 0;
+}
+int rank_scatter_wgs(int lam) { return rank_chunks(lam) > kMergeGroup ? rank_chunks(lam) : 0; }
+int recombine_wgs(int n, int mu) { return ceil_div(n, kRecRows) * ceil_div(mu, kRecRanks); }
+int reduce_yz_wgs(int n, int mu) {
+  return static_cast<int64_t>(ceil_div(mu, kRecRanks)) * n <= kSumHere ? 0 : ceil_div(n, 256);
 }
 
 hipError_t launch_active_cols(hipStream_t st, bool fp64, int n, int lam, int mu, const void* Y, const void* Z, int ld,
