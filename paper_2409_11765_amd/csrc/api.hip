@@ -398,7 +398,7 @@ int alloc_pop(cmaes* h) {
   free_pop_buffers(h);
   const size_t e = esz(h);
   int rc = 0;
-  const int row_tiles = ceil_div(n, 64);
+  const int row_tiles = ceil_div(n, h->fp64 ? kMinRowTile64 : 64);
   if ((rc = dev_alloc(h, &h->Z, e * ldn * lam)) || (rc = dev_alloc(h, &h->Y, e * ldn * lam)) ||
       (rc = dev_alloc(h, &h->Ysel, e * ldn * mu)) || (rc = dev_alloc(h, &h->partial, 8ull * row_tiles * lam)) ||
       (rc = dev_alloc(h, &h->part_yw, 8ull * ceil_div(mu, 64) * n)) ||

@@ -20,6 +20,7 @@
 // are bitwise reproducible.
 #include <algorithm>
 
+#include "dtile.h"
 #include "internal.h"
 
 namespace cmx {
@@ -27,7 +28,6 @@ namespace cmx {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 template <typename T>
 struct Cfg;
@@ -535,6 +535,70 @@ hipError_t run_gemm(hipStream_t st, int M, int N, int K, const T* A, int lda, co
   return hipGetLastError();
 }
 
+// C = A B in float64 while it has too few 64 x 64 tiles to fill the GPU: small
+// tiles, k split over the waves, operands straight to registers (dtile.h).  FIT:
+// the objective's terms of d + sigma A B are summed over the tile's rows instead
+// (a row tile's sums to partial[tile]).  Bound by the latency of its loads when
+// small, by the matrix cores and by L2 reads beyond.  Sampling / fitness, us, in
+// tiles of 64, 32 and 16:
+//   n = 40,   lambda = 15     7.7 / 12.7     6.4 / 8.0      6.3 / 6.4
+//   n = 200,  lambda = 19    18.0 / 25.1     8.3 / 10.3     6.4 / 6.9
+//   n = 200,  lambda = 608   18.4 / 24.8     8.7 / 10.4     7.3 / 8.0
+//   n = 333,  lambda = 1030  26.4 / 34.6    14.8 / 16.9    19.1 / 19.4
+//   n = 1000, lambda = 24    68.1 / 82.2    18.1 / 19.8    12.6 / 12.8
+//   n = 1000, lambda = 192   65.5 / 79.1    19.0 / 21.2    20.6 / 21.8
+//   n = 1000, lambda = 1536  95.2 / 110     73.0 / 79.4     133 / 134
+//   n = 1000, lambda = 3072   134 / 149      140 / 151      260 / 263
+//   n = 1000, lambda = 6144   244 / 285      273 / 295
+template <class TL, bool FIT>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_small_gemm(int M, int N, int K, const double* __restrict__ A,
+                                                               int lda, const double* __restrict__ B, int ldb,
+                                                               double* __restrict__ C, int ldc,
+                                                               EpiFitness<double> fit) {
+  __shared__ double lds[TL::LDS];
+  const int tiles_m = (M + TL::T - 1) / TL::T, t = xcd_order(blockIdx.x, gridDim.x);
+  const int m0 = (t % tiles_m) * TL::T, n0 = (t / tiles_m) * TL::T;
+  TL::template product<false, true>(lds, A, lda, B, ldb, (K + 15) / 16, m0, n0, M, N, K, true);
+  const double sigma = FIT ? fit.sc->sigma : 0.0;
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    const int row = m0 + r, col = n0 + c;
+    const double v = TL::get(lds, r, c);
+    if constexpr (FIT) {
+      double s = 0.0;
+      if (row < M) s = objective_term<double>(fit.kind, fit.d[row] + sigma * v, fit.kind == 2 ? fit.coef[row] : 1.0);
+#pragma unroll
+      for (int m = TL::T / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+      if (r == 0 && col < N) fit.partial[static_cast<int64_t>(m0 / TL::T) * fit.ldp + col] = s;
+    } else if (row < M && col < N) {
+      C[static_cast<int64_t>(col) * ldc + row] = v;
+    }
+  }
+}
+
+// from so many tiles of 64 on they are the faster ones, up to so many of 16 those
+// are (two workgroups per CU; 494 of them at n = 200, lambda = 608, 756 at n =
+// 1000, lambda = 192)
+constexpr int kSmallTiles64 = 768, kSmallTiles16 = 512;
+using Tile16 = Tile<1, 4>;
+using Tile32 = Tile<2, 4>;
+// the row tile of an M x N product
+int small_tile(int M, int N) {
+  if (ceil_div(M, 64) * ceil_div(N, 64) >= kSmallTiles64) return 64;
+  return ceil_div(M, 16) * ceil_div(N, 16) <= kSmallTiles16 ? 16 : 32;
+}
+template <bool FIT>
+hipError_t small_gemm(hipStream_t st, int tile, int M, int N, int K, const double* A, int lda, const double* B, int ldb,
+                      double* C, int ldc, const EpiFitness<double>& fit) {
+  const int tiles = ceil_div(M, tile) * ceil_div(N, tile);
+  if (tile == 16)
+    k_small_gemm<Tile16, FIT><<<tiles, Tile16::THREADS, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, fit);
+  else
+    k_small_gemm<Tile32, FIT><<<tiles, Tile32::THREADS, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, fit);
+  return hipGetLastError();
+}
+
 // Direct (unrotated) fitness: u = d + sigma * y read from Y, one block per
 // (row tile, column tile) with the same partial layout as the GEMM epilogue.
 template <typename T>
@@ -564,14 +628,18 @@ __global__ void __launch_bounds__(256) k_fitness_direct(int n, int lam, const T*
 
 hipError_t launch_sample_gemm_f64(hipStream_t st, int n, int lam, const double* BD, int ldbd, const double* Z,
                                   int ldz, double* Y, int ldy) {
+  const int tile = small_tile(n, lam);
+  if (tile != 64) return small_gemm<false>(st, tile, n, lam, n, BD, ldbd, Z, ldz, Y, ldy, EpiFitness<double>{});
   return run_gemm<double, false, false>(st, n, lam, n, BD, ldbd, Z, ldz, EpiStore<double>{Y, ldy});
 }
 
 hipError_t launch_fitness_gemm_f64(hipStream_t st, int n, int lam, const double* R, int ldr, const double* Y, int ldy,
                                    const FitnessArgs& fa, int* row_tiles) {
-  *row_tiles = ceil_div(n, Cfg<double>::BM);
+  const int tile = small_tile(n, lam);
+  *row_tiles = ceil_div(n, tile);
   EpiFitness<double> e{fa.kind, fa.d, static_cast<const double*>(fa.coef), fa.sc,
                        static_cast<double*>(fa.partial), fa.ld_partial};
+  if (tile != 64) return small_gemm<true>(st, tile, n, lam, n, R, ldr, Y, ldy, nullptr, 0, e);
   return run_gemm<double, false, false>(st, n, lam, n, R, ldr, Y, ldy, e);
 }
 

@@ -137,6 +137,8 @@ hipError_t launch_sample_gemm_f64(hipStream_t st, int n, int lam, const double* 
 size_t bf16x3_work_bytes(int n, int lam);
 hipError_t launch_sample_gemm_bf16x3(hipStream_t st, int n, int lam, const float* BD, int ldbd, const float* Z,
                                      int ldz, float* Y, int ldy, void* work, KTimer* kt, int kid);
+// (row tiles of at least kMinRowTile64 rows)
+constexpr int kMinRowTile64 = 16;
 hipError_t launch_fitness_gemm_f64(hipStream_t st, int n, int lam, const double* R, int ldr, const double* Y, int ldy,
                                    const FitnessArgs& fa, int* row_tiles);
 hipError_t launch_fitness_direct(hipStream_t st, bool fp64, int n, int lam, const void* Y, int ldy,
