@@ -290,11 +290,6 @@ void free_all(cmaes* h) {
   dev_free(h, h->ew.X1);
   dev_free(h, h->ew.X2);
   dev_free(h, h->ew.X3);
-  dev_free(h, h->ew.V2);
-  dev_free(h, h->ew.dsum);
-  dev_free(h, h->ew.rsum);
-  dev_free(h, h->ew.dv);
-  dev_free(h, h->ew.rctl);
   dev_free(h, h->ew.Q2);
   dev_free(h, h->ew.evals);
   dev_free(h, h->ew.perm);
@@ -442,14 +437,19 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.Q, 8ull * (N / 32) * 32 * 32)) || (rc = dev_alloc(h, &h->ew.T, 8 * nn)) ||
       (rc = dev_alloc(h, &h->ew.A2, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.Q2, 8ull * (N / 32) * 32 * 32)) ||
       (rc = dev_alloc(h, &h->ew.X1, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.X2, 8ull * N * N)) ||
-      (rc = dev_alloc(h, &h->ew.X3, 8ull * N * N)) || (rc = dev_alloc(h, &h->ew.V2, 8ull * N * N)) ||
-      (rc = dev_alloc(h, &h->ew.dsum, 8ull * (N / 32) * N)) ||
-      (rc = dev_alloc(h, &h->ew.rsum, 8ull * (N / 32) * N)) ||
-      (rc = dev_alloc(h, &h->ew.dv, 8ull * N)) || (rc = dev_alloc(h, &h->ew.rctl, 4ull * 16)) ||
       (rc = dev_alloc(h, &h->ew.evals, 8ull * N)) || (rc = dev_alloc(h, &h->ew.perm, 4ull * N)) ||
       (rc = dev_alloc(h, &h->ew.sign, 8ull * N)) || (rc = dev_alloc(h, &h->ew.scale, 16)) ||
       (rc = dev_alloc(h, &h->ew.status, 16)) || (rc = dev_alloc(h, &h->ew.gctl, 4ull * GC_WORDS)))
     return rc;
+  if (N > kWholeSolveN) {  // the refinement's buffers, in one block
+    const size_t NN = static_cast<size_t>(N) * N, rows = static_cast<size_t>(N / 32) * N;
+    if ((rc = dev_alloc(h, &h->ew.X3, 8 * (2 * NN + 2 * rows + N) + 64))) return rc;
+    h->ew.V2 = h->ew.X3 + NN;
+    h->ew.dsum = h->ew.V2 + NN;
+    h->ew.rsum = h->ew.dsum + rows;
+    h->ew.dv = h->ew.rsum + rows;
+    h->ew.rctl = reinterpret_cast<int*>(h->ew.dv + N);
+  }
   {
     const int q = N / 32;
     if ((rc = dev_alloc(h, &h->ew.part, 8ull * 4 * std::max(n, q * (q + 1) / 2)))) return rc;
@@ -539,7 +539,7 @@ int init_descent(cmaes* h, bool fresh) {
   h->ew.last_sweeps = 0;
   h->ew.last_closed = false;
   h->ew.last_steps = 0;
-  h->ew.last_long = kManySteps;
+  h->ew.last_long = h->ew.last_cube = kManySteps;
   refresh_stop_params(h);
   return 0;
 }
@@ -827,7 +827,7 @@ int finish_generation(cmaes* h) {
     h->ew.corrections = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
-    h->ew.last_long = kManySteps;
+    h->ew.last_long = h->ew.last_cube = kManySteps;
     h->ew.refined = true;
     h->ew.pending = false;
   }
@@ -1380,7 +1380,7 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     h->ew.last_sweeps = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
-    h->ew.last_long = kManySteps;
+    h->ew.last_long = h->ew.last_cube = kManySteps;
   }
   if (in->B || in->D)  // B D in the sampling precision
     CMX_HIP(launch_scale_columns(h->st, h->fp64, n, h->B, h->ldn, h->D, h->BD, h->ldn));
@@ -1988,7 +1988,7 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
         h->ew.last_sweeps = g.sweeps[i];
         h->ew.last_closed = false;
         h->ew.last_steps = 0;
-        h->ew.last_long = kManySteps;
+        h->ew.last_long = h->ew.last_cube = kManySteps;
         h->ew.refined = h->ew.N <= kWholeSolveN;
         h->ew.pending = false;
       }

@@ -853,13 +853,6 @@ __device__ __forceinline__ void eig_rank_body(int bx, const double* __restrict__
   }
 }
 
-__global__ void __launch_bounds__(256) k_eig_rank(const double* __restrict__ A, int stride, int n,
-                                                  int32_t* __restrict__ perm, double* __restrict__ ev,
-                                                  const int* __restrict__ status, DevScalars* __restrict__ sc) {
-  __shared__ double dg[1024];
-  eig_rank_body(blockIdx.x, A, stride, n, perm, ev, status, sc, dg);
-}
-
 // sign of each column: the entry of largest magnitude (first on ties) made positive
 __device__ __forceinline__ void colsign_body(int c, const double* __restrict__ Bn, int ld, int n,
                                              double* __restrict__ sign, double* bv, int* bi) {
@@ -889,13 +882,6 @@ __device__ __forceinline__ void colsign_body(int c, const double* __restrict__ B
   if (threadIdx.x == 0) sign[c] = Bn[static_cast<int64_t>(c) * ld + bi[0]] < 0.0 ? -1.0 : 1.0;
 }
 
-__global__ void __launch_bounds__(256) k_colsign(const double* __restrict__ Bn, int ld, int n,
-                                                 double* __restrict__ sign) {
-  __shared__ double bv[256];
-  __shared__ int bi[256];
-  colsign_body(blockIdx.x, Bn, ld, n, sign, bv, bi);
-}
-
 template <typename T>
 __device__ __forceinline__ void permute_body(int bx, int r, const double* __restrict__ Bn, int ldt, int n,
                                              const int32_t* __restrict__ perm, const double* __restrict__ ev,
@@ -911,12 +897,73 @@ __device__ __forceinline__ void permute_body(int bx, int r, const double* __rest
   BD[static_cast<int64_t>(r) * ldbd + row] = static_cast<T>(v * d);
 }
 
+// The end of one descent's eigensolve, a workgroup for each column c of V: its
+// eigenvalue's rank (ascending, ties by index, NaN last), the sign of its largest
+// entry (first on ties), then its column of B, D and B D.  One launch where status,
+// ranks, signs and the permuted copy took four (n = 200: 2 + 4.3 + 3.7 + 4 us and the
+// gaps between them, now 5); n times the n eigenvalues are read from L2.
 template <typename T>
-__global__ void __launch_bounds__(256) k_permute(const double* __restrict__ Bn, int ldt, int n,
-                                                 const int32_t* __restrict__ perm, const double* __restrict__ ev,
-                                                 const double* __restrict__ sign, double* __restrict__ B, int ldb,
-                                                 double* __restrict__ D, T* __restrict__ BD, int ldbd) {
-  permute_body<T>(blockIdx.x, blockIdx.y, Bn, ldt, n, perm, ev, sign, B, ldb, D, BD, ldbd);
+__global__ void __launch_bounds__(256) k_place_columns(const double* __restrict__ V, int ldv, int n,
+                                                       const double* __restrict__ ev, int stride, int code, int sweeps,
+                                                       int corrections, double* __restrict__ B, int ldb,
+                                                       double* __restrict__ D, T* __restrict__ BD, int ldbd,
+                                                       DevScalars* __restrict__ sc) {
+  __shared__ double bv[4];
+  __shared__ int bi[4], bc[4];
+  const int c = blockIdx.x, t = threadIdx.x;
+  const double* col = V + static_cast<int64_t>(c) * ldv;
+  const double vc = ev[static_cast<int64_t>(c) * stride];
+  int cnt = 0, arg = 0;
+  double best = -1.0;
+#pragma unroll 4
+  for (int j = t; j < n; j += 256) {
+    const double vj = ev[static_cast<int64_t>(j) * stride], a = fabs(col[j]);
+    cnt += vj < vc || (vj == vc && j < c) || (vc != vc && (vj == vj || j < c));
+    if (a > best) {
+      best = a;
+      arg = j;
+    }
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    cnt += __shfl_xor(cnt, m);
+    const double o = __shfl_xor(best, m);
+    const int oi = __shfl_xor(arg, m);
+    if (o > best || (o == best && oi < arg)) {
+      best = o;
+      arg = oi;
+    }
+  }
+  if ((t & 63) == 0) {
+    bv[t >> 6] = best;
+    bi[t >> 6] = arg;
+    bc[t >> 6] = cnt;
+  }
+  __syncthreads();
+  best = bv[0];
+  arg = bi[0];
+  cnt = bc[0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) {
+    cnt += bc[w];
+    if (bv[w] > best || (bv[w] == best && bi[w] < arg)) {
+      best = bv[w];
+      arg = bi[w];
+    }
+  }
+  const double sign = col[arg] < 0.0 ? -1.0 : 1.0, d = sqrt(fmax(vc, 0.0));
+  for (int r = t; r < n; r += 256) {
+    const double v = sign * col[r];
+    B[static_cast<int64_t>(cnt) * ldb + r] = v;
+    BD[static_cast<int64_t>(cnt) * ldbd + r] = static_cast<T>(v * d);
+  }
+  if (t != 0) return;
+  D[cnt] = d;
+  if (cnt == 0) {
+    sc->eig_ok = (vc > 0.0 && code == 1) ? 1 : 0;
+    sc->jac_sweeps = sweeps;
+    sc->jac_corr = corrections;
+  }
 }
 
 // ---- grouped eigensolve: the sweeps of many descents (one per entry of a
@@ -1180,14 +1227,6 @@ int eigen_begin(hipStream_t st, int n, const double* C, int ldc, const double* B
   return 0;
 }
 
-__global__ void k_set_status(int* status, int code, int sweeps, int corrections) {
-  if (threadIdx.x == 0) {
-    status[0] = code;
-    status[1] = sweeps;
-    status[2] = corrections;
-  }
-}
-
 void eigen_drop_graphs(EigWork& w) {
   for (auto& g : w.gx) {
     if (g) (void)hipGraphExecDestroy(g);
@@ -1304,9 +1343,13 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.thmax = (careful ? kThCareful : kThLimit) * n;  // of a first step
       const int in2 = w.Acur == w.A ? 0 : 1;
       // as many steps as had long rows in the previous solve look for them; beyond
-      // that while the last step known had some (3-4 us saved in each other one)
-      a.damp = !careful && (w.steps < w.last_long || (w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED]));
-      const int slot = (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) + (a.damp || careful ? 0 : 8);
+      // that while the last step known had some (3-4 us saved in each other one);
+      // likewise for the cube of Theta
+      const bool still = w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED];
+      a.damp = !careful && (w.steps < w.last_long || still);
+      a.cube = a.damp || careful || w.steps < w.last_cube;
+      const int slot = (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) +
+                       (a.damp || careful ? 0 : a.cube ? 8 : 14);
       if (const int rc = run(slot, [&] { return launch_refine_step(st, a, kt); })) return rc;
     }
     return 0;
@@ -1314,16 +1357,12 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
   // converged (1), sweep limit (2) or non-finite (3): V (N x N) holds
   // B_new = B_old V_rot; canonical order / signs into B, D, BD
   auto finish = [&](const double* V, const double* ev, int stride, int code, int nsweeps, int ncorr) -> int {
-    k_set_status<<<1, 64, 0, st>>>(w.status, code, nsweeps, ncorr);
-    k_eig_rank<<<ceil_div(n, 256 / kRankTPI), 256, 0, st>>>(ev, stride, n, w.perm, w.evals, w.status, sc);
-    k_colsign<<<n, 256, 0, st>>>(V, N, n, w.sign);
-    dim3 grid(ceil_div(n, 256), n);
     if (fp64_bd)
-      k_permute<double><<<grid, 256, 0, st>>>(V, N, n, w.perm, w.evals, w.sign, B, ldb, D, static_cast<double*>(BD),
-                                              ldbd);
+      k_place_columns<double><<<n, 256, 0, st>>>(V, N, n, ev, stride, code, nsweeps, ncorr, B, ldb, D,
+                                                 static_cast<double*>(BD), ldbd, sc);
     else
-      k_permute<float><<<grid, 256, 0, st>>>(V, N, n, w.perm, w.evals, w.sign, B, ldb, D, static_cast<float*>(BD),
-                                             ldbd);
+      k_place_columns<float><<<n, 256, 0, st>>>(V, N, n, ev, stride, code, nsweeps, ncorr, B, ldb, D,
+                                                static_cast<float*>(BD), ldbd, sc);
     CMX_HIP(hipGetLastError());
     w.pending = false;
     *done = true;
@@ -1378,6 +1417,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
         w.last_sweeps = w.recoveries > 0 ? w.lead : w.sweeps;
         w.last_steps = applied;
         w.last_long = w.recoveries > 0 ? kManySteps : w.hflags[RF_LONG];
+        w.last_cube = w.recoveries > 0 ? kManySteps : w.hflags[RF_CUBE];
         w.last_closed = false;
         w.refined = true;
         return finish(refined(applied), w.evals, 1, 1, w.sweeps + applied - small, small);

@@ -267,7 +267,7 @@ struct EigWork {
   int* hflags = nullptr;  // pinned host memory: [0] more sweeps needed, [1] non-finite,
                   // [2] off(A) small enough for a closing correction, [3] the last
                   // correction was rejected (its rotation was not small),
-                  // [RF_STATE .. RF_LONG] the refinement's outcome
+                  // [RF_STATE .. RF_CUBE] the refinement's outcome
   int* dflags = nullptr;  // device address of hflags (written by the convergence test)
   // progress of the eigensolve in flight
   double *Acur = nullptr, *Anext = nullptr, *Qcur = nullptr, *Qnext = nullptr;
@@ -290,21 +290,23 @@ struct EigWork {
   bool pending = false;
   int steps = 0;         // refinement steps queued so far since the last sweep
   int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
-  int last_long = kManySteps;  // how many of them had long rows (kManySteps: unknown)
+  // how many of them had long rows, and angles whose cube counts (kManySteps: unknown)
+  int last_long = kManySteps, last_cube = kManySteps;
   int recoveries = 0;    // refinements of this solve that went astray
   int lead = 0;          // sweeps before the first of them
   bool refined = false;  // the last solve ended with a refinement (B is orthogonal to rounding)
   // captured steps: [0] sweep from A, [1] from A2, [2] first sweep from A,
   // [3] from A2, [4] correction from A, [5] from A2, [6] first refinement step
   // from A, [7] from A2, [8 + 2 (S in A2) + parity] a later one, [12] a careful
-  // first one from A, [13] from A2, [14 ..] those of [6 .. 11] that leave long rows
-  hipGraphExec_t gx[20] = {};
+  // first one from A, [13] from A2, [14 ..] those of [6 .. 11] that leave long rows,
+  // [20 ..] and the cube of Theta
+  hipGraphExec_t gx[26] = {};
   hipStream_t gstream = nullptr;
 };
 // ---- refinement of a nearly diagonal solve by products (refine.hip)
 // outcome of the last step that ran (host flags; the words follow the
 // convergence flags, the stop bits and f_best)
-enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, RF_LONG = 11, kHostFlagWords = 16 };
+enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, RF_LONG = 11, RF_CUBE = 12, kHostFlagWords = 16 };
 // RS_ACTIVE: applied, more to do; RS_DONE: applied, the last; RS_REJECTED: the
 // first step's angles were too large, RS_DIVERGED: a later step's were, or V is
 // too far from orthogonal (neither is applied)
@@ -324,6 +326,7 @@ struct RefineStep {
   int par;     // the step's number mod 2
   bool first;  // S is given and V taken as orthogonal
   bool damp;   // shorten long rows of Theta
+  bool cube;   // Theta^3 / 6 where it counts
 };
 hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
 // one Newton-Schulz step on V's orthogonality, Vn = V (3 I - V^T V) / 2 (uses n, N, V, Vn, X and T)

@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
 // ---- control words of a solve's refinement.  Step j reads state[j & 1]
 // (0: run) and writes state[(j + 1) & 1] and bits[j & 1], so no workgroup
 // reads a word that its own launch writes.
-enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5, RC_TH2 = 6, RC_LONG = 8 };
+enum { RC_STATE = 0, RC_BITS = 2, RC_APPLIED = 4, RC_SMALL = 5, RC_TH2 = 6, RC_LONG = 8, RC_CUBES = 9 };
 enum { RB_APPLY = 1, RB_CUBE = 2 };
 
 // Theta damped where a row of it is long: theta_ij times min(1, c / |row i|,
@@ -302,13 +302,15 @@ __device__ __forceinline__ void make_x(double* lds, const double* __restrict__ T
 }
 
 // Decision on the step whose Theta is in place, by every workgroup alike, and
-// the lower tiles of Theta^2.  While Theta^3 counts, both triangles of Theta^2
+// the lower tiles of Theta^2.  While Theta^3 counts (and cube says that
+// k_ref_cube follows: without it the step is good to second order), both triangles of Theta^2
 // are stored and k_ref_cube forms X; else X is formed here.
 template <class TL>
 __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __restrict__ Th, int N, int n,
                                                                double* __restrict__ S2,
                                                                const double* __restrict__ part, int count, int first,
-                                                               double thmax, int par, int* __restrict__ ctl,
+                                                               double thmax, int cube, int par,
+                                                               int* __restrict__ ctl,
                                                                int* __restrict__ flags, double* __restrict__ X,
                                                                const double* __restrict__ dsum,
                                                                const double* __restrict__ dv,
@@ -340,7 +342,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
   const bool plain = !small_th && !first && th2 > kStall * th2_before && sums[2] <= kOffDone * kOffDone * sums[3];
   const bool last = (small_th || plain) && r2 <= kDoneR * kDoneR;
   const bool apply = isfinite(th2) && isfinite(r2) && (!first || th2 <= thmax) && r2 <= kRLimit * n;
-  const int bits = !apply ? 0 : RB_APPLY | (!plain && th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
+  const int bits = !apply ? 0 : RB_APPLY | (cube && !plain && th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
   if (lead) {
     const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : (last ? RS_DONE : RS_ACTIVE);
     const int applied = (first ? 0 : ctl[RC_APPLIED]) + (apply ? 1 : 0);
@@ -354,6 +356,9 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     __hip_atomic_store(&flags[RF_APPLIED], applied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int longs = th2 > kLong * n ? applied : first ? 0 : ctl[RC_LONG];
     ctl[RC_LONG] = longs;
+    const int cubes = th2 > kCubeFrom * kCubeFrom ? applied : first ? 0 : ctl[RC_CUBES];
+    ctl[RC_CUBES] = cubes;
+    __hip_atomic_store(&flags[RF_CUBE], cubes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_LONG], longs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_SMALL], small, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
@@ -418,9 +423,10 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
   k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.rsum, a.dv,
                                      a.first ? nullptr : state);
   if (a.damp) k_ref_damp<<<tiles, 256, 0, st>>>(a.Th, N, a.n, a.part, a.rsum, a.ctl, a.par, a.first ? 1 : 0);
-  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.thmax, a.par, a.ctl,
-                                                a.flags, a.X, a.dsum, a.dv, a.evals);
-  k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
+  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.thmax,
+                                                a.cube ? 1 : 0, a.par, a.ctl, a.flags, a.X, a.dsum, a.dv, a.evals);
+  if (a.cube)
+    k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, false, false>, full, TL::THREADS, st, a.V, N, a.X, N, a.n, a.Vn, N, N,
                bits, static_cast<int>(RB_APPLY), static_cast<int>(RB_APPLY));
   return hipGetLastError();
