@@ -27,13 +27,13 @@
 // device by every workgroup alike from the same partial sums, so several
 // steps can be queued behind one another; the host reads the outcome once.
 //
-// Measured at n = 1000 (us): C V 41.7, S and G 49.7, Theta 8.4, Theta^2 (with X
-// on most steps) 29.9, Theta^3 and X 23.7, V X 41.0, so about 180 a step against
-// 730 a sweep of 63 rounds; 48 TFLOP/s in the whole products (a library's
-// 1000^3 product takes 37.1), bound by the float64 matrix cores and, at one or
-// two tiles per CU, by the start of each tile's loads and the sum over the
-// waves.  At n = 200: 4.1, 4.3, 5.7, 5.9, 5.2 and 4.1, bound by latency; a sweep
-// of 13 rounds takes 150.
+// Measured at n = 1000 (us): C V 40.3, S and G 48.2, Theta 9.9 (its long rows
+// 7.3 more), Theta^2 (with X on most steps) 29.5, Theta^3 and X 32.0 where it counts, V X
+// 39.4, so about 190 a step against 730 a sweep of 63 rounds; 50 TFLOP/s in the
+// whole products (a library's 1000^3 product takes 37.1), bound by the float64
+// matrix cores and, at one or two tiles per CU, by the start of each tile's loads
+// and the sum over the waves.  At n = 200: 4.1, 4.3, 5.7, 5.9, 5.2 and 4.1, bound by
+// latency; a sweep of 13 rounds takes 150.
 #include "dtile.h"
 #include "internal.h"
 #include "refine.h"

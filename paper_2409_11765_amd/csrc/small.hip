@@ -17,11 +17,11 @@
 // Bound by one CU: at n = 64 a step takes 17 us, of which its six products
 // occupy the matrix cores for 10 (64 cycles for each of 4096 / 16 instructions a
 // product), and a sweep of 63 rounds, two barriers each, about 35.  A warm
-// solve takes 5-9 steps: 17-34 us at n = 10, 133 us at n = 64.  Against block sweeps of
-// 13 launches each with a host check between them, a whole generation went from
-// 116 to 88 us at n = 10 (lambda = 10), 315 to 167 at n = 40 (lambda = 15)
-// and 343 to 233 at n = 64 (lambda = 16); six generations of the first twelve from C = I
-// at n = 64, lambda = 16 take longer than before (532 against 497 us on average).
+// solve takes 5-9 steps: 17-34 us at n = 10, 133 us at n = 64.  Against block
+// sweeps of 13 launches each with a host check between them, a whole generation
+// went by this solve alone from 116 to 88 us at n = 10 (lambda = 10), 315 to 167
+// at n = 40 (lambda = 15) and 343 to 233 at n = 64 (lambda = 16); the first twelve
+// from C = I at n = 64, lambda = 16 took longer (532 against 497 us on average).
 #include "internal.h"
 #include "refine.h"
 
