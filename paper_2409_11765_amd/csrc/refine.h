@@ -39,20 +39,21 @@ constexpr double kOffDone = 1e-13;
 constexpr double kStall = 0.1;
 // Theta^3 / 6 is left out once ||Theta||_F is below this
 constexpr double kCubeFrom = 1e-3;
-// Entries at or below the sweeps' rotation threshold (eps = 2.2e-16 max d) get
-// no rotation.  Entries at the level of the products' rounding (0.7 sqrt(n) eps
-// each as measured for V far from the identity at n = 1000; counted up to 4
-// sqrt(n) eps) are as small as they can get: they do not count, and turn
+// Entries at the level of the products' rounding (0.7 sqrt(n) eps each, eps =
+// 2.2e-16 max d, as measured for V far from the identity at n = 1000; up to 4
+// sqrt(n) eps here) are as small as they can get: they do not count, and turn
 // nothing by more than kNoiseAngle (inside a multiple eigenvalue their angles
-// are arbitrary, and X is orthogonal only while they are small).
+// are arbitrary, and X is orthogonal only while they are small).  Between
+// separated eigenvalues they are turned, however small: left at eps, as the
+// sweeps leave them, B was off by 2.8e-13 at n = 333 and a condition of 100.
 constexpr double kNoiseAngle = 1e-6;
 __device__ __forceinline__ double noise_level(int n, double eps) { return fmax(16.0, 4.0 * sqrt(static_cast<double>(n))) * eps; }
 
 // angle of the rotation of a pair with off-diagonal entry a and eigenvalue
 // difference g; counts: whether it is above the noise
-__device__ __forceinline__ double refine_angle(double a, double g, double eps, double noise, bool& counts) {
+__device__ __forceinline__ double refine_angle(double a, double g, double noise, bool& counts) {
   counts = fabs(a) > noise;
-  if (!(fabs(a) > eps)) return 0.0;
+  if (!(fabs(a) > 0.0)) return 0.0;
   const double t = 2.0 * a / (fabs(g) + sqrt(fma(g, g, 4.0 * a * a)));
   double h = t / fma(0.28, t * t, 1.0);  // atan(t) to 0.005, exact to first order
   h = g < 0.0 ? -h : h;

@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
       const double a = sv[q] + 0.5 * rij * (dr[tx] + dc[k]);
       const double g = dr[tx] - dc[k];  // d_r - d_c: the rotation of the pair (c, r), c < r
       bool counts;
-      const double h = refine_angle(a, g, eps, noise, counts);
+      const double h = refine_angle(a, g, noise, counts);
       th = -h;  // Theta(r, c) = -Theta(c, r)
       w = h * a;  // theta_cr s: added to d_r, taken from d_c
       if (counts) th2 = fma(2.0 * h, h, th2);

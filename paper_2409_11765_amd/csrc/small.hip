@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(64 * NB * NB) kg_whole(const GEigDesc* __restr
       const double rij = -Gl[hi * LD + lo];
       const double a = Sl[hi * LD + lo] + 0.5 * rij * (dg[hi] + dg[lo]);
       bool counts;
-      const double h = refine_angle(a, dg[hi] - dg[lo], eps, noise, counts);
+      const double h = refine_angle(a, dg[hi] - dg[lo], noise, counts);
       Tl[lo * LD + hi] = h;
       Tl[hi * LD + lo] = -h;
       Sl[lo * LD + hi] = h * a;
