@@ -25,10 +25,11 @@
 //     is reduced); cosines and sines are float64 and orthogonal to rounding.
 //     Sweeps stop when the off-diagonal Frobenius norm of A falls below
 //     1e-13 of its total norm (summed per tile by the last round).  By default
-//     a solve of its own (n > 64) sweeps only until the angles that remain are
-//     moderate, and products finish it (refine.hip); with a narrower
-//     correction bound, a closing correction (below) takes the last sweep's
-//     place once the norm is below 1e-8.
+//     a solve of its own beyond n = 64 (192 with B D in float32) sweeps only
+//     while the angles are very large, and products do the rest (refine.hip);
+//     with a narrower correction bound, or up to n = 192 with B D in float32, a
+//     closing correction (below) takes the last sweep's place once the norm is
+//     below 1e-8.  Up to n = 64 the solve is small.hip's.
 //     V starts as B_old, so the rotations land straight in B = B_old V.
 //  3. D = sqrt(diag A), then the pairs are canonicalised like the
 //     oracle: ascending eigenvalues, each column's largest-magnitude entry
@@ -56,7 +57,7 @@ constexpr double kOffTol = 1e-13;
 // the angles satisfy ||Theta||_F <= EigWork::corr_max_theta (at most 2e-3)
 constexpr double kCorrOff = 1e-8;
 constexpr int kMaxCorrections = 4;  // per solve
-constexpr int kMaxSteps = 64;  // refinement steps before more sweeps
+constexpr int kMaxSteps = 64;  // refinement steps before more sweeps (40 seen, n = 1000 from C = I)
 constexpr int kMaxRecoveries = 3;  // per solve, before it is done by sweeps alone
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
