@@ -45,9 +45,10 @@ struct Tile {
   // ignored).  CLAMP: A's k is clamped to kmax; with TA that is a multiple of 4
   // past which any stored value is read, for B's zero rows; else it is the
   // number of k there are, and B's past it, whatever they hold, count as zero.
+  // TB (with CLAMP, without TA): B(k, n) is read along n.
   // Nothing is computed, and false returned, unless go (uniform; tested when the
   // first loads are under way).
-  template <bool TA, bool CLAMP>
+  template <bool TA, bool CLAMP, bool TB = false>
   __device__ static bool product(double* lds, const double* __restrict__ A, int lda, const double* __restrict__ B,
                                  int ldb, int kc, int m0, int n0, int rmax, int cmax, int kmax, bool go) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -58,7 +59,7 @@ struct Tile {
     for (int i = 0; i < MB; ++i) {
       const int row = min(m0 + 16 * i + li, rmax - 1), col = min(n0 + 16 * i + li, cmax - 1);
       pa[i] = TA ? A + static_cast<int64_t>(row) * lda + 2 * lg : A + static_cast<int64_t>(2 * lg) * lda + row;
-      pb[i] = B + static_cast<int64_t>(col) * ldb + 2 * lg;
+      pb[i] = TB ? B + static_cast<int64_t>(2 * lg) * ldb + col : B + static_cast<int64_t>(col) * ldb + 2 * lg;
     }
     doublex4 acc[MB][MB];
 #pragma unroll
@@ -85,7 +86,14 @@ struct Tile {
               f.a[i][2 * h + s] = pa[i][static_cast<int64_t>(o) * lda];
             }
           }
-          if constexpr (CLAMP && !TA) {
+          if constexpr (TB) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+              const int o = k + 8 * h + s, left = kmax - 2 * lg - o;
+              const double y = pb[i][static_cast<int64_t>(left > 0 ? o : -2 * lg) * ldb];
+              f.b[i][2 * h + s] = left > 0 ? y : 0.0;
+            }
+          } else if constexpr (CLAMP && !TA) {
             // (a pair's second element may be the first one of the padding)
             const int o = k + 8 * h, left = kmax - 2 * lg - o;
             const double2 y = *reinterpret_cast<const double2*>(pb[i] + (left > 0 ? o : -2 * lg));

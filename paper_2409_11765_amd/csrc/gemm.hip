@@ -624,6 +624,58 @@ __global__ void __launch_bounds__(256) k_fitness_direct(int n, int lam, const T*
   epi.partial[static_cast<int64_t>(m0 / C::BM) * epi.ldp + col] = sum;
 }
 
+// The whole covariance update in one launch: the lower tiles of Y Y2^T, k split
+// over the waves, and C <- a C + c1 pc pc^T + cmu times them with the mirror.  Against
+// k split over the GPU with a second launch to add it up (us, both, then tiles
+// of 16 and 48; K = lambda / 2 columns):
+//   n = 40,   lambda = 15    10.0    7.0     8.9
+//   n = 200,  lambda = 608   13.6    8.6    16.7
+//   n = 333,  lambda = 1030  16.8   10.7    22.3
+//   n = 100,  lambda = 4352  20.1   23.0    52.4   (few tiles, each with a long k)
+//   n = 700,  lambda = 2048  35.3   28.4    33.5
+//   n = 1000, lambda = 384   24.4   16.9    16.6
+//   n = 1000, lambda = 6144 117.1  128.3    78.6   (231 tiles of 48: one on every CU)
+template <class TL>
+__global__ void __launch_bounds__(TL::THREADS, 2) k_syrk_direct(int n, int K, const double* __restrict__ Y,
+                                                                const double* __restrict__ Y2, int ldy,
+                                                                double* __restrict__ C, int ldc,
+                                                                const double* __restrict__ pc, double c1, double cmu,
+                                                                const DevScalars* __restrict__ sc) {
+  __shared__ double lds[TL::LDS];
+  int tm, tn;
+  lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
+  const int m0 = tm * TL::T, n0 = tn * TL::T;
+  TL::template product<false, true, true>(lds, Y, ldy, Y2, ldy, (K + 15) / 16, m0, n0, n, n, K, true);
+  const double a = sc->c_coef;
+  double v[TL::PER];
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;
+    const int row = m0 + r, col = n0 + c;
+    v[e] = 0.0;
+    if (row >= n || col >= n || row < col) continue;
+    const int64_t at = static_cast<int64_t>(col) * ldc + row;
+    v[e] = a * C[at] + c1 * pc[row] * pc[col] + cmu * TL::get(lds, r, c);
+    C[at] = v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e;
+    lds[(idx % TL::T) * TL::PS + idx / TL::T] = v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < TL::PER; ++e) {
+    const int idx = threadIdx.x + TL::THREADS * e, r = idx % TL::T, c = idx / TL::T;  // row n0 + r, column m0 + c
+    if (m0 + c < n && n0 + r < m0 + c) C[static_cast<int64_t>(m0 + c) * ldc + n0 + r] = lds[c * TL::PS + r];
+  }
+}
+using Tile48 = Tile<3, 4>;
+// (the split stays for few tiles of a long k, and for large n in between, where it
+// costs up to 15 us of 2 ms)
+constexpr int kSyrkWideN = 850, kSyrkLongK = 1536, kSyrkShortK = 192;
+
 }  // namespace
 
 hipError_t launch_sample_gemm_f64(hipStream_t st, int n, int lam, const double* BD, int ldbd, const double* Z,
@@ -678,6 +730,15 @@ void syrk_plan_f64(int n, int K, int* ntl, int* splits, int* kspan, size_t* work
 hipError_t launch_syrk_update_f64(hipStream_t st, int n, int mu, const double* Ysel, const double* Ysel2, int ldsel,
                                   double* C, int ldc, const double* pc, double c1, double cmu, const DevScalars* sc,
                                   double* work) {
+  auto direct = [&](auto tile) {
+    using TL = decltype(tile);
+    const int side = ceil_div(n, TL::T);
+    k_syrk_direct<TL><<<side * (side + 1) / 2, TL::THREADS, 0, st>>>(n, mu, Ysel, Ysel2 ? Ysel2 : Ysel, ldsel, C, ldc,
+                                                                     pc, c1, cmu, sc);
+    return hipGetLastError();
+  };
+  if (n >= kSyrkWideN && mu >= kSyrkLongK) return direct(Tile48{});
+  if (mu <= (n < kSyrkWideN ? kSyrkLongK : kSyrkShortK)) return direct(Tile16{});
   int ntl, splits, kspan;
   size_t we;
   syrk_plan_f64(n, mu, &ntl, &splits, &kspan, &we);

@@ -3,7 +3,7 @@ sizes where they change: 32 rows to a workgroup; products of up to 512 columns i
 one launch, larger ones in chunks; sums over up to 8192 / n chunks of 64 ranks on
 the way; 256 keys to a sorted chunk, 8 chunks to a merge; the objective's shift
 beside the normals up to 1024 of their workgroups; float64 products in tiles of
-16 and 32.  One generation against the
+16 and 32, covariance updates in tiles of 16 and 48 or split.  One generation against the
 float64 oracle, to the bars of the parity tests."""
 
 import numpy as np
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("n,lam", [(31, 2), (32, 128), (33, 130), (64, 256), (65, 257), (512, 2048), (512, 2176),
-                                   (513, 512), (20, 2049), (40, 4100), (15, 17), (16, 16), (129, 1041), (127, 96)])
+                                   (513, 512), (20, 2049), (40, 4100), (15, 17), (16, 16), (129, 1041), (127, 96), (851, 301), (851, 3090)])
 def test_one_generation_at_the_edges(P, precision, n, lam):  # noqa: F811
     print(f"case front {precision} n={n} lam={lam}", flush=True)
     st = synth.random_state(n, lam, seed=n * 5 + lam, cond=50.0)
