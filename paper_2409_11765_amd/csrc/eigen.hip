@@ -1316,7 +1316,10 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
   // first step that the device rejects leaves A, V and the pair solves carried
   // over from the last sweep as they are, and the steps behind it return at once.
   auto refined = [&](int j) { return j == 0 ? w.V : j & 1 ? w.Anext : w.V2; };
+  // The outcome words are read before the first of them is queued: from then on
+  // the device writes them while the host goes on queueing.
   auto steps = [&](int count) -> int {
+    const bool still = w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED];
     for (int i = 0; i < count; ++i, ++w.steps) {
       const int par = w.steps & 1;
       RefineStep a{};
@@ -1344,9 +1347,8 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.thmax = (careful ? kThCareful : kThLimit) * n;  // of a first step
       const int in2 = w.Acur == w.A ? 0 : 1;
       // as many steps as had long rows in the previous solve look for them; beyond
-      // that while the last step known had some (3-4 us saved in each other one);
+      // that where the last step known had some (3-4 us saved in each other one);
       // likewise for the cube of Theta
-      const bool still = w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED];
       a.damp = !careful && (w.steps < w.last_long || still);
       a.cube = a.damp || careful || w.steps < w.last_cube;
       const int slot = (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) +
