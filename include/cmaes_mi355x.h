@@ -235,7 +235,10 @@ int cmaes_ipop_run(cmaes_t* h, int* descents);
 int cmaes_state(const cmaes_t* h, cmaes_state_t* out);
 
 /* Overwrite the state (test and resume hook).  n and lambda must match the
- * handle.  Clears the stop bits and the f-history of the descent. */
+ * handle.  Clears the stop bits and the f-history of the descent.  Where
+ * eigensolves sweep (see cmaes_set_eigen_correction), the sweeps queued at once
+ * and B's re-orthogonalisation follow the solves before, which the state does not
+ * hold: a descent taken up there differs by rounding from one that ran on. */
 int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in);
 
 /* ---- batched concurrent descents (K-Distributed, Sec. 3.2.3) ------------

@@ -442,13 +442,14 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.status, 16)) || (rc = dev_alloc(h, &h->ew.gctl, 4ull * GC_WORDS)))
     return rc;
   if (N > kWholeSolveN) {  // the refinement's buffers, in one block
-    const size_t NN = static_cast<size_t>(N) * N, rows = static_cast<size_t>(N / 32) * N;
-    if ((rc = dev_alloc(h, &h->ew.X3, 8 * (2 * NN + 2 * rows + N) + 64))) return rc;
+    const size_t NN = static_cast<size_t>(N) * N, q = N / 32, rows = q * N;
+    if ((rc = dev_alloc(h, &h->ew.X3, 8 * (2 * NN + 2 * rows + N) + 64 + 4 * q))) return rc;
     h->ew.V2 = h->ew.X3 + NN;
     h->ew.dsum = h->ew.V2 + NN;
     h->ew.rsum = h->ew.dsum + rows;
     h->ew.dv = h->ew.rsum + rows;
     h->ew.rctl = reinterpret_cast<int*>(h->ew.dv + N);
+    h->ew.reach = reinterpret_cast<unsigned*>(h->ew.rctl + 16);
   }
   {
     const int q = N / 32;
@@ -539,7 +540,7 @@ int init_descent(cmaes* h, bool fresh) {
   h->ew.last_sweeps = 0;
   h->ew.last_closed = false;
   h->ew.last_steps = 0;
-  h->ew.last_long = h->ew.last_cube = kManySteps;
+  h->ew.forget();
   refresh_stop_params(h);
   return 0;
 }
@@ -827,7 +828,7 @@ int finish_generation(cmaes* h) {
     h->ew.corrections = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
-    h->ew.last_long = h->ew.last_cube = kManySteps;
+    h->ew.forget();
     h->ew.refined = true;
     h->ew.pending = false;
   }
@@ -1374,13 +1375,15 @@ int cmaes_set_state(cmaes_t* h, const cmaes_state_t* in) {
     if (int rc = copy_in(h, h->C, in->C, h->ew.X1)) return rc;
   if (in->B) {
     if (int rc = copy_in(h, h->B, in->B, h->ew.X2)) return rc;
-    CMX_HIP(hipMemsetAsync(h->ew.gctl, 0, 4ull * GC_WORDS, h->st));  // no previous solve
     h->reorth_sweeps = 0;  // taken as orthogonal
     h->eig_uncounted = false;
+  }
+  if (in->B || in->C) {  // the solves so far say nothing of the next one
+    CMX_HIP(hipMemsetAsync(h->ew.gctl, 0, 4ull * GC_WORDS, h->st));
     h->ew.last_sweeps = 0;
     h->ew.last_closed = false;
     h->ew.last_steps = 0;
-    h->ew.last_long = h->ew.last_cube = kManySteps;
+    h->ew.forget();
   }
   if (in->B || in->D)  // B D in the sampling precision
     CMX_HIP(launch_scale_columns(h->st, h->fp64, n, h->B, h->ldn, h->D, h->BD, h->ldn));
@@ -1988,7 +1991,7 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
         h->ew.last_sweeps = g.sweeps[i];
         h->ew.last_closed = false;
         h->ew.last_steps = 0;
-        h->ew.last_long = h->ew.last_cube = kManySteps;
+        h->ew.forget();
         h->ew.refined = h->ew.N <= kWholeSolveN;
         h->ew.pending = false;
       }

@@ -40,6 +40,7 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -1316,9 +1317,9 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
   // first step that the device rejects leaves A, V and the pair solves carried
   // over from the last sweep as they are, and the steps behind it return at once.
   auto refined = [&](int j) { return j == 0 ? w.V : j & 1 ? w.Anext : w.V2; };
-  // The outcome words are read before the first of them is queued: from then on
+  // again: the first of them is a held one.  The outcome words are read before the first of them is queued: from then on
   // the device writes them while the host goes on queueing.
-  auto steps = [&](int count) -> int {
+  auto steps = [&](int count, bool again = false) -> int {
     const bool still = w.steps > 0 && !ahead && w.hflags[RF_LONG] == w.hflags[RF_APPLIED];
     for (int i = 0; i < count; ++i, ++w.steps) {
       const int par = w.steps & 1;
@@ -1336,6 +1337,7 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       a.part = w.part;
       a.dsum = w.dsum;
       a.rsum = w.rsum;
+      a.reach = w.reach;
       a.dv = w.dv;
       a.evals = w.evals;
       a.scale = w.scale;
@@ -1346,13 +1348,19 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
       const bool careful = a.first && w.recoveries > 0;
       a.thmax = (careful ? kThCareful : kThLimit) * n;  // of a first step
       const int in2 = w.Acur == w.A ? 0 : 1;
-      // as many steps as had long rows in the previous solve look for them; beyond
-      // that where the last step known had some (3-4 us saved in each other one);
-      // likewise for the cube of Theta
-      a.damp = !careful && (w.steps < w.last_long || still);
-      a.cube = a.damp || careful || w.steps < w.last_cube;
-      const int slot = (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) +
-                       (a.damp || careful ? 0 : a.cube ? 8 : 14);
+      // as many steps as had long rows in the last two solves are queued with their
+      // damping, and beyond that where the last step known had some (3-4 us saved in
+      // each other one); likewise for the cube of Theta.  A step that was to need
+      // either all the same is held and queued again.
+      a.damp = careful || still || w.steps < w.last_long;
+      a.cube = a.damp || w.steps < w.last_cube;
+      const int slot =
+          (!a.first ? 8 + 2 * in2 + par : (careful ? 12 : 6) + in2) + (a.damp ? 0 : a.cube ? 8 : 14);
+      a.again = again && i == 0;
+      if (a.again) {
+        CMX_HIP(launch_refine_step(st, a, kt));
+        continue;
+      }
       if (const int rc = run(slot, [&] { return launch_refine_step(st, a, kt); })) return rc;
     }
     return 0;
@@ -1419,11 +1427,23 @@ int eigen_step(hipStream_t st, int n, const double* C, int ldc, double* B, int l
         const int small = std::min(w.hflags[RF_SMALL], kMaxCorrections);
         w.last_sweeps = w.recoveries > 0 ? w.lead : w.sweeps;
         w.last_steps = applied;
-        w.last_long = w.recoveries > 0 ? kManySteps : w.hflags[RF_LONG];
-        w.last_cube = w.recoveries > 0 ? kManySteps : w.hflags[RF_CUBE];
+        if (w.recoveries > 0) {
+          w.forget();
+        } else {
+          const int longs = w.hflags[RF_LONG], cubes = w.hflags[RF_CUBE];
+          w.last_long = std::max(longs, std::exchange(w.seen_long, longs));
+          w.last_cube = std::max(cubes, std::exchange(w.seen_cube, cubes));
+        }
         w.last_closed = false;
         w.refined = true;
         return finish(refined(applied), w.evals, 1, 1, w.sweeps + applied - small, small);
+      }
+      if (state == RS_HELD) {
+        w.steps = applied;
+        w.last_long = std::max(w.last_long, applied + (w.hflags[RF_LONG] > applied ? 2 : 1));
+        w.last_cube = std::max(w.last_cube, applied + 2);
+        // (what the previous solve took from here on, and one more)
+        return steps(std::max(1, std::min(w.last_steps, kMaxSteps - 1) + 1 - applied), true);
       }
       if (state == RS_ACTIVE && applied < kMaxSteps)
         return steps(applied == 1 ? std::max(2, std::min(w.last_steps, kMaxSteps) - 1) : 1);

@@ -256,6 +256,7 @@ struct EigWork {
   double* V2 = nullptr;  // N*N: eigenvectors after an even number of its steps
   double* dsum = nullptr;  // (N/32) * N: the refinement's second-order eigenvalue terms
   double* rsum = nullptr;  // (N/32) * N: squared row lengths of its angles
+  unsigned* reach = nullptr;  // N/32: a bound of them for each 32 rows
   double* dv = nullptr;    // N: its first-order eigenvalues
   int* rctl = nullptr;     // its control words (16 ints, device memory)
   double* evals = nullptr;  // N
@@ -290,8 +291,12 @@ struct EigWork {
   bool pending = false;
   int steps = 0;         // refinement steps queued so far since the last sweep
   int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
-  // how many of them had long rows, and angles whose cube counts (kManySteps: unknown)
+  // how many of them had long rows, and angles whose cube counts, at most in the
+  // last two solves (kManySteps: unknown) and in the last: what is queued with the
+  // next solve's steps, not what they compute
   int last_long = kManySteps, last_cube = kManySteps;
+  int seen_long = 0, seen_cube = 0;
+  void forget() { last_long = last_cube = kManySteps; seen_long = seen_cube = 0; }
   int recoveries = 0;    // refinements of this solve that went astray
   int lead = 0;          // sweeps before the first of them
   bool refined = false;  // the last solve ended with a refinement (B is orthogonal to rounding)
@@ -308,9 +313,10 @@ struct EigWork {
 // convergence flags, the stop bits and f_best)
 enum { RF_STATE = 8, RF_APPLIED = 9, RF_SMALL = 10, RF_LONG = 11, RF_CUBE = 12, kHostFlagWords = 16 };
 // RS_ACTIVE: applied, more to do; RS_DONE: applied, the last; RS_REJECTED: the
-// first step's angles were too large, RS_DIVERGED: a later step's were, or V is
-// too far from orthogonal (neither is applied)
-enum { RS_ACTIVE = 0, RS_DONE = 1, RS_REJECTED = 2, RS_DIVERGED = 3 };
+// first step's angles were too large, RS_DIVERGED: V is too far from orthogonal at
+// a later step, RS_HELD: the step needs damp or cube and was queued without
+// (none of these is applied)
+enum { RS_ACTIVE = 0, RS_DONE = 1, RS_REJECTED = 2, RS_DIVERGED = 3, RS_HELD = 4 };
 struct RefineStep {
   int n, N;
   const double* C;
@@ -320,6 +326,7 @@ struct RefineStep {
   double* S;        // V^T C V: given to the first step, made by the others
   double *Th, *X, *T;  // N*N scratch
   double *part, *dsum, *rsum, *dv, *evals;
+  unsigned* reach;  // zero at the start of a step and at its end
   const double* scale;
   int *ctl, *flags;
   double thmax;  // largest ||Theta||_F^2 of a first step
@@ -327,6 +334,7 @@ struct RefineStep {
   bool first;  // S is given and V taken as orthogonal
   bool damp;   // shorten long rows of Theta
   bool cube;   // Theta^3 / 6 where it counts
+  bool again;  // a held step: Theta is in place
 };
 hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
 // one Newton-Schulz step on V's orthogonality, Vn = V (3 I - V^T V) / 2 (uses n, N, V, Vn, X and T)

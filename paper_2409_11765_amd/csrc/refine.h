@@ -25,8 +25,6 @@ __device__ __forceinline__ double longest_row(double th2, double before, int n) 
   if (before == 0.0) return th2 > 2.0 * n ? 0.5 : 0.75;
   return th2 > 0.9 * before ? 0.4 : th2 > 0.8 * before ? 0.55 : 0.75;
 }
-// ||Theta||_F^2 / n beyond which some row may be longer than that
-constexpr double kLong = 0.05;
 constexpr double kClip = 0.35;
 // a step is the last one once ||Theta||_F and ||R||_F are below these (what it
 // leaves of each is of the order of ||R||_F times either), or once the angles

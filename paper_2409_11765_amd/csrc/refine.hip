@@ -27,8 +27,8 @@
 // device by every workgroup alike from the same partial sums, so several
 // steps can be queued behind one another; the host reads the outcome once.
 //
-// Measured at n = 1000 (us): C V 40.3, S and G 48.2, Theta 9.9 (its long rows
-// 7.3 more), Theta^2 (with X on most steps) 29.5, Theta^3 and X 32.0 where it counts, V X
+// Measured at n = 1000 (us): C V 40.1, S and G 48.0, Theta 10.4 (its long rows
+// 7.2 more), Theta^2 (with X on most steps) 29.5, Theta^3 and X 32.0 where it counts, V X
 // 39.4, so about 190 a step against 730 a sweep of 63 rounds; 50 TFLOP/s in the
 // whole products (a library's 1000^3 product takes 37.1), bound by the float64
 // matrix cores and, at one or two tiles per CU, by the start of each tile's loads
@@ -53,13 +53,16 @@ __device__ __forceinline__ void lower_tile(int t, int& tm, int& tn) {
   tn = t - tm * (tm + 1) / 2;
 }
 
-// out = op(A) B over all tiles
+// out = op(A) B over all tiles; the first workgroup clears `count` words of `clear`
 template <class TL, bool TA, bool CLAMP>
 __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_full(const double* __restrict__ A, int lda,
                                                              const double* __restrict__ B, int N, int n,
                                                              double* __restrict__ out, int rmax, int kmax,
-                                                             const int* __restrict__ word, int mask, int want) {
+                                                             const int* __restrict__ word, int mask, int want,
+                                                             unsigned* __restrict__ clear, int count) {
   __shared__ double lds[TL::LDS];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < count; i += TL::THREADS) clear[i] = 0;
   const bool go = word == nullptr || (*word & mask) == want;
   const int side = (n + TL::T - 1) / TL::T;
   const int t = xcd_order(blockIdx.x, gridDim.x);
@@ -99,35 +102,42 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_sg(const double* __restr
   if (MIRROR && tm != tn) TL::store_mirror(lds, v, out, N, m0, n0);
 }
 
-// sums of four values over the workgroup, in a fixed order
-template <int NW>
-__device__ __forceinline__ void block_sum4(double (&v)[4], double (*red)[4]) {
+// sums of four values over the workgroup, in a fixed order, and the largest of a fifth
+template <int NW, int M>
+__device__ __forceinline__ void block_reduce(double (&v)[M], double (*red)[M]) {
+  static_assert(M == 4 || M == 5, "four sums, then one maximum");
+  auto join = [](int q, double a, double b) { return q < 4 ? a + b : fmax(a, b); };
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int q = 0; q < M; ++q)
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v[q] += __shfl_xor(v[q], m);
+    for (int m = 32; m >= 1; m >>= 1) v[q] = join(q, v[q], __shfl_xor(v[q], m));
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) red[threadIdx.x >> 6][q] = v[q];
+    for (int q = 0; q < M; ++q) red[threadIdx.x >> 6][q] = v[q];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < M; ++q) {
     v[q] = red[0][q];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v[q] += red[w][q];
+    for (int w = 1; w < NW; ++w) v[q] = join(q, v[q], red[w][q]);
   }
 }
 
 // Theta from the lower tiles of S and G (null: R = 0), 32 x 32 tiles; both
 // triangles of Theta; per tile the squared norms of Theta, R, s and d (tiles
-// of padding are zero); the first-order eigenvalues d, and per tile and row the sum over the
-// tile's columns of theta_ji s_ij, which is what rotating by Theta adds to d_i.
+// of padding are zero); the first-order eigenvalues d, and per tile and row the sums over
+// the tile's columns of theta_ji s_ij, which is what rotating by Theta adds to d_i, and
+// of theta_ij^2.  Of the latter a tile's longest row is added to reach, for each 32 rows
+// of Theta, which bounds their squared lengths: in units of 2^-16, since a sum of whole
+// numbers does not depend on which tile comes first, rounded down, so that most tiles
+// of the last steps add nothing, and k_ref_square counts one more for each tile.
 constexpr int kCT = 32;
+constexpr double kReachUnit = 1.0 / 65536.0;
 __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S, const double* __restrict__ G, int N,
                                                    int n, const double* __restrict__ scale, double* __restrict__ Th,
                                                    double* __restrict__ part, double* __restrict__ dsum,
-                                                   double* __restrict__ rsum, double* __restrict__ dv,
-                                                   const int* __restrict__ word) {
+                                                   double* __restrict__ rsum, unsigned* __restrict__ reach,
+                                                   double* __restrict__ dv, const int* __restrict__ word) {
   __shared__ double tl[kCT][kCT + 1], ts[kCT][kCT + 1];
   __shared__ double dr[kCT], dc[kCT];
   __shared__ double red[4][4];
@@ -178,7 +188,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
     ts[tx][k] = w;
   }
   double sums[4] = {th2, r2, off2, tot2};
-  block_sum4<4>(sums, red);  // (its barrier also covers tl and ts)
+  block_reduce<4>(sums, red);  // (its barrier also covers tl and ts)
   if (t < 4) part[4 * blockIdx.x + t] = t == 0 ? sums[0] : t == 1 ? sums[1] : t == 2 ? sums[2] : sums[3];
 #pragma unroll
   for (int q = 0; q < kCT / 8; ++q) {
@@ -194,8 +204,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
   // first wave; the second the same for theta^2, which has no sign)
   if (t < 128) {
     const int i = t & 31;
-    const bool sq = t >= 64, cols = (t & 32) != 0;
-    if (cols && bi == bj) return;
+    const bool sq = t >= 64, cols = (t & 32) != 0, twice = cols && bi == bj;
     double (*m)[kCT + 1] = sq ? tl : ts;
     double s = 0.0, o = 0.0;
 #pragma unroll
@@ -207,7 +216,15 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
 #pragma unroll
       for (int k = 0; k < kCT; ++k) o += sq ? m[k][i] * m[k][i] : m[k][i];
     const double sum = sq ? s + o : (cols ? -s : s - o);
-    (sq ? rsum : dsum)[static_cast<int64_t>(cols ? bi : bj) * N + (cols ? c0 : r0) + i] = sum;
+    if (!twice) (sq ? rsum : dsum)[static_cast<int64_t>(cols ? bi : bj) * N + (cols ? c0 : r0) + i] = sum;
+    if (sq) {
+      double most = sum;
+#pragma unroll
+      for (int m = 16; m >= 1; m >>= 1) most = fmax(most, __shfl_xor(most, m));
+      const unsigned units = static_cast<unsigned>(most / kReachUnit);
+      if (i == 0 && !twice && units > 0)
+        __hip_atomic_fetch_add(&reach[cols ? bj : bi], units, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
@@ -220,21 +237,28 @@ enum { RB_APPLY = 1, RB_CUBE = 2 };
 // Theta damped where a row of it is long: theta_ij times min(1, c / |row i|,
 // c / |row j|), c = longest_row, 32 x 32 tiles as in k_ref_theta.  A tile whose
 // rows and columns are all short, which is every tile in the last steps, is left
-// alone.
+// alone.  ||Theta||_F^2 is summed as by the NW waves of k_ref_square, so that both
+// see the same bits and with them the same bound.
+template <int NW>
 __global__ void __launch_bounds__(256) k_ref_damp(double* __restrict__ Th, int N, int n,
                                                   const double* __restrict__ part, const double* __restrict__ rsum,
                                                   const int* __restrict__ ctl, int par, int first) {
   __shared__ double f[2 * kCT];
-  __shared__ double red[4];
+  __shared__ double red[NW];
   if (!first && ctl[RC_STATE + par] != 0) return;
   const float before = first ? 0.0f : __int_as_float(ctl[RC_TH2 + par]);
-  double th2 = 0.0;
-  for (int i = threadIdx.x; i < gridDim.x; i += 256) th2 += part[4 * i];
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) th2 += __shfl_xor(th2, m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = th2;
+  for (int q = 0; q < NW / 4; ++q) {
+    double sum = 0.0;
+    for (int i = threadIdx.x + 256 * q; i < gridDim.x; i += 64 * NW) sum += part[4 * i];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m);
+    if ((threadIdx.x & 63) == 0) red[(threadIdx.x >> 6) + 4 * q] = sum;
+  }
   __syncthreads();
-  th2 = red[0] + red[1] + red[2] + red[3];
+  double th2 = red[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) th2 += red[w];
   const double row = longest_row(th2, before, n);
   int bi, bj;
   lower_tile(blockIdx.x, bi, bj);
@@ -302,28 +326,34 @@ __device__ __forceinline__ void make_x(double* lds, const double* __restrict__ T
 }
 
 // Decision on the step whose Theta is in place, by every workgroup alike, and
-// the lower tiles of Theta^2.  While Theta^3 counts (and cube says that
-// k_ref_cube follows: without it the step is good to second order), both triangles of Theta^2
-// are stored and k_ref_cube forms X; else X is formed here.
+// the lower tiles of Theta^2.  While Theta^3 counts, both triangles of Theta^2
+// are stored and k_ref_cube forms X; else X is formed here.  A step that may have
+// long rows without k_ref_damp queued before it, or needs Theta^3 without k_ref_cube
+// behind it, is held: the host queues it again from here on, with both (its row
+// counts are cleared by then: the held step has entered it among those with long rows).
+// So what a step computes does not depend on what was queued.
 template <class TL>
 __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __restrict__ Th, int N, int n,
                                                                double* __restrict__ S2,
-                                                               const double* __restrict__ part, int count, int first,
-                                                               double thmax, int cube, int par,
+                                                               const double* __restrict__ part, int count,
+                                                               const unsigned* __restrict__ reach, int first,
+                                                               double thmax, int damped, int cube, int again,
+                                                               int par,
                                                                int* __restrict__ ctl,
                                                                int* __restrict__ flags, double* __restrict__ X,
                                                                const double* __restrict__ dsum,
                                                                const double* __restrict__ dv,
                                                                double* __restrict__ evals) {
   __shared__ double lds[TL::LDS];
-  __shared__ double red[TL::NW][4];
+  __shared__ double red[TL::NW][5];
   const int before = first ? 0 : ctl[RC_STATE + par];
   const float th2_before = first ? 0.0f : __int_as_float(ctl[RC_TH2 + par]);
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-  double sums[4] = {0.0, 0.0, 0.0, 0.0};
+  double sums[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   for (int i = threadIdx.x; i < count; i += TL::THREADS)
 #pragma unroll
     for (int q = 0; q < 4; ++q) sums[q] += part[4 * i + q];
+  for (int i = threadIdx.x; i < N / kCT; i += TL::THREADS) sums[4] = fmax(sums[4], kReachUnit * (reach[i] + N / kCT));
   int tm, tn;
   lower_tile(xcd_order(blockIdx.x, gridDim.x), tm, tn);
   const int m0 = tm * TL::T, n0 = tn * TL::T;
@@ -335,18 +365,22 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     }
     return;
   }
-  block_sum4<TL::NW>(sums, red);
+  block_reduce<TL::NW>(sums, red);
   const double th2 = sums[0], r2 = sums[1];
   const bool small_th = th2 <= kDone * kDone;
   // rounding is left as it is, whatever its angles are: the step only takes out R
   const bool plain = !small_th && !first && th2 > kStall * th2_before && sums[2] <= kOffDone * kOffDone * sums[3];
   const bool last = (small_th || plain) && r2 <= kDoneR * kDoneR;
   const bool apply = isfinite(th2) && isfinite(r2) && (!first || th2 <= thmax) && r2 <= kRLimit * n;
-  const int bits = !apply ? 0 : RB_APPLY | (cube && !plain && th2 > kCubeFrom * kCubeFrom ? RB_CUBE : 0);
+  const double row = longest_row(th2, th2_before, n);
+  const bool rows = !plain && 1.001 * sums[4] > row * row;
+  const bool third = !plain && th2 > kCubeFrom * kCubeFrom;
+  const bool hold = apply && ((rows && !damped) || (third && !cube));
+  const int bits = !apply || hold ? 0 : RB_APPLY | (third ? RB_CUBE : 0);
   if (lead) {
-    const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : (last ? RS_DONE : RS_ACTIVE);
-    const int applied = (first ? 0 : ctl[RC_APPLIED]) + (apply ? 1 : 0);
-    const int small = (first ? 0 : ctl[RC_SMALL]) + (apply && th2 <= 4e-6 ? 1 : 0);
+    const int state = !apply ? (first ? RS_REJECTED : RS_DIVERGED) : hold ? RS_HELD : last ? RS_DONE : RS_ACTIVE;
+    const int applied = (first ? 0 : ctl[RC_APPLIED]) + (apply && !hold ? 1 : 0);
+    const int small = (first ? 0 : ctl[RC_SMALL]) + (apply && !hold && th2 <= 4e-6 ? 1 : 0);
     ctl[RC_STATE + (par ^ 1)] = state;
     ctl[RC_BITS + par] = bits;
     ctl[RC_APPLIED] = applied;
@@ -354,15 +388,15 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_square(const double* __r
     ctl[RC_SMALL] = small;
     __hip_atomic_store(&flags[RF_STATE], state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_APPLIED], applied, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    const int longs = th2 > kLong * n ? applied : first ? 0 : ctl[RC_LONG];
+    const int longs = rows ? applied + (hold ? 1 : 0) : first && !again ? 0 : ctl[RC_LONG];
     ctl[RC_LONG] = longs;
-    const int cubes = th2 > kCubeFrom * kCubeFrom ? applied : first ? 0 : ctl[RC_CUBES];
+    const int cubes = third ? applied : first ? 0 : ctl[RC_CUBES];
     ctl[RC_CUBES] = cubes;
     __hip_atomic_store(&flags[RF_CUBE], cubes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_LONG], longs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&flags[RF_SMALL], small, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  if (!apply) return;
+  if (!apply || hold) return;
   double v[TL::PER];
 #pragma unroll
   for (int e = 0; e < TL::PER; ++e) {
@@ -400,11 +434,14 @@ __global__ void __launch_bounds__(TL::THREADS, 2) k_ref_cube(const double* __res
              [&](int r, int c) { return -TL::get(lds, r, c); });
 }
 
+// the state that a held step reads, as it was before it
+__global__ void k_ref_again(int* __restrict__ state) { *state = RS_ACTIVE; }
+
 template <class TL>
 hipError_t queue_start(hipStream_t st, const RefineStep& a, KTimer* kt) {
   const int side = ceil_div(a.n, TL::T), low = side * (side + 1) / 2;
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, side * side, TL::THREADS, st, a.C, a.ldc, a.V, a.N, a.n,
-               a.T, a.n, a.ldc, nullptr, 0, 0);
+               a.T, a.n, a.ldc, nullptr, 0, 0, nullptr, 0);
   k_ref_sg<TL, true><<<low, TL::THREADS, 0, st>>>(a.V, a.T, a.N, a.n, low, a.S, nullptr, nullptr);
   return hipGetLastError();
 }
@@ -415,20 +452,24 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
   const int nt = N / kCT, tiles = nt * (nt + 1) / 2;
   int* state = a.ctl + RC_STATE + a.par;
   int* bits = a.ctl + RC_BITS + a.par;
-  if (!a.first) {
+  if (!a.first && !a.again) {
     timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, full, TL::THREADS, st, a.C, a.ldc, a.V, N, a.n, a.T,
-                 a.n, a.ldc, state, ~0, 0);  // C V (C is symmetric)
+                 a.n, a.ldc, state, ~0, 0, nullptr, 0);  // C V (C is symmetric)
     k_ref_sg<TL, false><<<2 * low, TL::THREADS, 0, st>>>(a.V, a.T, N, a.n, low, a.S, a.X, state);
   }
-  k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.rsum, a.dv,
-                                     a.first ? nullptr : state);
-  if (a.damp) k_ref_damp<<<tiles, 256, 0, st>>>(a.Th, N, a.n, a.part, a.rsum, a.ctl, a.par, a.first ? 1 : 0);
-  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.first ? 1 : 0, a.thmax,
-                                                a.cube ? 1 : 0, a.par, a.ctl, a.flags, a.X, a.dsum, a.dv, a.evals);
+  if (a.again && !a.first) k_ref_again<<<1, 1, 0, st>>>(state);
+  if (!a.again)
+    k_ref_theta<<<tiles, 256, 0, st>>>(a.S, a.first ? nullptr : a.X, N, a.n, a.scale, a.Th, a.part, a.dsum, a.rsum, a.reach,
+                                     a.dv, a.first ? nullptr : state);
+  if (a.damp)
+    k_ref_damp<TL::NW><<<tiles, 256, 0, st>>>(a.Th, N, a.n, a.part, a.rsum, a.ctl, a.par, a.first ? 1 : 0);
+  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.reach, a.first ? 1 : 0,
+                                                a.thmax, a.damp ? 1 : 0, a.cube ? 1 : 0, a.again ? 1 : 0, a.par, a.ctl,
+                                                a.flags, a.X, a.dsum, a.dv, a.evals);
   if (a.cube)
     k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, false, false>, full, TL::THREADS, st, a.V, N, a.X, N, a.n, a.Vn, N, N,
-               bits, static_cast<int>(RB_APPLY), static_cast<int>(RB_APPLY));
+               bits, static_cast<int>(RB_APPLY), static_cast<int>(RB_APPLY), a.reach, nt);
   return hipGetLastError();
 }
 

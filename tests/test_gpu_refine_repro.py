@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import synth
+from test_gpu_eigen_correction import check_decomposition
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +47,61 @@ def test_first_generations_are_reproducible(P, n, lam):
     for g, (a, b, c) in enumerate(zip(run(True), run(True), run(False))):
         same(a, b, (g, "twice"))
         same(a, c, (g, "eager"))
+
+
+def handle(P, n, lam):
+    return P.CMAES(n, lam, 1.0, seed=3, precision="fp64", objective="sphere", f_target=0.0, eigen_interval=1)
+
+
+@pytest.mark.parametrize("n", [100, 200, 400])
+def test_resumed_descent_equals_the_one_that_ran_on(P, n):
+    """A descent whose state goes out and back in before every generation: the solve
+    after that knows nothing of the solves before it, and must still do as they do."""
+    print(f"case resumed n={n}", flush=True)
+    lam = 3 * n
+    st = synth.random_state(n, lam, seed=n, cond=30.0)
+    with handle(P, n, lam) as on, handle(P, n, lam) as resumed:
+        on.set_state(st)
+        resumed.set_state(st)
+        for g in range(8):
+            on.generation()
+            resumed.set_state(resumed.state())
+            resumed.generation()
+            same(on.state(), resumed.state(), g)
+
+
+def turned(n, seed, size):
+    """A rotation by angles whose squares sum to size^2 in each row, on average."""
+    K = synth.rng(seed).standard_normal((n, n))
+    q, r = np.linalg.qr(np.eye(n) + size * (K - K.T) / np.sqrt(2 * n))
+    return q * np.sign(np.diag(r))
+
+
+@pytest.mark.parametrize("n", [96, 385, 700])
+@pytest.mark.parametrize("what", ["C", "p_c"])
+def test_large_angles_after_solves_with_none(P, n, what):
+    """A steady descent, then C replaced without B, or the evolution path, which
+    moves C far along one direction: the next solve's first step has long rows and
+    large angles that none of the solves before it had, and must treat them as a
+    solve of the same state on a new handle does."""
+    print(f"case large angles after none n={n} {what}", flush=True)
+    lam = 3 * n
+    with handle(P, n, lam) as es, handle(P, n, lam) as new:
+        es.set_state(synth.random_state(n, lam, seed=n, cond=30.0))
+        for _ in range(4):
+            es.generation()
+        s = es.state()
+        part = {"n": n, "lambda": lam, "gen": s["gen"], "sigma": s["sigma"]}
+        if what == "C":
+            Q = turned(n, n + 1, 1.0)
+            C = Q @ s["C"] @ Q.T
+            part["C"] = 0.5 * (C + C.T)
+        else:
+            part["p_c"] = 30.0 * n * synth.rng(n + 2).standard_normal(n)
+        es.set_state(part)
+        new.set_state({**s, **part})
+        es.generation()
+        new.generation()
+        a, b = es.state(), new.state()
+        check_decomposition(a)
+        same(a, b, what)
