@@ -441,7 +441,7 @@ int alloc_fixed(cmaes* h) {
       (rc = dev_alloc(h, &h->ew.sign, 8ull * N)) || (rc = dev_alloc(h, &h->ew.scale, 16)) ||
       (rc = dev_alloc(h, &h->ew.status, 16)) || (rc = dev_alloc(h, &h->ew.gctl, 4ull * GC_WORDS)))
     return rc;
-  if (N > kWholeSolveN) {  // the refinement's buffers, in one block
+  if (h->ew.may_refine() && h->opt.variant != CMAES_VARIANT_SEPARABLE) {  // the refinement's buffers, in one block
     const size_t NN = static_cast<size_t>(N) * N, q = N / 32, rows = q * N;
     if ((rc = dev_alloc(h, &h->ew.X3, 8 * (2 * NN + 2 * rows + N) + 64 + 4 * q))) return rc;
     h->ew.V2 = h->ew.X3 + NN;
@@ -1902,10 +1902,8 @@ int lockstep_generation(LockstepGroup& g, const std::vector<cmaes*>& hs) {
     if (h->obj_kind == CMAES_OBJ_NONE) return fail(CMAES_ESTATE, "every instance needs a fused objective");
   const int count = static_cast<int>(hs.size());
   if (count > kGroupMax) return fail(CMAES_EINVAL, "too many descents in one lockstep group");
-  for (cmaes* h : hs) {
+  for (cmaes* h : hs)
     if (int rc = ensure_ready(h)) return rc;
-    h->ew.grouped = true;
-  }
   const bool grouped = front_groupable(hs);
   GroupDueMask due{}, reorth{};
   bool any_reorth = false;
@@ -2057,6 +2055,7 @@ cmaes_batch_t* cmaes_batch_create(int count, const int* n, const int* lambda, co
       set_error("instance " + std::to_string(k) + ": " + why);
       return nullptr;
     }
+    h->ew.grouped = true;
     b->inst.push_back(h);
     b->restarts.push_back(0);
   }
@@ -2228,6 +2227,7 @@ cmaes_krep_t* cmaes_krep_create(int n, int lambda_start, int k_max, double sigma
       set_error("leaf " + std::to_string(j) + ": " + why);
       return nullptr;
     }
+    h->ew.grouped = true;
     r->handle[krep_slot(r, 0, j)] = h;
     r->lam0 = h->lam;
     if (krep_apply(r, h)) {

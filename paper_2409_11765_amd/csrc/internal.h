@@ -252,7 +252,8 @@ struct EigWork {
   double* T = nullptr;   // n*n scratch
   double* X1 = nullptr;  // N*N: angles, then the correction's rotation
   double* X2 = nullptr;  // N*N: products of the correction
-  double* X3 = nullptr;  // N*N: products of the refinement
+  // the refinement's, one block (null unless may_refine)
+  double* X3 = nullptr;  // N*N: products
   double* V2 = nullptr;  // N*N: eigenvectors after an even number of its steps
   double* dsum = nullptr;  // (N/32) * N: the refinement's second-order eigenvalue terms
   double* rsum = nullptr;  // (N/32) * N: squared row lengths of its angles
@@ -283,11 +284,10 @@ struct EigWork {
   double corr_max_theta = 2e-3;  // acceptance bound on ||Theta||_F (graphs capture it)
   // whether products refine what the sweeps leave: a caller that narrows the
   // closing correction's bound gets sweeps closed by corrections within it
-  bool grouped = false;  // the descent's eigensolves run in a group's (sweeps only)
+  bool grouped = false;  // the descent's eigensolves run in a group's (sweeps only), from its creation on
   bool narrow = false;   // B D is kept in float32
-  bool refines() const {
-    return correct_on && corr_max_theta >= 2e-3 && N > (narrow ? kNarrowSweepN : kWholeSolveN) && !grouped;
-  }
+  bool may_refine() const { return N > (narrow ? kNarrowSweepN : kWholeSolveN) && !grouped; }
+  bool refines() const { return correct_on && corr_max_theta >= 2e-3 && may_refine(); }
   bool pending = false;
   int steps = 0;         // refinement steps queued so far since the last sweep
   int last_steps = 0;    // steps the previous solve applied (0: none, or B replaced)
