@@ -47,8 +47,12 @@ constexpr double kCubeFrom = 1e-3;
 constexpr double kNoiseAngle = 1e-6;
 __device__ __forceinline__ double noise_level(int n, double eps) { return fmax(16.0, 4.0 * sqrt(static_cast<double>(n))) * eps; }
 
+// the power of two that takes v to [1/2, 1): angles are formed from values scaled by
+// it, whose squares then neither overflow nor vanish, and are the same bits
+__device__ __forceinline__ double unit_scale(double v) { return ldexp(1.0, min(-__builtin_amdgcn_frexp_exp(v), 1000)); }
+
 // angle of the rotation of a pair with off-diagonal entry a and eigenvalue
-// difference g; counts: whether it is above the noise
+// difference g (scaled, as the noise); counts: whether it is above the noise
 __device__ __forceinline__ double refine_angle(double a, double g, double noise, bool& counts) {
   counts = fabs(a) > noise;
   if (!(fabs(a) > 0.0)) return 0.0;

@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
     if (bi == bj && t < kCT && i < n) dv[i] = v;
   }
   __syncthreads();
-  const double eps = 2.2e-16 * scale[0], noise = noise_level(n, eps);
+  const double eps = 2.2e-16 * scale[0], unit = unit_scale(scale[0]), noise = unit * noise_level(n, eps);
   double th2 = 0.0, r2 = 0.0, off2 = 0.0, tot2 = 0.0;
 #pragma unroll
   for (int q = 0; q < kCT / 8; ++q) {
@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S,
       const double a = sv[q] + 0.5 * rij * (dr[tx] + dc[k]);
       const double g = dr[tx] - dc[k];  // d_r - d_c: the rotation of the pair (c, r), c < r
       bool counts;
-      const double h = refine_angle(a, g, noise, counts);
+      const double h = refine_angle(unit * a, unit * g, noise, counts);
       th = -h;  // Theta(r, c) = -Theta(c, r)
       w = h * a;  // theta_cr s: added to d_r, taken from d_c
       if (counts) th2 = fma(2.0 * h, h, th2);

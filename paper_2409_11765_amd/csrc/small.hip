@@ -167,6 +167,26 @@ __global__ void __launch_bounds__(64 * NB * NB) kg_whole(const GEigDesc* __restr
 #pragma unroll
     for (int r = 0; r < 4; ++r) m[(16 * bi + lk + 4 * r) * LD + 16 * bj + li] = acc[r];
   };
+  // the sums of two values over the workgroup
+  auto add_up = [&](double& x, double& y) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+      x += __shfl_xor(x, m);
+      y += __shfl_xor(y, m);
+    }
+    if (lane == 0) {
+      red[0][w] = x;
+      red[1][w] = y;
+    }
+    __syncthreads();
+    x = red[0][lane % NW];
+    y = red[1][lane % NW];
+#pragma unroll
+    for (int m = NW / 2; m >= 1; m >>= 1) {
+      x += __shfl_xor(x, m);
+      y += __shfl_xor(y, m);
+    }
+  };
   int sweeps = 0, steps = 0, tries = 0, code = 0;
   double limit = kThLimitSmall;
   while (code == 0) {
@@ -192,8 +212,8 @@ __global__ void __launch_bounds__(64 * NB * NB) kg_whole(const GEigDesc* __restr
     double dmax = fabs(dg[lane % S]);
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, m));
-    const double eps = 2.2e-16 * dmax, noise = noise_level(n, eps);
-    double th2 = 0.0, r2 = 0.0;
+    const double eps = 2.2e-16 * dmax, unit = unit_scale(dmax), noise = unit * noise_level(n, eps);
+    double th2 = 0.0, r2 = 0.0, all2 = 0.0;
     const int ne = n + (n & 1);
     for (int idx = t; idx < ne / 2 * (ne - 1); idx += NT) {
       const int i = idx / (ne - 1), j = idx - i * (ne - 1);
@@ -202,34 +222,31 @@ __global__ void __launch_bounds__(64 * NB * NB) kg_whole(const GEigDesc* __restr
       const double rij = -Gl[hi * LD + lo];
       const double a = Sl[hi * LD + lo] + 0.5 * rij * (dg[hi] + dg[lo]);
       bool counts;
-      const double h = refine_angle(a, dg[hi] - dg[lo], noise, counts);
+      const double h = refine_angle(unit * a, unit * (dg[hi] - dg[lo]), noise, counts);
       Tl[lo * LD + hi] = h;
       Tl[hi * LD + lo] = -h;
       Sl[lo * LD + hi] = h * a;
       if (counts) th2 = fma(2.0 * h, h, th2);
-      r2 = fma(2.0 * rij, rij, r2) + (a - a);  // (a - a): NaN when a is not finite
+      r2 = fma(2.0 * rij, rij, r2);
+      all2 = fma(2.0 * a, a, all2);
     }
     if (t < n) {
       const double rii = 1.0 - Gl[t * LD + t];
-      r2 = fma(rii, rii, r2) + (dg[t] - dg[t]);
+      r2 = fma(rii, rii, r2);
+      all2 = fma(dg[t], dg[t], all2);
       Tl[t * LD + t] = 0.0;
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      th2 += __shfl_xor(th2, m);
-      r2 += __shfl_xor(r2, m);
-    }
-    if (lane == 0) {
-      red[0][w] = th2;
-      red[1][w] = r2;
-    }
-    __syncthreads();
-    th2 = red[0][lane % NW];
-    r2 = red[1][lane % NW];
-#pragma unroll
-    for (int m = NW / 2; m >= 1; m >>= 1) {
-      th2 += __shfl_xor(th2, m);
-      r2 += __shfl_xor(r2, m);
+    // C is refused if it is not finite, or so large that the sum of its squares is
+    // not (as by the sweeps' test): that sum is formed only where a thread's part of
+    // it is near the end of the range, which a NaN in th2 tells all of them
+    const double part = th2;
+    if (!(all2 < 1e300)) th2 = __builtin_nan("");
+    add_up(th2, r2);
+    if (th2 != th2) {
+      th2 = part;
+      __syncthreads();
+      add_up(th2, all2);
+      if (!isfinite(all2)) r2 = all2;
     }
     bool square = true;
     if (!isfinite(th2) || !(r2 <= kRLimitSmall)) {
