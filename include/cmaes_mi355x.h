@@ -276,8 +276,8 @@ int cmaes_enable_timing(cmaes_t* h, int on);
 int cmaes_phase_times(const cmaes_t* h, double* out);
 
 /* Per-kernel device time while enabled (enabling resets the totals): the
- * float32 tile launches, the bf16 x 3 product (without its operand split) and
- * the Jacobi rounds record their own dispatch start and end timestamps; the
+ * float32 tile launches, the bf16 x 3 product (without its operand split), the
+ * products of the eigensolve's refinement and the Jacobi rounds record their own dispatch start and end timestamps; the
  * other kernels below are bracketed by HIP events.
  * cmaes_kernel_times() writes CMAES_NUM_KERNELS totals in microseconds and
  * launch counts, indexed by the CMAES_KERNEL_* values. */
@@ -288,6 +288,8 @@ int cmaes_phase_times(const cmaes_t* h, double* out);
 #define CMAES_KERNEL_SYRK 4        /* rank-mu SYRK (mixed: split-k products;    */
                                    /* float64: products + covariance epilogue)  */
 #define CMAES_KERNEL_EIG_GEMM 5    /* float64 products of the eigensolver       */
+                                   /* (n > 64; the angles between them are not  */
+                                   /* timed)                                    */
 #define CMAES_KERNEL_JACOBI 6      /* block-Jacobi rounds of the eigensolve     */
 #define CMAES_KERNEL_SYRK_EPI 7    /* mixed: split-k sum + covariance epilogue  */
 #define CMAES_NUM_KERNELS 8

@@ -442,7 +442,8 @@ hipError_t queue_start(hipStream_t st, const RefineStep& a, KTimer* kt) {
   const int side = ceil_div(a.n, TL::T), low = side * (side + 1) / 2;
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, side * side, TL::THREADS, st, a.C, a.ldc, a.V, a.N, a.n,
                a.T, a.n, a.ldc, nullptr, 0, 0, nullptr, 0);
-  k_ref_sg<TL, true><<<low, TL::THREADS, 0, st>>>(a.V, a.T, a.N, a.n, low, a.S, nullptr, nullptr);
+  timed_launch(kt, KID_EIG_GEMM, k_ref_sg<TL, true>, low, TL::THREADS, st, a.V, a.T, a.N, a.n, low, a.S, nullptr,
+               nullptr);
   return hipGetLastError();
 }
 
@@ -455,7 +456,8 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
   if (!a.first && !a.again) {
     timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, true, true>, full, TL::THREADS, st, a.C, a.ldc, a.V, N, a.n, a.T,
                  a.n, a.ldc, state, ~0, 0, nullptr, 0);  // C V (C is symmetric)
-    k_ref_sg<TL, false><<<2 * low, TL::THREADS, 0, st>>>(a.V, a.T, N, a.n, low, a.S, a.X, state);
+    timed_launch(kt, KID_EIG_GEMM, k_ref_sg<TL, false>, 2 * low, TL::THREADS, st, a.V, a.T, N, a.n, low, a.S, a.X,
+                 state);
   }
   if (a.again && !a.first) k_ref_again<<<1, 1, 0, st>>>(state);
   if (!a.again)
@@ -463,11 +465,12 @@ hipError_t queue_step(hipStream_t st, const RefineStep& a, KTimer* kt) {
                                      a.dv, a.first ? nullptr : state);
   if (a.damp)
     k_ref_damp<TL::NW><<<tiles, 256, 0, st>>>(a.Th, N, a.n, a.part, a.rsum, a.ctl, a.par, a.first ? 1 : 0);
-  k_ref_square<TL><<<low, TL::THREADS, 0, st>>>(a.Th, N, a.n, a.T, a.part, tiles, a.reach, a.first ? 1 : 0,
-                                                a.thmax, a.damp ? 1 : 0, a.cube ? 1 : 0, a.again ? 1 : 0, a.par, a.ctl,
-                                                a.flags, a.X, a.dsum, a.dv, a.evals);
+  timed_launch(kt, KID_EIG_GEMM, k_ref_square<TL>, low, TL::THREADS, st, a.Th, N, a.n, a.T, a.part, tiles, a.reach,
+               a.first ? 1 : 0, a.thmax, a.damp ? 1 : 0, a.cube ? 1 : 0, a.again ? 1 : 0, a.par, a.ctl, a.flags, a.X,
+               a.dsum, a.dv, a.evals);
   if (a.cube)
-    k_ref_cube<TL><<<low, TL::THREADS, 0, st>>>(a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum, a.dv, a.evals, bits);
+    timed_launch(kt, KID_EIG_GEMM, k_ref_cube<TL>, low, TL::THREADS, st, a.Th, a.T, N, a.n, a.first ? 0 : 1, a.X, a.dsum,
+                 a.dv, a.evals, bits);
   timed_launch(kt, KID_EIG_GEMM, k_ref_full<TL, false, false>, full, TL::THREADS, st, a.V, N, a.X, N, a.n, a.Vn, N, N,
                bits, static_cast<int>(RB_APPLY), static_cast<int>(RB_APPLY), a.reach, nt);
   return hipGetLastError();
