@@ -179,8 +179,8 @@ struct cmaes {
   uint32_t* xfer = nullptr;
   uint32_t* dxfer = nullptr;
   size_t xfer_words = 0;
-  // small n: the eigensolve runs as a grouped solve of this one descent
-  // (convergence tested on the device, several short sweeps per host wait)
+  // n <= 64: the eigensolve runs whole in one workgroup, as in a group of this one
+  // descent (its device table, and the host words that receive the outcome)
   GroupEig ge1{};
   uint64_t ge1_epoch = 0;
 };
@@ -456,7 +456,7 @@ int alloc_fixed(cmaes* h) {
     if ((rc = dev_alloc(h, &h->ew.part, 8ull * 4 * std::max(n, q * (q + 1) / 2)))) return rc;
   }
   // convergence flags (words 0-3), the stop bits (word 4), f_best (words 6-7)
-  // and the refinement's outcome (words 8-10): pinned, mapped host memory the
+  // and the refinement's outcome (words 8-12): pinned, mapped host memory the
   // device writes directly
   void* hf = nullptr;
   if (hipHostMalloc(&hf, sizeof(int) * kHostFlagWords, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)

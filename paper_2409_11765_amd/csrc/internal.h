@@ -236,10 +236,12 @@ constexpr int kManySteps = 1 << 20;
 // padded size up to which a float32 descent beyond that ends its sweeps with
 // the closing correction: refined eigenvectors are more accurate (3e-14 against
 // 3e-13 at n = 134), so the last bit of some float32 elements of B D differs, and a
-// seed leaves the trajectory that it had by 1e-8 (one seed in eight at n = 100,
-// lambda = 272, none of 40 at n = 200, lambda = 1216, where the spectrum is tighter).
-// Up to here that costs 460 against 290 us a generation (n = 100, lambda = 272; n =
-// 177, lambda = 68: 560 against 290); at n = 200 it would cost 730 against 370.
+// seed leaves the trajectory that it had by 1e-8: 5 of 40 seeds at n = 100, lambda =
+// 272, some at n = 134 and 177, none of 40 at n = 200, lambda = 1216.  The line lies
+// between those sizes; what makes the difference is the spectrum and how close ranks
+// are, not n, so it bounds the cases that were seen and no more.  Up to here it costs
+// 460 against 290 us a generation (n = 100, lambda = 272; n = 177, lambda = 68: 560
+// against 290); at n = 200 it would cost 730 against 370.
 constexpr int kNarrowSweepN = 192;
 struct EigWork {
   int N = 0;      // padded size (multiple of 32)
@@ -337,7 +339,6 @@ struct RefineStep {
   bool again;  // a held step: Theta is in place
 };
 hipError_t launch_refine_step(hipStream_t st, const RefineStep& a, KTimer* kt);
-// one Newton-Schulz step on V's orthogonality, Vn = V (3 I - V^T V) / 2 (uses n, N, V, Vn, X and T)
 // the warm start: S = V^T C V, both triangles (uses n, N, C, V, S and T)
 hipError_t launch_refine_start(hipStream_t st, const RefineStep& a, KTimer* kt);
 // Queue the warm start and the first convergence test; the host then

@@ -28,8 +28,8 @@
 // steps can be queued behind one another; the host reads the outcome once.
 //
 // Measured at n = 1000 (us): C V 40.1, S and G 48.0, Theta 10.4 (its long rows
-// 7.2 more), Theta^2 (with X on most steps) 29.5, Theta^3 and X 32.0 where it counts, V X
-// 39.4, so about 190 a step against 730 a sweep of 63 rounds; 50 TFLOP/s in the
+// 7.2 more), Theta^2 (with X where Theta^3 does not count) 29.7, Theta^3 and X 32 where it
+// does, V X 39.0, so about 190 a step against 730 a sweep of 63 rounds; 50 TFLOP/s in the
 // whole products (a library's 1000^3 product takes 37.1), bound by the float64
 // matrix cores and, at one or two tiles per CU, by the start of each tile's loads
 // and the sum over the waves.  At n = 200: 4.1, 4.3, 5.7, 5.9, 5.2 and 4.1, bound by
@@ -131,6 +131,9 @@ __device__ __forceinline__ void block_reduce(double (&v)[M], double (*red)[M]) {
 // of Theta, which bounds their squared lengths: in units of 2^-16, since a sum of whole
 // numbers does not depend on which tile comes first, rounded down, so that most tiles
 // of the last steps add nothing, and k_ref_square counts one more for each tile.
+// (0.4 us at n = 1000, nothing at n = 333; added up in k_ref_square from an array it took
+// 1.4 us there, and the number of tiles times the largest part of any of them, which
+// costs nothing, is so coarse a bound that nearly every step was damped in vain.)
 constexpr int kCT = 32;
 constexpr double kReachUnit = 1.0 / 65536.0;
 __global__ void __launch_bounds__(256) k_ref_theta(const double* __restrict__ S, const double* __restrict__ G, int N,
